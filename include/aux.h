@@ -89,11 +89,11 @@ typedef struct aux_options {
                                 are given the same window > 0 (then every choice is
                                 rule-based) */
     int graph;               /* 1: replay each CG iteration as a captured HIP graph (1) */
-    int sell_index16;        /* 1 (default): A_h's column indices may be stored as 16-bit offsets
-                                from a base per group of 64 entries, in every 64-row slice whose
-                                groups each span less than 2^16 (with sell_window 0 the setup
-                                times the layout with and without and keeps the faster);
-                                0: 32-bit columns.  Results are identical either way */
+    int sell_index16;        /* 1 (default): A_h's column indices are stored as 16-bit words (a
+                                range selector and an offset) relative to two bases per group of
+                                64 entries, in every 64-row slice whose groups each lie in two
+                                ranges of 2^15; 0: 32-bit columns.  Results are identical either
+                                way */
     int fuse_cycle;          /* 1 (default): evaluate the V-cycle with composite level operators
                                 (two passes per level: b' = P^T (I - A D^-1) b and
                                 y = (2 D^-1 - D^-1 A D^-1) b + (P - D^-1 A P) e) and the
@@ -178,25 +178,27 @@ typedef struct aux_info {
     int64_t level_nnz_P[32]; /* entries of the interpolation P_l from level l+1 to level l
                                 (0 on the coarsest level) */
     int64_t sell_slices;     /* 64-row slices of the device A_h */
-    int64_t sell_narrow_slices; /* of which store 16-bit column offsets */
+    int64_t sell_narrow_slices; /* of which have 16-bit columns that span less than 2^16 in every
+                                slot (one range; the other 16-bit slices use two) */
     int64_t sell_index_bytes; /* bytes of the column stream one product reads: 2 per stored
-                                entry of a 16-bit slice plus 4 per slot base, 4 per stored
-                                entry of a 32-bit slice */
+                                entry of a 16-bit slice plus 8 per slot for its bases, 4 per
+                                stored entry of a 32-bit slice */
     int64_t nnz_restrict;    /* entries of the fused restriction [I_R, -I_R A_h] (0 if not fused) */
     int64_t level_nnz_down[32]; /* entries of the fused down operator of level l */
     int64_t level_nnz_up[32];   /* entries of the fused up operator of level l */
     int32_t batch_tile_rows[2]; /* block products of the last batch width, FP32 and FP64: rows
                                 per LDS tile the batched autotuner chose, 0 = 64-row slices */
     double sell_tune_ms[4];  /* autotuner's time (one FP64 plus one FP32 product, ms) of the
-                                candidate layouts: global sort with 16-bit offsets, global
+                                candidate layouts: global sort with 16-bit columns, global
                                 sort 32-bit, 4096-row windows 16-bit, windows 32-bit; 0 for a
-                                candidate not timed */
+                                candidate not timed (the width is that of sell_index16) */
     /* Storage of the V-cycle's sparse operators in the single-vector solve:
      * L > 0 row-split sliced ELL with L lanes per row (64 / L rows per
      * wavefront), -L CSR with L lanes per row. */
     int32_t dense_cycle_level; /* first level evaluated by the dense cycle matrix, -1 if none */
-    int32_t sell_split;      /* 1: the single-vector A_h passes give each slice two wavefronts
-                                (32-bit layout with slices of at least 56 slots on average) */
+    int32_t sell_split;      /* 1: slices of at least 56 slots on average (wide: their
+                                single-vector passes share a slice among two to eight
+                                wavefronts; short slices do so only where they are few) */
     int32_t lanes_restrict;  /* fused restriction [I_R, -I_R A_h] (0 if not fused) */
     int32_t lanes_prolong;   /* I_P; 0: fixed-width column-major slots (its rows have 1 to 4
                                 entries; the default unless cycle_lanes forces a storage) */

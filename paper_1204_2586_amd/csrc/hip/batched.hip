@@ -92,43 +92,48 @@ __device__ __forceinline__ void bsell_slices(const DevSellView &A, XL xload, BOD
         sl_step = ((int)gridDim.x - d + 7) / 8;
     }
     for (; sl < sl_end; sl += sl_step) {
-        const int e0 = A.slice_off[sl], width = (A.slice_off[sl + 1] - e0) / kSlice;
-        const int mode = A.mode[sl];
+        const int4 m = A.meta[sl];
+        const int width = m.w;
         T acc[NP];
 #pragma unroll
         for (int p = 0; p < NP; p++) acc[p] = T(0);
         for (int j0 = 0; j0 < width; j0 += kChunk) {
             const int jn = min(kChunk, width - j0);
-            const int cnt = jn * kSlice, eb = e0 + j0 * kSlice;
-            // every load of the chunk is issued before any is waited on
-            // (indices clamped into the chunk, stores predicated)
-            constexpr int PER = kChunk * kSlice / kBlock;
-            T vt[PER];
-            int ct[PER];
-            if (mode == 0) {
+            // four consecutive entries of a row per load; every load of the
+            // chunk is issued before any is waited on (groups clamped into
+            // the slice, stores predicated)
+            constexpr int PER = kChunk / 4 * kSlice / kBlock, GW = kBlock / kSlice;
+            const int gn = (jn + 3) / 4, lane = threadIdx.x % kSlice, g0 = threadIdx.x / kSlice;
+            T vt[PER][4];
+            int ct[PER][4];
 #pragma unroll
-                for (int i = 0; i < PER; i++) {
-                    const int e = eb + min(threadIdx.x + i * kBlock, cnt - 1);
-                    vt[i] = val[e];
-                    ct[i] = A.base[e / kSlice] + (int)A.off[e];
-                }
-            } else {
-                const int *__restrict__ w = A.wide + (~mode) + (eb - e0);
+            for (int i = 0; i < PER; i++) {
+                const int g = j0 / 4 + min(g0 + i * GW, gn - 1);
+                const size_t at = ((size_t)m.x + g) * (4 * kSlice) + 4 * lane;
 #pragma unroll
-                for (int i = 0; i < PER; i++) {
-                    const int k = min(threadIdx.x + i * kBlock, cnt - 1);
-                    vt[i] = val[eb + k];
-                    ct[i] = w[k];
+                for (int k = 0; k < 4; k++) vt[i][k] = val[at + k];
+                if (m.z < 0) {
+                    const ushort4 o = *(const ushort4 *)(A.off + at);
+                    const int2 *__restrict__ bs = A.base + ((size_t)m.x + g) * 4;
+                    ct[i][0] = (o.x & 0x8000 ? bs[0].y : bs[0].x) + (o.x & 0x7fff);
+                    ct[i][1] = (o.y & 0x8000 ? bs[1].y : bs[1].x) + (o.y & 0x7fff);
+                    ct[i][2] = (o.z & 0x8000 ? bs[2].y : bs[2].x) + (o.z & 0x7fff);
+                    ct[i][3] = (o.w & 0x8000 ? bs[3].y : bs[3].x) + (o.w & 0x7fff);
+                } else {
+                    const int4 cc = *(const int4 *)(A.wide + ((size_t)m.z + g) * (4 * kSlice) + 4 * lane);
+                    ct[i][0] = cc.x, ct[i][1] = cc.y, ct[i][2] = cc.z, ct[i][3] = cc.w;
                 }
             }
             __syncthreads();                           // the previous chunk is consumed
 #pragma unroll
             for (int i = 0; i < PER; i++) {
-                const int k = threadIdx.x + i * kBlock;
-                if (k < cnt) {
-                    vs[k] = vt[i];
-                    cs[k] = ct[i];
-                }
+                const int g = g0 + i * GW;
+                if (g < gn)
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        vs[(4 * g + k) * kSlice + lane] = vt[i][k];
+                        cs[(4 * g + k) * kSlice + lane] = ct[i][k];
+                    }
             }
             __syncthreads();
             // the NP rows of a lane are independent: their gathers (for U

@@ -17,6 +17,24 @@ namespace {
 
 __device__ __forceinline__ bool stop(const int *done) { return done != nullptr && *done != 0; }
 
+// the stop flag itself, for kernels that request other words before testing it
+__device__ __forceinline__ int stop_word(const int *done)
+{
+    int d = 0;
+    if (done != nullptr) d = *done;
+    return d;
+}
+
+// Element j of a vector addressed by a 32-bit byte offset from its (uniform)
+// base: the load takes the scalar-base form, one address register instead of
+// two.  Vectors of the single-vector solve are far below 4 GiB (row numbers
+// are 32-bit, and an operator's stored entries too).
+template <typename T>
+__device__ __forceinline__ T at32(const T *__restrict__ base, int j)
+{
+    return *(const T *)((const char *)base + (unsigned)j * (unsigned)sizeof(T));
+}
+
 template <int LPR, typename A>
 __device__ __forceinline__ A group_sum(A v)
 {
@@ -25,10 +43,11 @@ __device__ __forceinline__ A group_sum(A v)
     return v;
 }
 
-// sum over the block (kBlock threads) in a fixed order; valid in thread 0
+// sum over the block (BS threads) in a fixed order; valid in thread 0
+template <int BS = kBlock>
 __device__ double block_sum(double v)
 {
-    __shared__ double red[kBlock / 64];
+    __shared__ double red[BS / 64];
     v = group_sum<64>(v);
     const int w = threadIdx.x / 64, l = threadIdx.x % 64;
     __syncthreads();
@@ -36,13 +55,14 @@ __device__ double block_sum(double v)
     __syncthreads();
     double s = 0.0;
     if (threadIdx.x == 0)
-        for (int i = 0; i < kBlock / 64; i++) s += red[i];
+        for (int i = 0; i < BS / 64; i++) s += red[i];
     return s;
 }
 
+template <int BS = kBlock>
 __device__ __forceinline__ void write_partial(double *partials, double v)
 {
-    double b = block_sum(v);
+    double b = block_sum<BS>(v);
     if (threadIdx.x == 0) partials[blockIdx.x] = b;
 }
 
@@ -55,169 +75,192 @@ inline int grid_cap(long long need)
 
 // ------------------------------------------------------------------ SELL
 
-// One wavefront per 64-row slice (or two, see sell_rows), one lane per row;
-// consecutive slices go to consecutive workgroups, which the dispatcher
-// spreads round-robin over the dies, so at any moment all dies gather from
-// the same neighbourhood of the vector and share it through the last-level
-// cache (giving each die its own contiguous range of slices measured twice as
-// slow, and no faster when the ranges are balanced by entries).
+// W wavefronts per 64-row slice, one lane per row; consecutive slices go to
+// consecutive workgroups, which the dispatcher spreads round-robin over the
+// dies, so at any moment all dies gather from the same neighbourhood of the
+// vector and share it through the last-level cache (giving each die its own
+// contiguous range of slices measured twice as slow, and no faster when the
+// ranges are balanced by entries).
 
-// MIXED = false: every slice has 32-bit columns, stored in entry order
-// (wide[e]); MIXED = true: a 16-bit or 32-bit choice per slice.
-template <typename T, bool MIXED, typename XF>
-__device__ __forceinline__ T sell_row(const DevSellView &A, int slice, int lane, XF x)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+
+// four consecutive values of a lane: one 16-byte load, or two
+__device__ __forceinline__ void load4(const float *p, float v[4])
 {
-    const T *__restrict__ val = (const T *)A.val;
-    slice = __builtin_amdgcn_readfirstlane(slice);      // one slice per wavefront
-    const int e0 = A.slice_off[slice], e1 = A.slice_off[slice + 1];
-    T s = T(0);
-    if (!MIXED) {
-        const int *__restrict__ col = A.wide;
-#pragma unroll 8
-        for (int e = e0 + lane; e < e1; e += kSlice) s += val[e] * x(col[e]);
-        return s;
-    }
-    const int mode = A.mode[slice];
-    if (mode == 0) {
-        // 16-bit offsets: the bases of 64 slots come in one vector load and
-        // are broadcast from their lanes
-        const int t0 = e0 / kSlice, width = (e1 - e0) / kSlice;
-        for (int jc = 0; jc < width; jc += kSlice) {
-            const int jn = min(kSlice, width - jc);
-            const int bl = lane < jn ? A.base[t0 + jc + lane] : 0;
-            const int eb = e0 + jc * kSlice + lane;
-#pragma unroll 4
-            for (int jj = 0; jj < jn; jj++) {
-                const int e = eb + jj * kSlice;
-                s += val[e] * x(__builtin_amdgcn_readlane(bl, jj) + (int)A.off[e]);
-            }
+    const f32x4 t = *(const f32x4 *)p;
+    v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
+}
+__device__ __forceinline__ void load4(const double *p, double v[4])
+{
+    const f64x2 a = *(const f64x2 *)p, b = *(const f64x2 *)(p + 2);
+    v[0] = a.x, v[1] = a.y, v[2] = b.x, v[3] = b.y;
+}
+
+// Groups h, h + W, ... of a slice (m its meta) for the row of this lane; four
+// accumulators, one per entry of a group.
+template <typename T, int W, typename XF>
+__device__ __forceinline__ T sell_part(const DevSellView &A, const int4 m, int lane, int h, XF x)
+{
+    const T *__restrict__ val = (const T *)A.val + (size_t)m.x * (4 * kSlice) + 4 * lane;
+    T s0 = T(0), s1 = T(0), s2 = T(0), s3 = T(0);
+    if (m.z < 0) {
+        const unsigned short *__restrict__ off = A.off + (size_t)m.x * (4 * kSlice) + 4 * lane;
+        const int2 *__restrict__ base = A.base + (size_t)m.x * 4;
+#pragma unroll 2
+        for (int g = h; g < m.y; g += W) {
+            T v[4];
+            load4(val + (size_t)g * (4 * kSlice), v);
+            const u16x4 o = *(const u16x4 *)(off + (size_t)g * (4 * kSlice));
+            const int2 *__restrict__ b = base + 4 * g;
+            s0 += v[0] * x((o.x & 0x8000 ? b[0].y : b[0].x) + (o.x & 0x7fff));
+            s1 += v[1] * x((o.y & 0x8000 ? b[1].y : b[1].x) + (o.y & 0x7fff));
+            s2 += v[2] * x((o.z & 0x8000 ? b[2].y : b[2].x) + (o.z & 0x7fff));
+            s3 += v[3] * x((o.w & 0x8000 ? b[3].y : b[3].x) + (o.w & 0x7fff));
         }
     } else {
-        const int *__restrict__ w = A.wide + ~mode;
-#pragma unroll 4
-        for (int k = lane; k < e1 - e0; k += kSlice) s += val[e0 + k] * x(w[k]);
+        const int *__restrict__ col = A.wide + (size_t)m.z * (4 * kSlice) + 4 * lane;
+#pragma unroll 2
+        for (int g = h; g < m.y; g += W) {
+            T v[4];
+            load4(val + (size_t)g * (4 * kSlice), v);
+            const i32x4 c = *(const i32x4 *)(col + (size_t)g * (4 * kSlice));
+            s0 += v[0] * x(c.x);
+            s1 += v[1] * x(c.y);
+            s2 += v[2] * x(c.z);
+            s3 += v[3] * x(c.w);
+        }
     }
-    return s;
+    return (s0 + s1) + (s2 + s3);
 }
 
+// threads of a workgroup with W wavefronts per slice, and its slices
+template <int W>
+constexpr int sell_block() { return W > 4 ? 64 * W : kBlock; }
+template <int W>
+constexpr int sell_per_block() { return sell_block<W>() / (64 * W); }
 
-// Slots [half ? ceil(w/2) : 0, half ? w : ceil(w/2)) of a 32-bit slice of
-// width w (the split form)
-template <typename T, typename XF>
-__device__ __forceinline__ T sell_row_half(const DevSellView &A, int slice, int lane, int half, XF x)
+// Every row of A: s = (A x)_row, then epi(row, s, in) with in = pre(row) the
+// row's other inputs, requested before the row's entries; nothing when the
+// stop flag `halt` is set (it is tested after the first slice's meta is
+// requested, so the two loads overlap).  With W > 1 the other wavefronts' sums
+// pass through LDS and are added in a fixed order; every thread of the block
+// then runs the same number of steps, so the barriers are uniform.
+template <typename T, int W, typename XF, typename PRE, typename EPI>
+__device__ __forceinline__ void sell_rows(const DevSellView &A, int halt, XF x, PRE pre, EPI epi)
 {
-    const T *__restrict__ val = (const T *)A.val;
-    const int *__restrict__ col = A.wide;
-    slice = __builtin_amdgcn_readfirstlane(slice);
-    const int e0 = A.slice_off[slice], e1 = A.slice_off[slice + 1];
-    const int wh = ((e1 - e0) / kSlice + 1) / 2;
-    const int b = half ? e0 + wh * kSlice : e0, end = half ? e1 : e0 + wh * kSlice;
-    T s = T(0);
-#pragma unroll 8
-    for (int e = b + lane; e < end; e += kSlice) s += val[e] * x(col[e]);
-    return s;
-}
-
-// Every row of A: s = (A x)_row, then epi(row, s).  F = 0: one wavefront per
-// 32-bit slice; F = 1: the same with per-slice 16/32-bit columns; F = 2 (wide
-// 32-bit slices): two wavefronts per slice, each summing half of its slots
-// (shorter dependent chains, twice the wavefronts in flight); the second
-// half's sums pass through LDS and are added to the first in a fixed order.
-// In the split form every thread of the block runs the same number of steps,
-// so the barriers are uniform.
-template <typename T, int F, typename XF, typename EPI>
-__device__ __forceinline__ void sell_rows(const DevSellView &A, XF x, EPI epi)
-{
-    const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6);
-    if constexpr (F != 2) {
-        for (int sl = blockIdx.x * (kBlock / 64) + w; sl < A.nslices; sl += gridDim.x * (kBlock / 64)) {
-            const T s = sell_row<T, F == 1>(A, sl, lane, x);
+    constexpr int S = sell_per_block<W>();
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int q = w / W, h = w % W;
+    int sl = (int)blockIdx.x * S + q;
+    int4 m = make_int4(0, 0, -1, 0);
+    if (sl < A.nslices) m = A.meta[sl];
+    asm volatile("" ::"s"(m.x), "s"(halt));
+    if (halt) return;
+    if constexpr (W == 1) {
+        for (; sl < A.nslices; sl += (int)gridDim.x * S) {
+            if (sl != (int)blockIdx.x * S + q) m = A.meta[sl];
             const int row = sl * kSlice + lane;
-            if (row < A.n) epi(row, s);
+            const auto in = pre(min(row, A.n - 1));
+            const T s = sell_part<T, W>(A, m, lane, 0, x);
+            if (row < A.n) epi(row, s, in);
         }
     } else {
-        constexpr int kPairs = kBlock / 128;
-        __shared__ T part[kPairs][64];
-        const int q = w >> 1, h = w & 1;
-        const int per_step = kPairs * (int)gridDim.x;
+        __shared__ T part[S][W - 1][64];
+        const int per_step = S * (int)gridDim.x;
         const int steps = (A.nslices + per_step - 1) / per_step;
-        for (int it = 0; it < steps; it++) {
-            const int sl = (it * (int)gridDim.x + (int)blockIdx.x) * kPairs + q;
+        for (int it = 0; it < steps; it++, sl += per_step) {
+            const int row = sl * kSlice + lane;
+            decltype(pre(0)) in = {};
             T s = T(0);
-            if (sl < A.nslices) s = sell_row_half<T>(A, sl, lane, h, x);
-            if (h == 1) part[q][lane] = s;
+            if (sl < A.nslices) {
+                if (it > 0) m = A.meta[sl];
+                if (h == 0) in = pre(min(row, A.n - 1));
+                s = sell_part<T, W>(A, m, lane, h, x);
+            }
+            if (it > 0) __syncthreads();           // the previous step's sums are consumed
+            if (h > 0) part[q][h - 1][lane] = s;
             __syncthreads();
             if (h == 0 && sl < A.nslices) {
-                s += part[q][lane];
-                const int row = sl * kSlice + lane;
-                if (row < A.n) epi(row, s);
+#pragma unroll
+                for (int k = 0; k < W - 1; k++) s += part[q][k][lane];
+                if (row < A.n) epi(row, s, in);
             }
-            __syncthreads();
         }
     }
 }
 
-#define FORM_SWITCH(A, CALL)                                \
-    do {                                                    \
-        if ((A).mixed) {                                    \
-            constexpr int F = 1;                            \
-            CALL;                                           \
-        } else if ((A).split) {                             \
-            constexpr int F = 2;                            \
-            CALL;                                           \
-        } else {                                            \
-            constexpr int F = 0;                            \
-            CALL;                                           \
-        }                                                   \
-    } while (0)
+#define WAVES_SWITCH(A, CALL)                                     \
+    switch ((A).waves) {                                          \
+    case 1: { constexpr int W = 1; CALL; } break;                 \
+    case 2: { constexpr int W = 2; CALL; } break;                 \
+    case 4: { constexpr int W = 4; CALL; } break;                 \
+    default: { constexpr int W = 8; CALL; } break;                \
+    }
 
+template <int W>
 inline int sell_grid(const DevSellView &A)
 {
-    return A.split && !A.mixed ? grid_cap(((long long)A.nslices + 1) / 2) : grid_cap(((long long)A.nslices + 3) / 4);
+    return grid_cap(((long long)A.nslices + sell_per_block<W>() - 1) / sell_per_block<W>());
 }
 
-template <typename T, typename TR, typename TZ, bool DOT, int F>
-__global__ __launch_bounds__(kBlock) void k_sell_sweep(DevSellView A, const T *__restrict__ dinv,
-                                                       const TR *__restrict__ rhs, const T *__restrict__ zin,
-                                                       TZ *__restrict__ zout, const double *__restrict__ rdot,
-                                                       double *partials, const int *done)
+template <typename T, typename TR, typename TZ, bool DOT, int W>
+__global__ __launch_bounds__(sell_block<W>()) void k_sell_sweep(DevSellView A, const T *__restrict__ dinv,
+                                                                const TR *__restrict__ rhs, const T *__restrict__ zin,
+                                                                TZ *__restrict__ zout, const double *__restrict__ rdot,
+                                                                double *partials, const int *done)
 {
-    if (stop(done)) return;
+    const int halt = stop_word(done);
     double acc = 0.0;
-    sell_rows<T, F>(A, [&](int j) { return zin[j]; }, [&](int row, T s) {
-        T zi = zin[row] + dinv[row] * ((T)rhs[row] - s);
-        zout[row] = (TZ)zi;
-        if (DOT) acc += rdot[row] * (double)(TZ)zi;
-    });
-    if (DOT) write_partial(partials, acc);
+    struct In {
+        T z, d, b;
+        double r;
+    };
+    sell_rows<T, W>(
+        A, halt, [&](int j) { return at32(zin, j); },
+        [&](int row) { return In{zin[row], dinv[row], (T)rhs[row], DOT ? rdot[row] : 0.0}; },
+        [&](int row, T s, const In &in) {
+            T zi = in.z + in.d * (in.b - s);
+            zout[row] = (TZ)zi;
+            if (DOT) acc += in.r * (double)(TZ)zi;
+        });
+    if (DOT) write_partial<sell_block<W>()>(partials, acc);
 }
 
-template <typename T, int F>
-__global__ __launch_bounds__(kBlock) void k_sell_resid(DevSellView A, const T *__restrict__ rhs,
-                                                       const T *__restrict__ z, T *__restrict__ res, const int *done)
+template <typename T, int W>
+__global__ __launch_bounds__(sell_block<W>()) void k_sell_resid(DevSellView A, const T *__restrict__ rhs,
+                                                                const T *__restrict__ z, T *__restrict__ res,
+                                                                const int *done)
 {
-    if (stop(done)) return;
-    sell_rows<T, F>(A, [&](int j) { return z[j]; }, [&](int row, T s) { res[row] = rhs[row] - s; });
+    sell_rows<T, W>(A, stop_word(done), [&](int j) { return at32(z, j); },
+                    [&](int row) { return rhs[row]; }, [&](int row, T s, T b) { res[row] = b - s; });
 }
 
-template <bool DOT, int F>
-__global__ __launch_bounds__(kBlock) void k_sell_spmv64(DevSellView A, const double *__restrict__ x,
-                                                        double *__restrict__ y, double *partials, const int *done)
+template <bool DOT, int W>
+__global__ __launch_bounds__(sell_block<W>()) void k_sell_spmv64(DevSellView A, const double *__restrict__ x,
+                                                                 double *__restrict__ y, double *partials,
+                                                                 const int *done)
 {
-    if (stop(done)) return;
+    const int halt = stop_word(done);
     double acc = 0.0;
-    sell_rows<double, F>(A, [&](int j) { return x[j]; }, [&](int row, double s) {
-        y[row] = s;
-        if (DOT) acc += x[row] * s;
-    });
-    if (DOT) write_partial(partials, acc);
+    sell_rows<double, W>(A, halt, [&](int j) { return at32(x, j); },
+                         [&](int row) { return DOT ? x[row] : 0.0; },
+                         [&](int row, double s, double xr) {
+                             y[row] = s;
+                             if (DOT) acc += xr * s;
+                         });
+    if (DOT) write_partial<sell_block<W>()>(partials, acc);
 }
 
-template <int F>
-__global__ __launch_bounds__(kBlock) void k_sell_residual64(DevSellView A, const double *__restrict__ f,
-                                                            const double *__restrict__ u, double *__restrict__ r)
+template <int W>
+__global__ __launch_bounds__(sell_block<W>()) void k_sell_residual64(DevSellView A, const double *__restrict__ f,
+                                                                     const double *__restrict__ u,
+                                                                     double *__restrict__ r)
 {
-    sell_rows<double, F>(A, [&](int j) { return u[j]; }, [&](int row, double s) { r[row] = f[row] - s; });
+    sell_rows<double, W>(A, 0, [&](int j) { return at32(u, j); }, [&](int row) { return f[row]; },
+                         [&](int row, double s, double b) { r[row] = b - s; });
 }
 
 template <typename T, typename TR>
@@ -586,38 +629,40 @@ template <typename T, typename TR, typename TZ>
 int sell_sweep(hipStream_t s, const DevSellView &A, const T *dinv, const TR *rhs, const T *zin, TZ *zout,
                const double *rdot, double *partials, const int *done)
 {
-    int g = sell_grid(A);
-    FORM_SWITCH(A, if (partials) hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, true, F>), dim3(g), dim3(kBlock), 0, s, A,
-                                                     dinv, rhs, zin, zout, rdot, partials, done);
-                 else hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, false, F>), dim3(g), dim3(kBlock), 0, s, A, dinv,
-                                         rhs, zin, zout, rdot, partials, done));
+    int g = 0;
+    WAVES_SWITCH(A, g = sell_grid<W>(A);
+                 if (partials) hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, true, W>), dim3(g), dim3(sell_block<W>()), 0,
+                                                  s, A, dinv, rhs, zin, zout, rdot, partials, done);
+                 else hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, false, W>), dim3(g), dim3(sell_block<W>()), 0, s, A,
+                                         dinv, rhs, zin, zout, rdot, partials, done));
     return g;
 }
 
 template <typename T>
 int sell_resid(hipStream_t s, const DevSellView &A, const T *rhs, const T *z, T *res, const int *done)
 {
-    int g = sell_grid(A);
-    FORM_SWITCH(A, hipLaunchKernelGGL((k_sell_resid<T, F>), dim3(g), dim3(kBlock), 0, s, A, rhs, z, res, done));
+    int g = 0;
+    WAVES_SWITCH(A, g = sell_grid<W>(A); hipLaunchKernelGGL((k_sell_resid<T, W>), dim3(g), dim3(sell_block<W>()), 0, s,
+                                                            A, rhs, z, res, done));
     return g;
 }
 
 int sell_spmv64(hipStream_t s, const DevSellView &A, const double *x, double *y, double *partials, const int *done)
 {
-    int g = sell_grid(A);
-    if (partials)
-        FORM_SWITCH(A, hipLaunchKernelGGL((k_sell_spmv64<true, F>), dim3(g), dim3(kBlock), 0, s, A, x, y, partials,
-                                           done));
-    else
-        FORM_SWITCH(A, hipLaunchKernelGGL((k_sell_spmv64<false, F>), dim3(g), dim3(kBlock), 0, s, A, x, y, partials,
-                                           done));
+    int g = 0;
+    WAVES_SWITCH(A, g = sell_grid<W>(A);
+                 if (partials) hipLaunchKernelGGL((k_sell_spmv64<true, W>), dim3(g), dim3(sell_block<W>()), 0, s, A, x,
+                                                  y, partials, done);
+                 else hipLaunchKernelGGL((k_sell_spmv64<false, W>), dim3(g), dim3(sell_block<W>()), 0, s, A, x, y,
+                                         partials, done));
     return g;
 }
 
 int sell_residual64(hipStream_t s, const DevSellView &A, const double *f, const double *u, double *r)
 {
-    int g = sell_grid(A);
-    FORM_SWITCH(A, hipLaunchKernelGGL((k_sell_residual64<F>), dim3(g), dim3(kBlock), 0, s, A, f, u, r));
+    int g = 0;
+    WAVES_SWITCH(A, g = sell_grid<W>(A); hipLaunchKernelGGL((k_sell_residual64<W>), dim3(g), dim3(sell_block<W>()), 0, s,
+                                                            A, f, u, r));
     return g;
 }
 

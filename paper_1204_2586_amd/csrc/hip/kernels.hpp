@@ -1,8 +1,8 @@
 // Solve-phase kernels for gfx950 (CDNA4, wave64).
 //
-// The P^k operator A_h is stored as sliced ELLPACK with 64-row slices
-// (one wavefront per slice, one lane per row, entries of a slice stored
-// column-major so every load of a wavefront is 64 consecutive words).  Its
+// The P^k operator A_h is stored as sliced ELLPACK with 64-row slices (one
+// lane per row, four consecutive entries of a row adjacent: one load of a
+// wavefront brings 1 or 2 KB of values and 512 bytes of 16-bit columns).  Its
 // rows are numbered in an internal order, sorted by length so the padding of
 // each slice stays small: either over the whole operator (a stable sort,
 // which on structured meshes groups nodes of one kind and keeps a slice's
@@ -49,16 +49,16 @@ struct DevSellView {
     int n;               // rows
     int nslices;
     int max_width;       // longest slice, in slots of 64 entries
-    int mixed;           // 0: every slice 32-bit with wide[e] the column of entry e
-    const int *slice_off;  // [nslices+1] first entry of each slice (multiple of 64)
-    // Columns.  mode[s] == 0: entry e of slot t = e / 64 has column
-    // base[t] + off[e]; mode[s] = ~w < 0: column wide[w + e - slice_off[s]].
-    const int *mode;
-    const int *base;
+    int waves;           // single-vector kernels: wavefronts per slice (1, 2, 4 or 8)
+    // per slice: first group (of 4 slots, 256 entries), groups, first group
+    // in wide or -1 (16-bit columns), slots in use
+    const int4 *meta;
+    // 16-bit columns: entry e of slot t has column
+    // (off[e] >> 15 ? base[t].y : base[t].x) + (off[e] & 0x7fff)
+    const int2 *base;
     const unsigned short *off;
-    const int *wide;
+    const int *wide;     // 32-bit columns of the other slices
     const void *val;     // double or float, padding entries are 0
-    int split;           // with mixed == 0: two wavefronts per slice (wide slices)
     // block kernels only: when set, die d (the workgroups b with b % 8 == d,
     // which the dispatcher places on die d) takes slices [die_off[d],
     // die_off[d + 1]) (9 entries); otherwise slices go round-robin

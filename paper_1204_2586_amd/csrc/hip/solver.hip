@@ -76,20 +76,40 @@ struct DevOp {   // CSR with values in both precisions
 struct DevSell {
     int n = 0, nslices = 0, max_width = 0;
     int64_t stored = 0, narrow_slices = 0, index_bytes = 0;
-    int *slice_off = nullptr, *mode = nullptr, *base = nullptr, *wide = nullptr;
+    int4 *meta = nullptr;
+    int2 *base = nullptr;
+    int *wide = nullptr;
     unsigned short *off = nullptr;
     double *v64 = nullptr;
     float *v32 = nullptr;
-    // 32-bit layouts whose slices average at least this many slots give each
-    // slice two wavefronts in the single-vector kernels: P4 (72 slots) gains
-    // 10-14 %, P3 (47) loses up to 5 % in FP64, P2 (28) keeps one
+    // slices of at least this many slots on average count as wide (aux_info)
     static constexpr int kSplitSlots = 56;
-    bool split() const { return narrow_slices == 0 && nslices > 0 && stored >= (int64_t)kSplitSlots * 64 * nslices; }
+    bool split() const { return nslices > 0 && stored >= (int64_t)kSplitSlots * 64 * nslices; }
+    // Wavefronts per slice of the single-vector passes.  One wavefront walks
+    // its groups as a chain of two dependent loads each, so where the slices
+    // are too few to fill the 1024 SIMDs, or long (P3: 12 groups, P4: 18),
+    // several wavefronts share a slice; where they are many and short the
+    // extra wavefronts only add the exchange through LDS.  Measured, FP32
+    // sweep in us with 1 / 2 / 4 / 8 wavefronts: P2 13^3 10.1 / 7.6 / 6.5 /
+    // 6.5, 26^3 14.3 / 11.1 / 9.7 / 10.8, 33^3 17.3 / 13.8 / 13.7 / 17.4,
+    // 48^3 38.3 / 37.9 / 40.4 / 48.2; P3 15^3 25.6 / 16.4 / 12.6 / 10.4, 25^3
+    // 40.3 / 26.9 / 25.9 / 28.1, 32^3 67.8 / 64.9 / 66.7 / 68.8; P4 14^3 51.9 /
+    // 32.4 / 21.8 / 18.5, 20^3 88.0 / 57.7 / 51.6 / 51.1 (event pairs of
+    // about 3 us included).  The FP64 passes order the same way.
+    int waves() const
+    {
+        const double groups = nslices ? (double)stored / (4.0 * kSlice * nslices) : 0.0;
+        for (int w = 8; w > 1; w /= 2) {
+            const int64_t most = groups < 10.0 ? 16384 : w == 8 ? 22000 : 32000;
+            if (groups >= 1.4 * w && (int64_t)nslices * w <= most) return w;
+        }
+        return 1;
+    }
     template <typename T>
     DevSellView view() const
     {
-        return {n, nslices, max_width, narrow_slices > 0 ? 1 : 0, slice_off, mode, base, off, wide,
-                std::is_same<T, float>::value ? (const void *)v32 : (const void *)v64, split() ? 1 : 0};
+        return {n, nslices, max_width, waves(), meta, base, off, wide,
+                std::is_same<T, float>::value ? (const void *)v32 : (const void *)v64};
     }
 };
 
@@ -539,34 +559,43 @@ struct aux_handle {
         d.nslices = sl.nslices;
         d.max_width = sl.max_width;
         d.stored = (int64_t)sl.val.size();
+        d.narrow_slices = sl.narrow_slices;
+        const int group = kSellGroup * sl.slice;
+        std::vector<int4> meta((size_t)sl.nslices);
         for (int s = 0; s < sl.nslices; s++) {
-            const int64_t entries = sl.slice_off[s + 1] - sl.slice_off[s];
-            d.narrow_slices += sl.mode[s] == 0;
-            d.index_bytes += sl.mode[s] == 0 ? 2 * entries + 4 * (entries / sl.slice) : 4 * entries;
+            const int entries = sl.slice_off[s + 1] - sl.slice_off[s];
+            const bool wide = sl.wide_off[s] >= 0;
+            meta[s] = make_int4(sl.slice_off[s] / group, entries / group, wide ? sl.wide_off[s] / group : -1, sl.width[s]);
+            d.index_bytes += wide ? 4 * (int64_t)entries : 2 * (int64_t)entries + 8 * (int64_t)(entries / sl.slice);
         }
-        d.slice_off = upload(sl.slice_off);
-        d.mode = upload(sl.mode);
-        d.base = upload(sl.base);
+        d.meta = upload(meta);
+        d.base = (int2 *)upload(sl.base);
         d.off = upload(sl.off);
         d.wide = upload(sl.wide);
         d.v64 = upload(sl.val);
         return d;
     }
+    // the FP32 values: the FP64 ones rounded on the device
+    float *rounded(const double *v, int64_t count)
+    {
+        float *f = dnew<float>((size_t)count);
+        to_f32_device(stream, (long long)count, v, f);
+        return f;
+    }
 
     void free_sell(DevSell &d)
     {
-        for (void *b : {(void *)d.slice_off, (void *)d.mode, (void *)d.base, (void *)d.off, (void *)d.wide,
-                        (void *)d.v64, (void *)d.v32})
+        for (void *b : {(void *)d.meta, (void *)d.base, (void *)d.off, (void *)d.wide, (void *)d.v64, (void *)d.v32})
             dfree(b);
         d = DevSell();
     }
 
     // mean time of a few products with a device layout, FP64 plus FP32 (the
     // autotuner's measure: the CG product and the preconditioner's passes)
-    double time_sell(DevSell &d, const Sell &sl)
+    double time_sell(DevSell &d)
     {
         const int n = disc.ndof;
-        d.v32 = upload(to_f32(sl.val));
+        d.v32 = rounded(d.v64, d.stored);
         double *x = dnew<double>(n), *y = dnew<double>(n);
         float *xf = dnew<float>(n), *yf = dnew<float>(n), *bf = dnew<float>(n);
         HIPCHECK(hipMemsetAsync(x, 0, (size_t)n * sizeof(double), stream));
@@ -600,31 +629,19 @@ struct aux_handle {
         // type so a slice gathers nearly contiguous entries; and a 4096-row
         // window, which keeps locality on unstructured meshes), times a few
         // products with each on the device and keeps the faster.
-        std::vector<std::pair<int, bool>> cands;
+        // (16-bit columns in every slice that allows them unless switched off:
+        // a quarter fewer bytes per FP32 product, and never slower.)
         std::vector<int> windows;
         if (opt.sell_window > 0) windows.push_back(opt.sell_window);
         else windows = {std::max(disc.ndof, 1), kSellWindow};
-        for (int win : windows) {
-            if (opt.sell_index16) cands.push_back({win, true});
-            if (!opt.sell_index16 || opt.sell_window <= 0) cands.push_back({win, false});
-        }
+        if (windows.size() == 2 && disc.ndof <= kSellWindow) windows.pop_back();   // the same layout
         double best = 1e300;
-        int same_as_32 = -1;       // a window whose 16-bit build has no 16-bit slice
-        for (auto [win, idx16] : cands) {
+        for (int win : windows) {
             Sell cand;
-            if (!idx16 && win == same_as_32) continue;   // timed already, as the 32-bit form
-            build_sell(disc.A, kSlice, win, idx16, cand);
-            if (idx16 && cands.size() > 1 &&
-                std::none_of(cand.mode.begin(), cand.mode.end(), [](int m) { return m == 0; })) {
-                // no slice takes 16-bit offsets: the build is the 32-bit layout
-                cand.base.clear();
-                cand.off.clear();
-                idx16 = false;
-                same_as_32 = win;
-            }
+            build_sell(disc.A, kSlice, win, opt.sell_index16 != 0, cand);
             DevSell d = upload_sell(cand);
-            double ms = cands.size() > 1 ? time_sell(d, cand) : 0.0;
-            tune_ms[(win == kSellWindow ? 2 : 0) + (idx16 ? 0 : 1)] = ms;
+            const double ms = windows.size() > 1 ? time_sell(d) : 0.0;
+            tune_ms[(win == kSellWindow ? 2 : 0) + (opt.sell_index16 ? 0 : 1)] = ms;
             if (ms < best) {
                 if (A.v64) free_sell(A);
                 best = ms;
@@ -983,8 +1000,7 @@ struct aux_handle {
     {
         if (child) child->ensure_fp32();
         if (fp32_ready) return;
-        ensure_host_values();
-        A.v32 = upload(to_f32(sell.val));
+        A.v32 = rounded(A.v64, A.stored);
         if (!IP.v32) IP.v32 = upload(to_f32(IPi.val));
         IR.v32 = upload(to_f32(IRi.val));
         fp32_coefficient_part();
@@ -1964,7 +1980,7 @@ struct aux_handle {
         bo.from_single.resize(n);
         for (int i = 0; i < n; i++) bo.from_single[i] = iperm[sell.perm[i]];
         bo.A = upload_sell(sl);
-        bo.A.v32 = upload(to_f32(sl.val));
+        bo.A.v32 = rounded(bo.A.v64, bo.A.stored);
         // die ranges of equal stored entries
         std::vector<int> off(kDies + 1, 0);
         const double total = (double)sl.slice_off[sl.nslices];
@@ -2237,7 +2253,7 @@ struct aux_handle {
         build_sell(op, kSlice, kSellWindow, false, sl, false);
         BOp b;
         b.m = upload_sell(sl);
-        b.m.v32 = upload(to_f32(sl.val));
+        b.m.v32 = rounded(b.m.v64, b.m.stored);
         b.perm = upload(sl.perm);
         // long rows (level matrices, restrictions) take the unrolled kernels,
         // and so do small operators, whose few slices leave the chip idle and
@@ -2742,12 +2758,7 @@ struct aux_handle {
         assembly_map(disc.A, nt, disc.nloc, disc.tet_dof.data(), ptr, idx);
         asmd.a_ptr = upload(ptr);
         asmd.a_idx = upload(idx);
-        std::vector<int> pos(disc.A.col.size());
-        for (int r = 0; r < n; r++) {
-            const int sl = r / kSlice, lane = r % kSlice, i = sell.perm[r];
-            for (int e = disc.A.ptr[i], j = 0; e < disc.A.ptr[i + 1]; e++, j++)
-                pos[e] = sell.slice_off[sl] + j * kSlice + lane;
-        }
+        std::vector<int> pos = sell_positions(disc.A, sell);
         asmd.a_pos = upload(pos);
         a_pos_host = std::move(pos);
         asmd.a_rowptr = upload(disc.A.ptr);

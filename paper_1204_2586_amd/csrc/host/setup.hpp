@@ -130,25 +130,36 @@ std::vector<double> dense_cycle(const std::vector<FusedLevel> &fused, const Hier
 
 namespace auxp {
 
-// Sliced ELLPACK in an internal row order (see formats.cpp).
+// Sliced ELLPACK in an internal row order (see formats.cpp).  A slice's
+// entries are stored in groups of four slots: entry j of the row at lane l of
+// slice s sits at sell_pos(slice_off[s], j, l), so a lane reads four
+// consecutive entries of its row with one load.
+constexpr int kSellGroup = 4;
 struct Sell {
     int n = 0, slice = 64, nslices = 0;
     std::vector<int> perm;        // internal row -> original row
     std::vector<int> iperm;       // original row -> internal row
-    std::vector<int> slice_off;   // [nslices+1]
-    std::vector<int> col;         // internal column numbers
-    std::vector<double> val;
-    // Column indices as stored on the device.  A slice is narrow when, for
-    // every slot t of it (the t-th group of `slice` consecutive entries), the
-    // columns of the slot span less than 2^16: then entry e has column
-    // base[t] + off[e] and mode[s] = 0.  Otherwise mode[s] = ~w and the
-    // slice's entries have 32-bit columns wide[w + (e - slice_off[s])].
-    std::vector<int> mode;        // [nslices]
-    std::vector<int> base;        // [slice_off[nslices] / slice]
-    std::vector<uint16_t> off;    // [slice_off[nslices]]
-    std::vector<int> wide;        // columns of the wide slices
+    std::vector<int> slice_off;   // [nslices+1] first stored entry, multiples of 4 * slice
+    std::vector<int> width;       // [nslices] longest row of the slice
+    std::vector<double> val;      // padding 0
+    // Columns.  Slot t (the t-th group of `slice` entries with one j) has two
+    // bases; entry e of a slice with wide_off[s] < 0 has column
+    // base[2 t + (off[e] >> 15)] + (off[e] & 0x7fff).  A slice with a slot
+    // that two such ranges do not cover stores 32-bit columns instead, its
+    // first at wide[wide_off[s]], in the order of the entries.
+    std::vector<int> base;        // [2 slice_off[nslices] / slice]
+    std::vector<uint16_t> off;    // [slice_off[nslices]] (empty without 16-bit columns)
+    std::vector<int> wide_off;    // [nslices]
+    std::vector<int> wide;
     int max_width = 0;            // longest slice, in slots
+    int narrow_slices = 0;        // 16-bit slices whose slots all have a single range (span < 2^16)
+    int short_slices = 0;         // slices with 16-bit columns
 };
+// place of entry j of the row at lane l in a slice whose first entry is off
+inline size_t sell_pos(size_t off, int j, int l)
+{
+    return off + (size_t)(j / kSellGroup) * (kSellGroup * 64) + (size_t)l * kSellGroup + j % kSellGroup;
+}
 
 // Row-split sliced ELL for the V-cycle's sparse operators: slices of
 // 64 / lanes consecutive rows, one wavefront each; entry k of the slice's
@@ -185,9 +196,12 @@ void build_tiles(const Csr &A, const std::vector<int> &iperm, int tile, Tiles &o
 // Rows sorted by decreasing length (stably) within windows of `window` rows;
 // index16 = false stores every slice with plain 32-bit columns.  With
 // permute_cols the columns are renumbered like the rows (a square operator
-// acting on vectors in the internal order); otherwise only the rows move
-// (results go to row perm[r]).
+// acting on vectors in the internal order) and each row's entries are put in
+// increasing internal column; otherwise only the rows move (results go to row
+// perm[r]) and entries keep their order.
 void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bool permute_cols = true);
+// place of every entry of A (CSR order) in its layout built with permute_cols
+std::vector<int> sell_positions(const Csr &A, const Sell &s);
 // rows of A in the order perm (row r of the result is row perm[r] of A)
 Csr permute_rows(const Csr &A, const std::vector<int> &perm);
 // Points ordered along the Morton (Z-order) curve of their positions
