@@ -551,38 +551,81 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int n, const int *__restrict
 
 // ------------------------------------------------------------- adjoint
 
-// One thread per tet; NLOC is a template argument so the element vectors
-// stay in registers (the node loops unroll) and the reference tables, read at
-// indices uniform over the wavefront, come through scalar loads.
-template <int NLOC>
-__global__ __launch_bounds__(kBlock) void k_kappa_grad(int nt, const int *__restrict__ tet_dof,
-                                                       const double *__restrict__ G, const double *__restrict__ kappa,
-                                                       const double *__restrict__ M, const double *__restrict__ u,
-                                                       const double *__restrict__ lam, double *__restrict__ g)
+// 64 tets per workgroup, one lane each in every one of its NW wavefronts.
+// The rows of G_t sum to zero, so
+//     sum_pq G_pq lam^T M^pq u = -sum_k G_k lam^T S^k u
+// over the six vertex pairs k = (p, q), S^k = M^pp + M^qq - M^pq - M^qp, and
+// the S^k are symmetric: per node pair (a <= b) one entry sum_k G_k S^k_ab
+// meets lam_a u_b + lam_b u_a (the diagonal's tables halved), nine FP64
+// operations per pair and tet instead of 16 (nloc + 1) / nloc per entry of the
+// sixteen tables.  The element vectors are staged in LDS, so the node loops
+// are short loops (unrolled over the nodes they are 20 KB of code at P3, run
+// once by each of a few waves, and the instruction fetch cost more than the
+// arithmetic); a step takes the rows 2 m and 2 m + 1 at one column b: two LDS
+// words per lane, twelve table words uniform over the wavefront (scalar
+// loads), eighteen operations.  The steps of row pair m number nloc - 2 m;
+// the wavefronts take the pairs in a zigzag, so their sums are nearly equal,
+// and the partial sums meet in LDS in a fixed order.  Node numbers and
+// metrics are stored by column (entry a of tet t at a nt + t), so every load
+// but the gathers is coalesced.  Measured: P3 24^3 76.7 -> 12.4 us (19 MB and
+// 0.31 GFLOP: 3 and 4 us at the card's rates), 32^3 23.1, P2 40^3 17.6 (1, 2
+// and 4 wavefronts: 26.5, 19.6, 17.6), P4 18^3 16.0 (4 and 8: 18.6, 16.0).
+template <int NLOC, int NW>
+__global__ __launch_bounds__(64 * NW) void k_kappa_grad(int nt, const int *__restrict__ dofs,
+                                                        const double *__restrict__ G6,
+                                                        const double *__restrict__ kappa,
+                                                        const double *__restrict__ S, const double *__restrict__ u,
+                                                        const double *__restrict__ lam, double *__restrict__ g)
 {
-    for (int t = blockIdx.x * kBlock + threadIdx.x; t < nt; t += gridDim.x * kBlock) {
-        double ue[NLOC], le[NLOC];
+    constexpr int NP = (NLOC + 1) / 2, NA = (NLOC + NW - 1) / NW;
+    __shared__ double us[2 * NP][64], ls[2 * NP][64], part[NW][64];
+    const int lane = threadIdx.x & 63, h = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int t = blockIdx.x * 64 + lane, tc = min(t, nt - 1);
+    double G[6];
+    int at[NA];
 #pragma unroll
-        for (int a = 0; a < NLOC; a++) {
-            const int i = tet_dof[(size_t)t * NLOC + a];
-            ue[a] = i >= 0 ? u[i] : 0.0;
-            le[a] = i >= 0 ? lam[i] : 0.0;
+    for (int i = 0; i < NA; i++) at[i] = dofs[(size_t)min(h + i * NW, NLOC - 1) * nt + tc];
+#pragma unroll
+    for (int k = 0; k < 6; k++) G[k] = G6[(size_t)k * nt + tc];
+    const double kap = kappa[tc];
+#pragma unroll
+    for (int i = 0; i < NA; i++) {
+        const int a = h + i * NW, j = max(at[i], 0);
+        const double ua = u[j], la = lam[j];
+        if (a < NLOC) {
+            us[a][lane] = at[i] < 0 ? 0.0 : ua;
+            ls[a][lane] = at[i] < 0 ? 0.0 : la;
         }
-        double s = 0.0;
-#pragma unroll 1
-        for (int pq = 0; pq < 16; pq++) {
-            const double *Mpq = M + (size_t)pq * NLOC * NLOC;
-            double w = 0.0;
+    }
+    if (NLOC % 2 && h == 0) us[2 * NP - 1][lane] = ls[2 * NP - 1][lane] = 0.0;
+    __syncthreads();
+    double acc0 = 0.0, acc1 = 0.0;
+    for (int r = 0; r * NW < NP; r++) {
+        const int m = r * NW + (r % 2 ? NW - 1 - h : h);
+        if (m >= NP) continue;
+        // steps before row pair m: sum over m' < m of nloc - 2 m'
+        const double *__restrict__ T = S + 12 * (m * NLOC - m * (m - 1));
+        const double u0 = us[2 * m][lane], l0 = ls[2 * m][lane], u1 = us[2 * m + 1][lane], l1 = ls[2 * m + 1][lane];
+#pragma unroll 2
+        for (int b = 2 * m; b < NLOC; b++, T += 12) {
+            const double ub = us[b][lane], lb = ls[b][lane];
+            double e0 = G[0] * T[0], e1 = G[0] * T[6];
 #pragma unroll
-            for (int a = 0; a < NLOC; a++) {
-                double ra = 0.0;
-#pragma unroll
-                for (int b = 0; b < NLOC; b++) ra += Mpq[a * NLOC + b] * ue[b];
-                w += le[a] * ra;
+            for (int k = 1; k < 6; k++) {
+                e0 += G[k] * T[k];
+                e1 += G[k] * T[6 + k];
             }
-            s += G[(size_t)t * 16 + pq] * w;
+            acc0 += e0 * (l0 * ub + u0 * lb);
+            acc1 += e1 * (l1 * ub + u1 * lb);
         }
-        g[t] = -kappa[t] * s;
+    }
+    part[h][lane] = acc0 + acc1;
+    __syncthreads();
+    if (h == 0 && t < nt) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; w++) s += part[w][lane];
+        g[t] = kap * s;
     }
 }
 
@@ -778,22 +821,20 @@ void vec_scatter(hipStream_t s, int n, const int *idx, const double *x, double *
     hipLaunchKernelGGL(k_scatter, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, idx, x, y);
 }
 
-void kappa_grad(hipStream_t s, int nt, int nloc, const int *tet_dof, const double *G, const double *kappa,
-                const double *M, const double *u, const double *lam, double *g)
+void kappa_grad(hipStream_t s, int nt, int nloc, const int *dofs, const double *G6, const double *kappa,
+                const double *S, const double *u, const double *lam, double *g)
 {
+    const int grid = (nt + 63) / 64;
+    if (grid == 0) return;
+#define GRAD(N, W)                                                                                              \
+    hipLaunchKernelGGL((k_kappa_grad<N, W>), dim3(grid), dim3(64 * W), 0, s, nt, dofs, G6, kappa, S, u, lam, g)
     switch (nloc) {
-    case 10:
-        hipLaunchKernelGGL(k_kappa_grad<10>, dim3(vec_grid(nt)), dim3(kBlock), 0, s, nt, tet_dof, G, kappa, M, u, lam, g);
-        break;
-    case 20:
-        hipLaunchKernelGGL(k_kappa_grad<20>, dim3(vec_grid(nt)), dim3(kBlock), 0, s, nt, tet_dof, G, kappa, M, u, lam, g);
-        break;
-    case 35:
-        hipLaunchKernelGGL(k_kappa_grad<35>, dim3(vec_grid(nt)), dim3(kBlock), 0, s, nt, tet_dof, G, kappa, M, u, lam, g);
-        break;
-    default:
-        throw std::invalid_argument("kappa gradient: nodes per tet must be 10, 20 or 35");
+    case 10: GRAD(10, 4); break;
+    case 20: GRAD(20, 8); break;
+    case 35: GRAD(35, 8); break;
+    default: throw std::invalid_argument("kappa gradient: nodes per tet must be 10, 20 or 35");
     }
+#undef GRAD
 }
 
 #define INST(T)                                                                                              \

@@ -143,10 +143,15 @@ void vec_gather(hipStream_t s, int n, const int *idx, const double *x, double *y
 // y[idx[i]] = x[i]
 void vec_scatter(hipStream_t s, int n, const int *idx, const double *x, double *y);
 
-// g_t = -kappa_t sum_pq G_pq lam_t^T M^pq u_t per tet (FP64); tet_dof holds
-// internal dof numbers (-1 on the boundary)
-void kappa_grad(hipStream_t s, int nt, int nloc, const int *tet_dof, const double *G, const double *kappa,
-                const double *M, const double *u, const double *lam, double *g);
+// g_t = -kappa_t sum_pq G_pq lam_t^T M^pq u_t per tet (FP64).  By column (entry
+// a of tet t at a nt + t): dofs, the tets' dof numbers (-1 on the boundary);
+// G6, the metrics of the vertex pairs (0,1) (0,2) (0,3) (1,2) (1,3) (2,3).
+// S: the pairs' symmetric tables S^k = M^pp + M^qq - M^pq - M^qp: for each pair
+// of rows (2 m, 2 m + 1) and column b >= 2 m the six entries of the first row,
+// then of the second (zero below the diagonal and past the last row), the
+// diagonal's halved.
+void kappa_grad(hipStream_t s, int nt, int nloc, const int *dofs, const double *G6, const double *kappa,
+                const double *S, const double *u, const double *lam, double *g);
 
 int pick_lpr(double avg_row_nnz);
 

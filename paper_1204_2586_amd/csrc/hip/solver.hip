@@ -20,6 +20,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "../host/parallel.hpp"
 #include "../host/setup.hpp"
 #include "aux.h"
 #include "amgsetup.hpp"
@@ -275,9 +276,10 @@ struct aux_handle {
     double last_ff = 0.0;
     std::vector<void *> host_bufs;   // other pinned buffers
 
-    // adjoint data (external dof numbering)
+    // adjoint data (external dof numbering); the gradient's by column
     double *G = nullptr, *kappa_d = nullptr, *Mtab = nullptr;
-    int *tet_dof_d = nullptr;
+    double *grad_G6 = nullptr, *grad_S = nullptr;
+    int *grad_dofs = nullptr;
 
     // matrix-free element operator (internal dof numbering)
     bool mf_ready = false;
@@ -285,20 +287,44 @@ struct aux_handle {
     double *mf_w64 = nullptr, *mf_S64 = nullptr, *mf_Y64 = nullptr;
     float *mf_w32 = nullptr, *mf_S32 = nullptr, *mf_Y32 = nullptr;
 
-    void ensure_mf()
+    // the six vertex pairs k = (p, q) and their reference matrices S^k =
+    // M^pp + M^qq - M^pq - M^qp, entry (a, b) at (6 a + k) nloc + b
+    static constexpr int pairs[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
+    std::vector<double> pair_tables() const
     {
-        if (mf_ready) return;
-        const int nt = disc.nt, nl = disc.nloc, n = disc.ndof;
-        static const int pairs[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
+        const int nl = disc.nloc;
         const std::vector<double> &M = stiffness_tables(disc.k);
         auto Mat = [&](int p, int q, int a, int b) { return M[(((size_t)p * 4 + q) * nl + a) * nl + b]; };
         std::vector<double> S((size_t)nl * 6 * nl);
         for (int k = 0; k < 6; k++) {
-            int p = pairs[k][0], q = pairs[k][1];
+            const int p = pairs[k][0], q = pairs[k][1];
             for (int a = 0; a < nl; a++)
                 for (int b = 0; b < nl; b++)
                     S[(size_t)a * 6 * nl + k * nl + b] = Mat(p, p, a, b) + Mat(q, q, a, b) - Mat(p, q, a, b) - Mat(q, p, a, b);
         }
+        return S;
+    }
+    // tet_metric of every tet: f(t, G_t), tets shared among the host threads
+    template <typename F>
+    void for_metrics(F f) const
+    {
+        const int nt = disc.nt, parts = setup_threads((size_t)nt * 8);
+        run_tasks(parts, [&](int part) {
+            for (int t = (int)((int64_t)nt * part / parts); t < (int)((int64_t)nt * (part + 1) / parts); t++) {
+                const int *v = &disc.tets[4 * (size_t)t];
+                double Gt[4][4];
+                tet_metric(&disc.xyz[3 * (size_t)v[0]], &disc.xyz[3 * (size_t)v[1]], &disc.xyz[3 * (size_t)v[2]],
+                           &disc.xyz[3 * (size_t)v[3]], Gt);
+                f(t, Gt);
+            }
+        });
+    }
+
+    void ensure_mf()
+    {
+        if (mf_ready) return;
+        const int nt = disc.nt, nl = disc.nloc, n = disc.ndof;
+        const std::vector<double> S = pair_tables();
         std::vector<double> w((size_t)nt * 6);
         std::vector<int> emap((size_t)nt * nl), cnt((size_t)n + 1, 0);
         for (int t = 0; t < nt; t++) {
@@ -2914,22 +2940,40 @@ struct aux_handle {
         vec_scatter(stream, n, perm, q, y);
     }
 
+    void ensure_kappa_device()
+    {
+        if (!kappa_d) kappa_d = upload(disc.kappa);
+    }
     void ensure_adjoint()
     {
         if (G) return;
-        int nt = disc.nt;
-        std::vector<double> g((size_t)nt * 16);
-        for (int t = 0; t < nt; t++) {
-            const int *v = &disc.tets[4 * (size_t)t];
-            double Gt[4][4];
-            tet_metric(&disc.xyz[3 * (size_t)v[0]], &disc.xyz[3 * (size_t)v[1]], &disc.xyz[3 * (size_t)v[2]],
-                       &disc.xyz[3 * (size_t)v[3]], Gt);
-            for (int pq = 0; pq < 16; pq++) g[(size_t)t * 16 + pq] = Gt[pq / 4][pq % 4];
-        }
-        G = upload(g);
-        kappa_d = upload(disc.kappa);
+        std::vector<double> g((size_t)disc.nt * 16);
+        for_metrics([&](int t, const double(&Gt)[4][4]) { std::memcpy(&g[(size_t)t * 16], Gt, sizeof(Gt)); });
+        ensure_kappa_device();
         Mtab = upload(stiffness_tables(disc.k));
-        tet_dof_d = upload(disc.tet_dof);
+        G = upload(g);
+    }
+    // the gradient's arrays (see kappa_grad)
+    void ensure_gradient()
+    {
+        if (grad_dofs) return;
+        const int nt = disc.nt, nl = disc.nloc;
+        std::vector<double> g((size_t)nt * 6), S;
+        std::vector<int> dofs((size_t)nt * nl);
+        for_metrics([&](int t, const double(&Gt)[4][4]) {
+            for (int k = 0; k < 6; k++) g[(size_t)k * nt + t] = Gt[pairs[k][0]][pairs[k][1]];
+            for (int a = 0; a < nl; a++) dofs[(size_t)a * nt + t] = disc.tet_dof[(size_t)t * nl + a];
+        });
+        const std::vector<double> T = pair_tables();
+        for (int m = 0; 2 * m < nl; m++)
+            for (int b = 2 * m; b < nl; b++)
+                for (int a = 2 * m; a <= 2 * m + 1; a++)
+                    for (int k = 0; k < 6; k++)
+                        S.push_back(a >= nl || b < a ? 0.0 : T[((size_t)a * 6 + k) * nl + b] * (a == b ? 0.5 : 1.0));
+        ensure_kappa_device();
+        grad_G6 = upload(g);
+        grad_S = upload(S);
+        grad_dofs = upload(dofs);
     }
 
     void release()
@@ -3547,8 +3591,8 @@ int aux_kappa_grad(aux_handle *h, const double *u, const double *lam, double *g)
         need_device(h);
         if (!u || !lam || !g) throw AuxError(AUX_EINVAL, "null vector");
         set_dev(h);
-        h->ensure_adjoint();
-        kappa_grad(h->stream, h->disc.nt, h->disc.nloc, h->tet_dof_d, h->G, h->kappa_d, h->Mtab, u, lam, g);
+        h->ensure_gradient();
+        kappa_grad(h->stream, h->disc.nt, h->disc.nloc, h->grad_dofs, h->grad_G6, h->kappa_d, h->grad_S, u, lam, g);
         HIPCHECK(hipGetLastError());
         return AUX_OK;
     });
