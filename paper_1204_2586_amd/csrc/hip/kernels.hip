@@ -73,6 +73,65 @@ inline int grid_cap(long long need)
     return (int)need;
 }
 
+// The sum of a reduction's partials by one workgroup of BS threads, in a fixed
+// order (valid in thread 0): four accumulators, loads unrolled, so all of a
+// thread's partials are in flight.
+template <int BS>
+__device__ __forceinline__ double partials_sum(const double *__restrict__ partials, int nparts)
+{
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int i = threadIdx.x;
+    for (; i + 3 * BS < nparts; i += 4 * BS) {
+        s0 += partials[i];
+        s1 += partials[i + BS];
+        s2 += partials[i + 2 * BS];
+        s3 += partials[i + 3 * BS];
+    }
+    for (; i < nparts; i += BS) s0 += partials[i];
+    return block_sum<BS>((s0 + s1) + (s2 + s3));
+}
+// the same, known to every thread
+template <int BS>
+__device__ __forceinline__ double partials_sum_all(const double *__restrict__ partials, int nparts)
+{
+    __shared__ double total;
+    const double s = partials_sum<BS>(partials, nparts);
+    if (threadIdx.x == 0) total = s;
+    __syncthreads();
+    return total;
+}
+
+// the stop code an inner product (r.z or p.Ap) gives: 0 to go on
+__device__ __forceinline__ int product_stop(double s) { return !std::isfinite(s) ? 4 : !(s > 0.0) ? 3 : 0; }
+
+// One workgroup: the sum of a reduction's partials into its CG slot, and what
+// follows from it (the stop flag, the iteration count).
+template <int BS>
+__device__ __forceinline__ void finish_block(const double *__restrict__ partials, int nparts, int mode, double *out,
+                                             const CgState &st)
+{
+    if (mode != FIN_PLAIN && *st.done) return;
+    const double s = partials_sum<BS>(partials, nparts);
+    if (threadIdx.x != 0) return;
+    if (mode == FIN_PLAIN) {
+        *out = s;
+        return;
+    }
+    const int k = *st.iter;
+    int d = 0;
+    if (mode == FIN_RR) {
+        st.rr[k + 1] = s;
+        *st.iter = k + 1;
+        if (!std::isfinite(s)) d = 4;
+        else if (s <= st.scal[2]) d = 1;
+        else if (k + 1 >= st.maxit) d = 2;
+    } else {
+        (mode == FIN_PQ ? st.pq : st.rz)[k] = s;
+        d = product_stop(s);
+    }
+    if (d) *st.done = d;
+}
+
 // ------------------------------------------------------------------ SELL
 
 // W wavefronts per 64-row slice, one lane per row; consecutive slices go to
@@ -142,14 +201,14 @@ constexpr int sell_block() { return W > 4 ? 64 * W : kBlock; }
 template <int W>
 constexpr int sell_per_block() { return sell_block<W>() / (64 * W); }
 
-// Every row of A: s = (A x)_row, then epi(row, s, in) with in = pre(row) the
+// Every row of A by `grid` workgroups: s = (A x)_row, then epi(row, s, in) with in = pre(row) the
 // row's other inputs, requested before the row's entries; nothing when the
 // stop flag `halt` is set (it is tested after the first slice's meta is
 // requested, so the two loads overlap).  With W > 1 the other wavefronts' sums
 // pass through LDS and are added in a fixed order; every thread of the block
 // then runs the same number of steps, so the barriers are uniform.
 template <typename T, int W, typename XF, typename PRE, typename EPI>
-__device__ __forceinline__ void sell_rows(const DevSellView &A, int halt, XF x, PRE pre, EPI epi)
+__device__ __forceinline__ void sell_rows(const DevSellView &A, int grid, int halt, XF x, PRE pre, EPI epi)
 {
     constexpr int S = sell_per_block<W>();
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -160,7 +219,7 @@ __device__ __forceinline__ void sell_rows(const DevSellView &A, int halt, XF x, 
     asm volatile("" ::"s"(m.x), "s"(halt));
     if (halt) return;
     if constexpr (W == 1) {
-        for (; sl < A.nslices; sl += (int)gridDim.x * S) {
+        for (; sl < A.nslices; sl += grid * S) {
             if (sl != (int)blockIdx.x * S + q) m = A.meta[sl];
             const int row = sl * kSlice + lane;
             const auto in = pre(min(row, A.n - 1));
@@ -169,7 +228,7 @@ __device__ __forceinline__ void sell_rows(const DevSellView &A, int halt, XF x, 
         }
     } else {
         __shared__ T part[S][W - 1][64];
-        const int per_step = S * (int)gridDim.x;
+        const int per_step = S * grid;
         const int steps = (A.nslices + per_step - 1) / per_step;
         for (int it = 0; it < steps; it++, sl += per_step) {
             const int row = sl * kSlice + lane;
@@ -206,24 +265,37 @@ inline int sell_grid(const DevSellView &A)
     return grid_cap(((long long)A.nslices + sell_per_block<W>() - 1) / sell_per_block<W>());
 }
 
-template <typename T, typename TR, typename TZ, bool DOT, int W>
+// FIN: the last workgroup is one more than the rows take and finishes the
+// r.r reduction of the CG update before (nothing here waits for its result;
+// a stop flag it sets is read by the kernels that follow).  operm: row r goes
+// to zout[operm[r]].
+template <typename T, typename TR, typename TZ, bool DOT, bool FIN, int W>
 __global__ __launch_bounds__(sell_block<W>()) void k_sell_sweep(DevSellView A, const T *__restrict__ dinv,
                                                                 const TR *__restrict__ rhs, const T *__restrict__ zin,
                                                                 TZ *__restrict__ zout, const double *__restrict__ rdot,
-                                                                double *partials, const int *done)
+                                                                double *partials, const int *done,
+                                                                const int *__restrict__ operm, RrFinish fin)
 {
+    const int grid = (int)gridDim.x - (FIN ? 1 : 0);
+    if (FIN && (int)blockIdx.x == grid) {
+        finish_block<sell_block<W>()>(fin.partials, fin.nparts, FIN_RR, nullptr, fin.st);
+        return;
+    }
     const int halt = stop_word(done);
     double acc = 0.0;
     struct In {
         T z, d, b;
         double r;
+        int o;
     };
     sell_rows<T, W>(
-        A, halt, [&](int j) { return at32(zin, j); },
-        [&](int row) { return In{zin[row], dinv[row], (T)rhs[row], DOT ? rdot[row] : 0.0}; },
+        A, grid, halt, [&](int j) { return at32(zin, j); },
+        [&](int row) {
+            return In{zin[row], dinv[row], (T)rhs[row], DOT ? rdot[row] : 0.0, operm ? operm[row] : row};
+        },
         [&](int row, T s, const In &in) {
             T zi = in.z + in.d * (in.b - s);
-            zout[row] = (TZ)zi;
+            zout[in.o] = (TZ)zi;
             if (DOT) acc += in.r * (double)(TZ)zi;
         });
     if (DOT) write_partial<sell_block<W>()>(partials, acc);
@@ -234,24 +306,62 @@ __global__ __launch_bounds__(sell_block<W>()) void k_sell_resid(DevSellView A, c
                                                                 const T *__restrict__ z, T *__restrict__ res,
                                                                 const int *done)
 {
-    sell_rows<T, W>(A, stop_word(done), [&](int j) { return at32(z, j); },
+    sell_rows<T, W>(A, (int)gridDim.x, stop_word(done), [&](int j) { return at32(z, j); },
                     [&](int row) { return rhs[row]; }, [&](int row, T s, T b) { res[row] = b - s; });
 }
 
+// operm: row r goes to y[operm[r]]
 template <bool DOT, int W>
 __global__ __launch_bounds__(sell_block<W>()) void k_sell_spmv64(DevSellView A, const double *__restrict__ x,
                                                                  double *__restrict__ y, double *partials,
-                                                                 const int *done)
+                                                                 const int *done, const int *__restrict__ operm)
 {
     const int halt = stop_word(done);
     double acc = 0.0;
-    sell_rows<double, W>(A, halt, [&](int j) { return at32(x, j); },
-                         [&](int row) { return DOT ? x[row] : 0.0; },
-                         [&](int row, double s, double xr) {
-                             y[row] = s;
-                             if (DOT) acc += xr * s;
+    struct In {
+        double x;
+        int o;
+    };
+    sell_rows<double, W>(A, (int)gridDim.x, halt, [&](int j) { return at32(x, j); },
+                         [&](int row) { return In{DOT ? x[row] : 0.0, operm ? operm[row] : row}; },
+                         [&](int row, double s, const In &in) {
+                             y[in.o] = s;
+                             if (DOT) acc += in.x * s;
                          });
     if (DOT) write_partial<sell_block<W>()>(partials, acc);
+}
+
+// The CG product with the direction formed on the way: p = z + beta p_old
+// (p = z at k = 0), q = A p, partials of p.q, beta = r.z / (r.z)_{k-1} with r.z
+// summed from its partials by every workgroup in the same order (the first
+// one records it and its stop code).  p and p_old are different buffers.
+template <int W>
+__global__ __launch_bounds__(sell_block<W>()) void k_cg_product(DevSellView A, const double *__restrict__ z,
+                                                                const double *__restrict__ p_old,
+                                                                double *__restrict__ p, double *__restrict__ q,
+                                                                const double *__restrict__ rz_parts, int rz_n,
+                                                                double *__restrict__ pq_parts, CgState st)
+{
+    if (*st.done) return;
+    const int k = *st.iter;
+    const double rz = partials_sum_all<sell_block<W>()>(rz_parts, rz_n);
+    const int bad = product_stop(rz);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st.rz[k] = rz;
+        if (bad) *st.done = bad;
+    }
+    if (bad) return;
+    const double beta = k > 0 ? rz / st.rz[k - 1] : 0.0;
+    const double *__restrict__ po = k > 0 ? p_old : z;
+    double acc = 0.0;
+    sell_rows<double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(z, j) + beta * at32(po, j); },
+                         [&](int row) { return z[row] + beta * po[row]; },
+                         [&](int row, double s, double pr) {
+                             p[row] = pr;
+                             q[row] = s;
+                             acc += pr * s;
+                         });
+    write_partial<sell_block<W>()>(pq_parts, acc);
 }
 
 template <int W>
@@ -259,7 +369,7 @@ __global__ __launch_bounds__(sell_block<W>()) void k_sell_residual64(DevSellView
                                                                      const double *__restrict__ u,
                                                                      double *__restrict__ r)
 {
-    sell_rows<double, W>(A, 0, [&](int j) { return at32(u, j); }, [&](int row) { return f[row]; },
+    sell_rows<double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(u, j); }, [&](int row) { return f[row]; },
                          [&](int row, double s, double b) { r[row] = b - s; });
 }
 
@@ -270,6 +380,22 @@ __global__ __launch_bounds__(kBlock) void k_jacobi0(int n, const T *__restrict__
     if (stop(done)) return;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         T ri = (T)r[i];
+        z[i] = dinv[i] * ri;
+        if (rT) rT[i] = ri;
+    }
+}
+
+// r_int = r[perm], z = D^{-1} r_int (and r_int in the working precision)
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_gather_jacobi0(int n, const int *__restrict__ perm,
+                                                           const T *__restrict__ dinv, const double *__restrict__ r,
+                                                           double *__restrict__ rint, T *__restrict__ z,
+                                                           T *__restrict__ rT)
+{
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        const double v = r[perm[i]];
+        const T ri = (T)v;
+        rint[i] = v;
         z[i] = dinv[i] * ri;
         if (rT) rT[i] = ri;
     }
@@ -436,37 +562,7 @@ __global__ __launch_bounds__(kBlock) void k_dot(int n, const double *__restrict_
 __global__ __launch_bounds__(kBlock) void k_finish(const double *__restrict__ partials, int nparts, int mode,
                                                    double *out, CgState st)
 {
-    if (mode != FIN_PLAIN && *st.done) return;
-    // four accumulators, loads unrolled: all of a thread's partials in flight
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int i = threadIdx.x;
-    for (; i + 3 * kBlock < nparts; i += 4 * kBlock) {
-        s0 += partials[i];
-        s1 += partials[i + kBlock];
-        s2 += partials[i + 2 * kBlock];
-        s3 += partials[i + 3 * kBlock];
-    }
-    for (; i < nparts; i += kBlock) s0 += partials[i];
-    double s = block_sum((s0 + s1) + (s2 + s3));
-    if (threadIdx.x != 0) return;
-    if (mode == FIN_PLAIN) {
-        *out = s;
-        return;
-    }
-    const int k = *st.iter;
-    int d = 0;
-    if (mode == FIN_RR) {
-        st.rr[k + 1] = s;
-        *st.iter = k + 1;
-        if (!std::isfinite(s)) d = 4;
-        else if (s <= st.scal[2]) d = 1;
-        else if (k + 1 >= st.maxit) d = 2;
-    } else {
-        (mode == FIN_PQ ? st.pq : st.rz)[k] = s;
-        if (!std::isfinite(s)) d = 4;
-        else if (!(s > 0.0)) d = 3;
-    }
-    if (d) *st.done = d;
+    finish_block<kBlock>(partials, nparts, mode, out, st);
 }
 
 __global__ void k_cg_init(CgState st, double tol2)
@@ -482,35 +578,32 @@ __global__ void k_cg_init(CgState st, double tol2)
     *st.done = d;
 }
 
-__global__ __launch_bounds__(kBlock) void k_cg_update(int n, double *__restrict__ x, double *__restrict__ r,
-                                                      const double *__restrict__ p, const double *__restrict__ q,
-                                                      CgState st, double *partials)
-{
-    if (*st.done) return;
-    const int k = *st.iter;
-    const double alpha = st.rz[k] / st.pq[k];
-    double acc = 0.0;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-        x[i] += alpha * p[i];
-        double ri = r[i] - alpha * q[i];
-        r[i] = ri;
-        acc += ri * ri;
-    }
-    write_partial(partials, acc);
-}
-
 // the update fused with the preconditioner's first sweep from zero:
 // z0 = D^-1 r in the preconditioner's type (and its copy of r), with the
-// expressions of k_jacobi0
-template <typename T>
+// expressions of k_jacobi0.  RESUM: p.q is summed from its pq_n partials by
+// every workgroup in the same order (the first one records it).
+template <typename T, bool RESUM>
 __global__ __launch_bounds__(kBlock) void k_cg_update_prep(int n, double *__restrict__ x, double *__restrict__ r,
                                                            const double *__restrict__ p, const double *__restrict__ q,
                                                            CgState st, double *partials, const T *__restrict__ dinv,
-                                                           T *__restrict__ z0, T *__restrict__ rT)
+                                                           T *__restrict__ z0, T *__restrict__ rT,
+                                                           const double *__restrict__ pq_parts, int pq_n)
 {
     if (*st.done) return;
     const int k = *st.iter;
-    const double alpha = st.rz[k] / st.pq[k];
+    double pq;
+    if (RESUM) {
+        pq = partials_sum_all<kBlock>(pq_parts, pq_n);
+        const int bad = product_stop(pq);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st.pq[k] = pq;
+            if (bad) *st.done = bad;
+        }
+        if (bad) return;
+    } else {
+        pq = st.pq[k];
+    }
+    const double alpha = st.rz[k] / pq;
     double acc = 0.0;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         x[i] += alpha * p[i];
@@ -524,16 +617,30 @@ __global__ __launch_bounds__(kBlock) void k_cg_update_prep(int n, double *__rest
     write_partial(partials, acc);
 }
 
+// RESUM: r.z is summed from its rz_n partials as p.q above
+template <bool RESUM>
 __global__ __launch_bounds__(kBlock) void k_cg_direction(int n, const double *__restrict__ z, double *__restrict__ p,
-                                                         CgState st)
+                                                         CgState st, const double *__restrict__ rz_parts, int rz_n)
 {
     if (*st.done) return;
     const int k = *st.iter;
+    double rz;
+    if (RESUM) {
+        rz = partials_sum_all<kBlock>(rz_parts, rz_n);
+        const int bad = product_stop(rz);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st.rz[k] = rz;
+            if (bad) *st.done = bad;
+        }
+        if (bad) return;
+    } else {
+        rz = st.rz[k];
+    }
     if (k == 0) {
         for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = z[i];
         return;
     }
-    const double beta = st.rz[k] / st.rz[k - 1];
+    const double beta = rz / st.rz[k - 1];
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = z[i] + beta * p[i];
 }
 
@@ -663,6 +770,12 @@ int vec_jacobi0(hipStream_t s, int n, const T *dinv, const double *r, T *z, T *r
 }
 
 template <typename T>
+void vec_gather_jacobi0(hipStream_t s, int n, const int *perm, const T *dinv, const double *r, double *rint, T *z, T *rT)
+{
+    hipLaunchKernelGGL(k_gather_jacobi0<T>, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, perm, dinv, r, rint, z, rT);
+}
+
+template <typename T>
 void vec_jacobi0_t(hipStream_t s, int n, const T *dinv, const T *r, T *z, const int *done)
 {
     hipLaunchKernelGGL((k_jacobi0<T, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, dinv, r, z, nullptr, done);
@@ -670,14 +783,17 @@ void vec_jacobi0_t(hipStream_t s, int n, const T *dinv, const T *r, T *z, const 
 
 template <typename T, typename TR, typename TZ>
 int sell_sweep(hipStream_t s, const DevSellView &A, const T *dinv, const TR *rhs, const T *zin, TZ *zout,
-               const double *rdot, double *partials, const int *done)
+               const double *rdot, double *partials, const int *done, const int *operm, const RrFinish *fin)
 {
     int g = 0;
+#define SWEEP(DOT, FIN)                                                                                             \
+    hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, DOT, FIN, W>), dim3(g + (FIN ? 1 : 0)), dim3(sell_block<W>()), 0, s, \
+                       A, dinv, rhs, zin, zout, rdot, partials, done, operm, fin ? *fin : RrFinish())
     WAVES_SWITCH(A, g = sell_grid<W>(A);
-                 if (partials) hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, true, W>), dim3(g), dim3(sell_block<W>()), 0,
-                                                  s, A, dinv, rhs, zin, zout, rdot, partials, done);
-                 else hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, false, W>), dim3(g), dim3(sell_block<W>()), 0, s, A,
-                                         dinv, rhs, zin, zout, rdot, partials, done));
+                 if (partials) SWEEP(true, false);
+                 else if (fin) SWEEP(false, true);
+                 else SWEEP(false, false));
+#undef SWEEP
     return g;
 }
 
@@ -690,14 +806,32 @@ int sell_resid(hipStream_t s, const DevSellView &A, const T *rhs, const T *z, T 
     return g;
 }
 
-int sell_spmv64(hipStream_t s, const DevSellView &A, const double *x, double *y, double *partials, const int *done)
+int sell_spmv64(hipStream_t s, const DevSellView &A, const double *x, double *y, double *partials, const int *done,
+                const int *operm)
 {
     int g = 0;
     WAVES_SWITCH(A, g = sell_grid<W>(A);
                  if (partials) hipLaunchKernelGGL((k_sell_spmv64<true, W>), dim3(g), dim3(sell_block<W>()), 0, s, A, x,
-                                                  y, partials, done);
+                                                  y, partials, done, operm);
                  else hipLaunchKernelGGL((k_sell_spmv64<false, W>), dim3(g), dim3(sell_block<W>()), 0, s, A, x, y,
-                                         partials, done));
+                                         partials, done, operm));
+    return g;
+}
+
+int sell_parts(const DevSellView &A)
+{
+    int g = 0;
+    WAVES_SWITCH(A, g = sell_grid<W>(A));
+    return g;
+}
+
+int cg_product(hipStream_t s, const DevSellView &A, const double *z, const double *p_old, double *p, double *q,
+               const double *rz_parts, int rz_n, double *pq_parts, const CgState &st)
+{
+    int g = 0;
+    WAVES_SWITCH(A, g = sell_grid<W>(A);
+                 hipLaunchKernelGGL((k_cg_product<W>), dim3(g), dim3(sell_block<W>()), 0, s, A, z, p_old, p, q, rz_parts,
+                                    rz_n, pq_parts, st));
     return g;
 }
 
@@ -785,30 +919,32 @@ void cg_init(hipStream_t s, const CgState &st, double tol2)
     hipLaunchKernelGGL(k_cg_init, dim3(1), dim3(1), 0, s, st, tol2);
 }
 
-int cg_update(hipStream_t s, int n, double *x, double *r, const double *p, const double *q, const CgState &st,
-              double *partials)
-{
-    int g = vec_grid(n);
-    hipLaunchKernelGGL(k_cg_update, dim3(g), dim3(kBlock), 0, s, n, x, r, p, q, st, partials);
-    return g;
-}
-
 template <typename T>
 int cg_update_prep(hipStream_t s, int n, double *x, double *r, const double *p, const double *q, const CgState &st,
-                   double *partials, const T *dinv, T *z0, T *rT)
+                   double *partials, const T *dinv, T *z0, T *rT, const double *pq_parts, int pq_n)
 {
     int g = vec_grid(n);
-    hipLaunchKernelGGL(k_cg_update_prep<T>, dim3(g), dim3(kBlock), 0, s, n, x, r, p, q, st, partials, dinv, z0, rT);
+    if (pq_n > 0)
+        hipLaunchKernelGGL((k_cg_update_prep<T, true>), dim3(g), dim3(kBlock), 0, s, n, x, r, p, q, st, partials, dinv,
+                           z0, rT, pq_parts, pq_n);
+    else
+        hipLaunchKernelGGL((k_cg_update_prep<T, false>), dim3(g), dim3(kBlock), 0, s, n, x, r, p, q, st, partials, dinv,
+                           z0, rT, pq_parts, 0);
     return g;
 }
 template int cg_update_prep<float>(hipStream_t, int, double *, double *, const double *, const double *,
-                                   const CgState &, double *, const float *, float *, float *);
+                                   const CgState &, double *, const float *, float *, float *, const double *, int);
 template int cg_update_prep<double>(hipStream_t, int, double *, double *, const double *, const double *,
-                                    const CgState &, double *, const double *, double *, double *);
+                                    const CgState &, double *, const double *, double *, double *, const double *,
+                                    int);
 
-void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st)
+void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st, const double *rz_parts, int rz_n)
 {
-    hipLaunchKernelGGL(k_cg_direction, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, z, p, st);
+    const int g = vec_grid(n);
+    if (rz_n > 0)
+        hipLaunchKernelGGL(k_cg_direction<true>, dim3(g), dim3(kBlock), 0, s, n, z, p, st, rz_parts, rz_n);
+    else
+        hipLaunchKernelGGL(k_cg_direction<false>, dim3(g), dim3(kBlock), 0, s, n, z, p, st, rz_parts, 0);
 }
 
 void vec_gather(hipStream_t s, int n, const int *idx, const double *x, double *y)
@@ -841,8 +977,10 @@ void kappa_grad(hipStream_t s, int nt, int nloc, const int *dofs, const double *
     template int vec_jacobi0<T>(hipStream_t, int, const T *, const double *, T *, T *, const int *);         \
     template void vec_jacobi0_t<T>(hipStream_t, int, const T *, const T *, T *, const int *);               \
     template int sell_resid<T>(hipStream_t, const DevSellView &, const T *, const T *, T *, const int *);    \
+    template void vec_gather_jacobi0<T>(hipStream_t, int, const int *, const T *, const double *, double *, T *, \
+                                        T *);                                                                \
     template int sell_sweep<T, T, T>(hipStream_t, const DevSellView &, const T *, const T *, const T *, T *, \
-                                     const double *, double *, const int *);                                 \
+                                     const double *, double *, const int *, const int *, const RrFinish *);  \
     template void csr_matvec<T>(hipStream_t, const DevCsrView &, const T *, T *, const int *);               \
     template void csr_matvec_add<T>(hipStream_t, const DevCsrView &, const T *, T *, const int *);           \
     template void csr_matvec2<T>(hipStream_t, const DevCsrView &, const T *, const T *, int, T *, const int *); \
@@ -854,6 +992,7 @@ void kappa_grad(hipStream_t s, int nt, int nloc, const int *dofs, const double *
 INST(double)
 INST(float)
 template int sell_sweep<float, double, double>(hipStream_t, const DevSellView &, const float *, const double *,
-                                               const float *, double *, const double *, double *, const int *);
+                                               const float *, double *, const double *, double *, const int *,
+                                               const int *, const RrFinish *);
 
 }  // namespace auxp

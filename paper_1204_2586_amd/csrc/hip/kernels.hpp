@@ -76,6 +76,13 @@ struct CgState {
     int maxit;
 };
 
+// the r.r reduction of a CG update, finished by a later kernel
+struct RrFinish {
+    const double *partials = nullptr;
+    int nparts = 0;
+    CgState st = {};
+};
+
 enum FinishMode { FIN_PLAIN = 0, FIN_PQ = 1, FIN_RZ = 2, FIN_RR = 3 };
 
 // ---- P^k level (SELL).  Kernels that reduce write one partial per
@@ -87,15 +94,28 @@ int vec_jacobi0(hipStream_t s, int n, const T *dinv, const double *r, T *z, T *r
 // z = D^{-1} r for r in the working precision
 template <typename T>
 void vec_jacobi0_t(hipStream_t s, int n, const T *dinv, const T *r, T *z, const int *done);
-// zout = zin + D^{-1} (rhs - A zin); with partials, also sum_i rdot_i zout_i
+// rint = r[perm], z = D^{-1} rint; rT = (T) rint if rT
+template <typename T>
+void vec_gather_jacobi0(hipStream_t s, int n, const int *perm, const T *dinv, const double *r, double *rint, T *z, T *rT);
+// zout = zin + D^{-1} (rhs - A zin); with partials, also sum_i rdot_i zout_i;
+// with operm, row r's result goes to zout[operm[r]]; with fin (and no
+// partials) one more workgroup finishes that r.r reduction
 template <typename T, typename TR, typename TZ>
 int sell_sweep(hipStream_t s, const DevSellView &A, const T *dinv, const TR *rhs, const T *zin, TZ *zout,
-               const double *rdot, double *partials, const int *done);
+               const double *rdot, double *partials, const int *done, const int *operm = nullptr,
+               const RrFinish *fin = nullptr);
 // res = rhs - A z
 template <typename T>
 int sell_resid(hipStream_t s, const DevSellView &A, const T *rhs, const T *z, T *res, const int *done);
-// y = A x (FP64); with partials also x.y
-int sell_spmv64(hipStream_t s, const DevSellView &A, const double *x, double *y, double *partials, const int *done);
+// y = A x (FP64); with partials also x.y; with operm, row r's result goes to y[operm[r]]
+int sell_spmv64(hipStream_t s, const DevSellView &A, const double *x, double *y, double *partials, const int *done,
+                const int *operm = nullptr);
+// workgroups (so partials) of a pass over A
+int sell_parts(const DevSellView &A);
+// p = z + beta p_old and q = A p in one pass, with the p.q partials; beta from
+// the r.z partials (see k_cg_product)
+int cg_product(hipStream_t s, const DevSellView &A, const double *z, const double *p_old, double *p, double *q,
+               const double *rz_parts, int rz_n, double *pq_parts, const CgState &st);
 // r = f - A u (FP64)
 int sell_residual64(hipStream_t s, const DevSellView &A, const double *f, const double *u, double *r);
 
@@ -128,16 +148,16 @@ int vec_dot(hipStream_t s, int n, const double *a, const double *b, double *part
 // the current iteration and update the state (see kernels.hip)
 void finish(hipStream_t s, const double *partials, int nparts, FinishMode mode, double *out, const CgState &st);
 void cg_init(hipStream_t s, const CgState &st, double tol2);
-// x += alpha p ; r -= alpha q ; partial r.r
-int cg_update(hipStream_t s, int n, double *x, double *r, const double *p, const double *q, const CgState &st,
-              double *partials);
-// the same, also writing the preconditioner's first sweep from zero,
-// z0 = D^-1 r, and (rT non-null) r in the preconditioner's type
+// x += alpha p ; r -= alpha q ; partial r.r; also the preconditioner's first
+// sweep from zero, z0 = D^-1 r, and (rT non-null) r in the preconditioner's
+// type.  pq_n > 0: p.q is summed from its partials here, else read from st.
 template <typename T>
 int cg_update_prep(hipStream_t s, int n, double *x, double *r, const double *p, const double *q, const CgState &st,
-                   double *partials, const T *dinv, T *z0, T *rT);
-// p = z + beta p, beta = rz[k]/rz[k-1] (p = z at k = 0)
-void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st);
+                   double *partials, const T *dinv, T *z0, T *rT, const double *pq_parts, int pq_n);
+// p = z + beta p, beta = rz[k]/rz[k-1] (p = z at k = 0); rz_n > 0: rz[k] is
+// summed from its partials here
+void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st,
+                  const double *rz_parts = nullptr, int rz_n = 0);
 // y[i] = x[idx[i]]
 void vec_gather(hipStream_t s, int n, const int *idx, const double *x, double *y);
 // y[idx[i]] = x[i]

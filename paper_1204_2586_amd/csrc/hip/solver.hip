@@ -261,7 +261,7 @@ struct aux_handle {
     Work<float> w32;
 
     // CG buffers (internal order)
-    double *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *xi = nullptr, *fi = nullptr;
+    double *r = nullptr, *z = nullptr, *p = nullptr, *p2 = nullptr, *q = nullptr, *xi = nullptr, *fi = nullptr;
     double *partials = nullptr;
     double *scal = nullptr;          // [0] f.f, [1] r0.r0, [2] tol^2 f.f
     int *istate = nullptr;           // [0] iter, [1] done
@@ -377,16 +377,18 @@ struct aux_handle {
     bool use_mf() const { return opt.op == AUX_OP_MATFREE; }
 
     // P^k smoothing sweep zout = zin + D^{-1}(rhs - A zin) with the configured operator
+    // (fin: one more workgroup finishes that r.r reduction, assembled operator
+    // only; operm: the result's order, assembled operator only)
     template <typename T, typename TR, typename TZ>
     int pk_sweep(const T *d, const TR *rhs, const T *zin, TZ *zout, const double *rdot, double *partials,
-                 const int *done)
+                 const int *done, const int *operm = nullptr, const RrFinish *fin = nullptr)
     {
         if (use_mf()) {
             MfView<T> v = mf_view<T>();
             mf_apply<T>(stream, v, zin, mf_Y<T>(), done);
             return mf_sweep<T, TR, TZ>(stream, v, mf_Y<T>(), zin, d, rhs, zout, rdot, partials, done);
         }
-        return sell_sweep<T, TR, TZ>(stream, A.view<T>(), d, rhs, zin, zout, rdot, partials, done);
+        return sell_sweep<T, TR, TZ>(stream, A.view<T>(), d, rhs, zin, zout, rdot, partials, done, operm, fin);
     }
     template <typename T>
     void pk_resid(const T *rhs, const T *z, T *res, const int *done)
@@ -689,6 +691,7 @@ struct aux_handle {
         r = dnew<double>(n);
         z = dnew<double>(n);
         p = dnew<double>(n);
+        if (resum_size()) p2 = dnew<double>(n);
         q = dnew<double>(n);
         xi = dnew<double>(n);
         fi = dnew<double>(n);
@@ -1185,8 +1188,11 @@ struct aux_handle {
     // writes the partial sums of rin . zout and the number of partials is
     // returned.
     // prepped: z = D^-1 r (and the FP32 copy of r) are already in w.za / w.rT
+    // fin: the CG update's r.r reduction, finished beside the first pass that
+    // has a workgroup to spare (rides_finish()); operm: the order of zout
     template <typename T>
-    int apply_B(const double *rin, double *zout, double *rz_partials, const int *done, bool prepped = false)
+    int apply_B(const double *rin, double *zout, double *rz_partials, const int *done, bool prepped = false,
+                const RrFinish *fin = nullptr, const int *operm = nullptr)
     {
         Work<T> &w = work<T>();
         hipStream_t s = stream;
@@ -1205,7 +1211,7 @@ struct aux_handle {
         const T *rT = rTbuf ? (const T *)rTbuf : (const T *)(const void *)rin;
         for (int k = 1; k < nu; k++) {
             pk = pbeg(AUX_PROF_PK_SWEEP);
-            pk_sweep<T, T, T>(d, rT, zc, zn, nullptr, nullptr, done);
+            pk_sweep<T, T, T>(d, rT, zc, zn, nullptr, nullptr, done, nullptr, k == 1 ? fin : nullptr);
             pend(pk);
             std::swap(zc, zn);
         }
@@ -1218,7 +1224,7 @@ struct aux_handle {
             std::swap(zc, zn);
         }
         pk = pbeg(AUX_PROF_PK_LAST);
-        int g = pk_sweep<T, double, double>(d, rin, zc, zout, rin, rz_partials, done);
+        int g = pk_sweep<T, double, double>(d, rin, zc, zout, rin, rz_partials, done, operm);
         pend(pk);
         pend(pb);
         return g;
@@ -1308,15 +1314,19 @@ struct aux_handle {
         RF2 = upload_op2(RF2_host);
     }
 
-    int apply(const double *rin, double *zout, double *rz_partials, const int *done, bool prepped = false)
+    int apply(const double *rin, double *zout, double *rz_partials, const int *done, bool prepped = false,
+              const RrFinish *fin = nullptr, const int *operm = nullptr)
     {
         if (use_mf()) ensure_mf();
         if (opt.precision == AUX_MIXED) {
             ensure_fp32();
-            return apply_B<float>(rin, zout, rz_partials, done, prepped);
+            return apply_B<float>(rin, zout, rz_partials, done, prepped, fin, operm);
         }
-        return apply_B<double>(rin, zout, rz_partials, done, prepped);
+        return apply_B<double>(rin, zout, rz_partials, done, prepped, fin, operm);
     }
+    // whether apply() can finish a reduction on the way: it has a pre-sweep
+    // of the assembled operator
+    bool rides_finish() const { return !use_mf() && opt.nu > 1; }
 
     // ------------------------------------------------------------ CG
     // Device buffers one CG solve reduces into and keeps its state in: the
@@ -1335,13 +1345,37 @@ struct aux_handle {
         return {b.istate, b.istate + 1, b.hist, b.hist + b.hist_cap, b.hist + 2 * b.hist_cap, b.scal, maxit};
     }
 
-    // one CG iteration: q = A p, alpha, x/r update, z = B r, beta, p update
-    // (forming p inside the product, from gathered z and p, measured twice as
-    // slow as the separate update pass)
-    void cg_iteration(const CgState &st, double *part)
+    // How a CG iteration's three inner products are finished.  A launch of
+    // its own costs 2 to 4 us, as much as a pass of a small problem, so with
+    // few partials the consumers add them up themselves (every workgroup in
+    // the same order) and the direction is formed inside the product (two
+    // gathers per entry instead of one, a launch less): eight launches per
+    // iteration instead of eleven.  Solves without and with it, us: P2 6^3
+    // 668 / 591, 13^3 818 / 746, 20^3 1234 / 1189, P3 6^3 1303 / 1245, 12^3
+    // 1756 / 1698, but P4 10^3 (4.2 million entries) 4625 / 4846.  With
+    // thousands of workgroups reading thousands of partials it loses more
+    // (P2 48^3: 7.49 -> 7.65 ms, and the product with two gathers takes 118
+    // instead of 61 us).  r.r, which only the stop test reads, is finished by
+    // a spare workgroup of the pre-sweep at every size.
+    static constexpr int kResumParts = kMaxBlocks / 4;
+    static constexpr int64_t kResumEntries = 3000000;
+    bool resum_size() const
+    {
+        return A.stored <= kResumEntries && sell_parts(A.view<double>()) <= kResumParts &&
+               (disc.ndof + kBlock - 1) / kBlock <= kResumParts;
+    }
+    bool resum() const { return !use_mf() && resum_size(); }
+
+    // one CG iteration: q = A p, alpha, x/r update, z = B r, beta, p update.
+    // In the resum form the iterations alternate between two direction
+    // buffers (odd: the second one is written).
+    void cg_iteration(const CgState &st, double *part, bool odd)
     {
         hipStream_t s = stream;
         int n = disc.ndof;
+        const bool rs = resum();
+        double *part_pq = rs ? part + kResumParts : part, *part_rr = rs ? part + 2 * kResumParts : part;
+        double *pn = rs && odd ? p2 : p;
         int pk = pbeg(AUX_PROF_CG_SPMV);
         int g;
         if (use_mf()) {
@@ -1351,24 +1385,30 @@ struct aux_handle {
             MfView<double> v = mf_view<double>();
             mf_apply<double>(s, v, p, mf_Y64, st.done);
             g = mf_product<double>(s, v, mf_Y64, q, p, part, st.done);
+        } else if (rs) {
+            g = cg_product(s, A.view<double>(), z, odd ? p : p2, pn, q, part, sell_parts(A.view<double>()), part_pq, st);
         } else {
             g = sell_spmv64(s, A.view<double>(), p, q, part, st.done);
         }
         pend(pk);
-        finish(s, part, g, FIN_PQ, nullptr, st);
+        if (!rs) finish(s, part, g, FIN_PQ, nullptr, st);
         // the update also starts the preconditioner: z = D^-1 r
         if (opt.precision == AUX_MIXED) {
             ensure_fp32();
             Work<float> &w = work<float>();
-            g = cg_update_prep<float>(s, n, xi, r, p, q, st, part, dinv32, w.za, w.rT);
+            g = cg_update_prep<float>(s, n, xi, r, pn, q, st, part_rr, dinv32, w.za, w.rT, part_pq, rs ? g : 0);
         } else {
             Work<double> &w = work<double>();
-            g = cg_update_prep<double>(s, n, xi, r, p, q, st, part, dinv64, w.za, nullptr);
+            g = cg_update_prep<double>(s, n, xi, r, pn, q, st, part_rr, dinv64, w.za, nullptr, part_pq, rs ? g : 0);
         }
-        finish(s, part, g, FIN_RR, nullptr, st);
-        g = apply(r, z, part, st.done, true);
-        finish(s, part, g, FIN_RZ, nullptr, st);
-        cg_direction(s, n, z, p, st);
+        const RrFinish fin{part_rr, g, st};
+        const bool ride = rides_finish();
+        if (!ride) finish(s, part_rr, g, FIN_RR, nullptr, st);
+        g = apply(r, z, part, st.done, true, ride ? &fin : nullptr);
+        if (!rs) {
+            finish(s, part, g, FIN_RZ, nullptr, st);
+            cg_direction(s, n, z, p, st);
+        }
     }
 
     // Cached graph of one CG iteration; recaptured when anything its kernels
@@ -1420,8 +1460,8 @@ struct aux_handle {
         // two iterations per graph: half the gaps between graph launches
         const int key[4] = {opt.precision, opt.op, st.maxit, 1};
         return captured(g_single, key, [&]() {
-            cg_iteration(st, partials);
-            cg_iteration(st, partials);
+            cg_iteration(st, partials, false);
+            cg_iteration(st, partials, true);
         });
     }
 
@@ -1461,8 +1501,10 @@ struct aux_handle {
         cg_init(s, st, tol * tol);
         prof_tag = 0;
         g = apply(r, z, partials, st.done);
-        finish(s, partials, g, FIN_RZ, nullptr, st);
-        cg_direction(s, n, z, p, st);
+        if (!resum()) {
+            finish(s, partials, g, FIN_RZ, nullptr, st);
+            cg_direction(s, n, z, p, st);
+        }
 
         // two CG iterations as a HIP graph (its kernels have fixed arguments:
         // the iteration index and the stopping state live in device memory,
@@ -1480,7 +1522,7 @@ struct aux_handle {
                     c += 2;
                 } else {
                     prof_tag = issued + 1;
-                    cg_iteration(st, partials);
+                    cg_iteration(st, partials, issued % 2 != 0);
                     issued++;
                     c++;
                 }
@@ -2924,20 +2966,37 @@ struct aux_handle {
         coef_ready = true;
     }
 
+    // the first sweep reads the caller's order and the last pass writes it
+    // (the matrix-free passes take separate permutations)
+    template <typename T>
+    void gather_prep(const double *rext)
+    {
+        Work<T> &w = work<T>();
+        vec_gather_jacobi0<T>(stream, disc.ndof, perm, dinv<T>(), rext, fi, w.za,
+                              std::is_same<T, float>::value ? w.rT : nullptr);
+    }
     void apply_external(const double *rext, double *zext)
     {
         int n = disc.ndof;
-        vec_gather(stream, n, perm, rext, fi);
-        apply(fi, z, nullptr, nullptr);
-        vec_scatter(stream, n, perm, z, zext);
+        if (use_mf() || prof_on) {
+            vec_gather(stream, n, perm, rext, fi);
+            apply(fi, z, nullptr, nullptr);
+            vec_scatter(stream, n, perm, z, zext);
+            return;
+        }
+        if (opt.precision == AUX_MIXED) {
+            ensure_fp32();
+            gather_prep<float>(rext);
+        } else {
+            gather_prep<double>(rext);
+        }
+        apply(fi, zext, nullptr, nullptr, true, nullptr, perm);
     }
 
     void matvec_external(const double *x, double *y)
     {
-        int n = disc.ndof;
-        vec_gather(stream, n, perm, x, fi);
-        sell_spmv64(stream, A.view<double>(), fi, q, nullptr, nullptr);
-        vec_scatter(stream, n, perm, q, y);
+        vec_gather(stream, disc.ndof, perm, x, fi);
+        sell_spmv64(stream, A.view<double>(), fi, y, nullptr, nullptr, perm);
     }
 
     void ensure_kappa_device()
