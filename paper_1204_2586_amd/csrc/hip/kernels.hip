@@ -6,6 +6,7 @@
 // one pass over A).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <stdexcept>
 
@@ -104,6 +105,23 @@ __device__ __forceinline__ double partials_sum_all(const double *__restrict__ pa
 // the stop code an inner product (r.z or p.Ap) gives: 0 to go on
 __device__ __forceinline__ int product_stop(double s) { return !std::isfinite(s) ? 4 : !(s > 0.0) ? 3 : 0; }
 
+// (one thread) the state of the solve after k iterations with stop flag d, for the host
+__device__ __forceinline__ void report(const CgState &st, int k, int d, double rr)
+{
+    if (!st.report) return;
+    st.report->rr = rr;
+    const double target = st.scal[2];
+    const float ratio = (float)fmin(target > 0.0 ? rr / target : 3e38, 3e38);
+    const unsigned long long w = (unsigned long long)((unsigned)k | (unsigned)d << 28) << 32 | __float_as_uint(ratio);
+    __hip_atomic_store(&st.report->word, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// (one thread) a breakdown at iteration k: the last iterate stands
+__device__ __forceinline__ void stop_solve(const CgState &st, int k, int d)
+{
+    *st.done = d;
+    report(st, k, d, st.rr[k]);
+}
+
 // One workgroup: the sum of a reduction's partials into its CG slot, and what
 // follows from it (the stop flag, the iteration count).
 template <int BS>
@@ -125,11 +143,13 @@ __device__ __forceinline__ void finish_block(const double *__restrict__ partials
         if (!std::isfinite(s)) d = 4;
         else if (s <= st.scal[2]) d = 1;
         else if (k + 1 >= st.maxit) d = 2;
+        if (d) *st.done = d;
+        report(st, k + 1, d, s);
     } else {
         (mode == FIN_PQ ? st.pq : st.rz)[k] = s;
         d = product_stop(s);
+        if (d) stop_solve(st, k, d);
     }
-    if (d) *st.done = d;
 }
 
 // ------------------------------------------------------------------ SELL
@@ -348,7 +368,7 @@ __global__ __launch_bounds__(sell_block<W>()) void k_cg_product(DevSellView A, c
     const int bad = product_stop(rz);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st.rz[k] = rz;
-        if (bad) *st.done = bad;
+        if (bad) stop_solve(st, k, bad);
     }
     if (bad) return;
     const double beta = k > 0 ? rz / st.rz[k - 1] : 0.0;
@@ -565,10 +585,10 @@ __global__ __launch_bounds__(kBlock) void k_finish(const double *__restrict__ pa
     finish_block<kBlock>(partials, nparts, mode, out, st);
 }
 
-__global__ void k_cg_init(CgState st, double tol2)
+// the state of a solve from f.f and r_0.r_0
+__device__ __forceinline__ void cg_state_init(const CgState &st, double f2, double r2, double tol2)
 {
     *st.iter = 0;
-    double f2 = st.scal[0], r2 = st.scal[1];
     st.rr[0] = r2;
     st.scal[2] = tol2 * f2;
     int d = 0;
@@ -576,6 +596,59 @@ __global__ void k_cg_init(CgState st, double tol2)
     else if (r2 <= tol2 * f2) d = 1;     // includes f = 0 with u = 0
     else if (st.maxit <= 0) d = 2;
     *st.done = d;
+    if (st.report) st.report->ff = f2;
+    if (d) report(st, 0, d, r2);
+    else if (st.report) st.report->rr = r2;
+}
+
+__global__ void k_cg_init(CgState st, double tol2) { cg_state_init(st, st.scal[0], st.scal[1], tol2); }
+
+__global__ __launch_bounds__(kBlock) void k_cg_init_sums(const double *__restrict__ partials, int nparts, CgState st,
+                                                         double tol2)
+{
+    const double r2 = partials_sum<kBlock>(partials, nparts), f2 = partials_sum<kBlock>(partials + nparts, nparts);
+    if (threadIdx.x != 0) return;
+    st.scal[0] = f2;
+    st.scal[1] = r2;
+    cg_state_init(st, f2, r2, tol2);
+}
+
+__global__ __launch_bounds__(kBlock) void k_gather_pair(int n, const int *__restrict__ idx,
+                                                        const double *__restrict__ a, const double *__restrict__ b,
+                                                        double *__restrict__ x, double *__restrict__ y)
+{
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        const int j = idx[i];
+        x[i] = a[j];
+        y[i] = b[j];
+    }
+}
+
+// r = f - A u with the partials of r.r, then of f.f, and the first sweep
+template <typename T, int W>
+__global__ __launch_bounds__(sell_block<W>()) void k_cg_first(DevSellView A, const double *__restrict__ f,
+                                                              const double *__restrict__ u, double *__restrict__ r,
+                                                              const T *__restrict__ dinv, T *__restrict__ z0,
+                                                              T *__restrict__ rT, double *partials)
+{
+    double r2 = 0.0, f2 = 0.0;
+    struct In {
+        double f;
+        T d;
+    };
+    sell_rows<double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(u, j); },
+                         [&](int row) { return In{f[row], dinv[row]}; },
+                         [&](int row, double s, const In &in) {
+                             const double v = in.f - s;
+                             const T t = (T)v;
+                             r[row] = v;
+                             z0[row] = in.d * t;
+                             if (rT) rT[row] = t;
+                             r2 += v * v;
+                             f2 += in.f * in.f;
+                         });
+    write_partial<sell_block<W>()>(partials, r2);
+    write_partial<sell_block<W>()>(partials + gridDim.x, f2);
 }
 
 // the update fused with the preconditioner's first sweep from zero:
@@ -597,7 +670,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update_prep(int n, double *__rest
         const int bad = product_stop(pq);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             st.pq[k] = pq;
-            if (bad) *st.done = bad;
+            if (bad) stop_solve(st, k, bad);
         }
         if (bad) return;
     } else {
@@ -630,7 +703,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_direction(int n, const double *__
         const int bad = product_stop(rz);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             st.rz[k] = rz;
-            if (bad) *st.done = bad;
+            if (bad) stop_solve(st, k, bad);
         }
         if (bad) return;
     } else {
@@ -946,6 +1019,23 @@ void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgStat
     else
         hipLaunchKernelGGL(k_cg_direction<false>, dim3(g), dim3(kBlock), 0, s, n, z, p, st, rz_parts, 0);
 }
+
+template <typename T>
+void cg_start(hipStream_t s, const DevSellView &A, const int *perm, const double *f, const double *u, double *fi,
+              double *x, double *r, const T *dinv, T *z0, T *rT, double *partials, const CgState &st, double tol2)
+{
+    hipLaunchKernelGGL(k_gather_pair, dim3(vec_grid(A.n)), dim3(kBlock), 0, s, A.n, perm, f, u, fi, x);
+    int g = 0;
+    WAVES_SWITCH(A, g = std::min(sell_grid<W>(A), kMaxBlocks / 2);
+                 hipLaunchKernelGGL((k_cg_first<T, W>), dim3(g), dim3(sell_block<W>()), 0, s, A, fi, x, r, dinv, z0, rT,
+                                    partials));
+    hipLaunchKernelGGL(k_cg_init_sums, dim3(1), dim3(kBlock), 0, s, partials, g, st, tol2);
+}
+template void cg_start<float>(hipStream_t, const DevSellView &, const int *, const double *, const double *, double *,
+                              double *, double *, const float *, float *, float *, double *, const CgState &, double);
+template void cg_start<double>(hipStream_t, const DevSellView &, const int *, const double *, const double *, double *,
+                               double *, double *, const double *, double *, double *, double *, const CgState &,
+                               double);
 
 void vec_gather(hipStream_t s, int n, const int *idx, const double *x, double *y)
 {

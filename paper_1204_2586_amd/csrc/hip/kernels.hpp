@@ -74,6 +74,16 @@ struct CgState {
     double *rr;          // rr[k] = r_k . r_k
     double *scal;        // [0] f.f, [1] r_0.r_0, [2] tol^2 f.f
     int maxit;
+    struct CgReport *report = nullptr;   // host memory the kernels write to, or null
+};
+
+// What the host sees of a running solve without a copy or a wait: written by
+// the kernels that finish r.r (and by those that stop a solve) into pinned
+// host memory.  word: iterations, stop flag << 28, and in the low half the
+// bits of the float r.r / (tol^2 f.f).
+struct CgReport {
+    unsigned long long word;
+    double rr, ff;
 };
 
 // the r.r reduction of a CG update, finished by a later kernel
@@ -116,6 +126,13 @@ int sell_parts(const DevSellView &A);
 // the r.z partials (see k_cg_product)
 int cg_product(hipStream_t s, const DevSellView &A, const double *z, const double *p_old, double *p, double *q,
                const double *rz_parts, int rz_n, double *pq_parts, const CgState &st);
+// The start of a CG solve: f and u gathered into the internal order (fi, x),
+// then r = fi - A x with the partials of r.r and f.f and the preconditioner's
+// first sweep from zero (z0 = D^-1 r, and with rT non-null r in its type), and
+// the solve's state from them.  partials: 2 kMaxBlocks / 2 words.
+template <typename T>
+void cg_start(hipStream_t s, const DevSellView &A, const int *perm, const double *f, const double *u, double *fi,
+              double *x, double *r, const T *dinv, T *z0, T *rT, double *partials, const CgState &st, double tol2);
 // r = f - A u (FP64)
 int sell_residual64(hipStream_t s, const DevSellView &A, const double *f, const double *u, double *r);
 

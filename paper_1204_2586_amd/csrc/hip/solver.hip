@@ -267,9 +267,9 @@ struct aux_handle {
     int *istate = nullptr;           // [0] iter, [1] done
     double *hist = nullptr;          // rz, pq, rr each [hist_cap]
     int hist_cap = 0;
-    int *host_state = nullptr;       // pinned: iter, done
-    double *host_scal = nullptr;     // pinned: r.r window of the chunk prediction, target, final r.r and f.f,
-                                     // true residual r.r
+    CgReport *cg_report = nullptr;   // pinned: what the kernels report of a running solve
+    static constexpr int kAhead = 4;
+    double *host_scal = nullptr;     // pinned: true residual r.r
     // the last single-vector CG solve: its r_k.r_k history (device), count and f.f
     const double *last_rr = nullptr;
     int last_iters = -1;
@@ -698,7 +698,7 @@ struct aux_handle {
         partials = dnew<double>(kMaxBlocks);
         scal = dnew<double>(8);
         istate = dnew<int>(4);
-        HIPCHECK(hipHostMalloc((void **)&host_state, 4 * sizeof(int), hipHostMallocDefault));
+        HIPCHECK(hipHostMalloc((void **)&cg_report, sizeof(CgReport), hipHostMallocDefault));
         HIPCHECK(hipHostMalloc((void **)&host_scal, 8 * sizeof(double), hipHostMallocDefault));
         ensure_hist(std::max(opt.maxit, 16));
     }
@@ -1342,7 +1342,7 @@ struct aux_handle {
     CgBufs own_cg() const { return {partials, scal, istate, hist, hist_cap}; }
     static CgState cg_state(const CgBufs &b, int maxit)
     {
-        return {b.istate, b.istate + 1, b.hist, b.hist + b.hist_cap, b.hist + 2 * b.hist_cap, b.scal, maxit};
+        return {b.istate, b.istate + 1, b.hist, b.hist + b.hist_cap, b.hist + 2 * b.hist_cap, b.scal, maxit, nullptr};
     }
 
     // How a CG iteration's three inner products are finished.  A launch of
@@ -1491,16 +1491,20 @@ struct aux_handle {
         double *partials = cb.partials, *scal = cb.scal;
         int *istate = cb.istate;
         CgState st = cg_state(cb, maxit);
-        vec_gather(s, n, perm, f, fi);
-        vec_gather(s, n, perm, u, xi);
-        sell_residual64(s, A.view<double>(), fi, xi, r);
-        int g = vec_dot(s, n, fi, fi, partials);
-        finish(s, partials, g, FIN_PLAIN, scal + 0, st);
-        g = vec_dot(s, n, r, r, partials);
-        finish(s, partials, g, FIN_PLAIN, scal + 1, st);
-        cg_init(s, st, tol * tol);
+        st.report = cg_report;
+        cg_report->word = 0;
+        // (with kernel timing on, the preconditioner's first sweep stays a
+        // launch of its own and the one made here is not used)
+        if (opt.precision == AUX_MIXED) {
+            ensure_fp32();
+            Work<float> &w = work<float>();
+            cg_start<float>(s, A.view<double>(), perm, f, u, fi, xi, r, dinv32, w.za, w.rT, partials, st, tol * tol);
+        } else {
+            cg_start<double>(s, A.view<double>(), perm, f, u, fi, xi, r, dinv64, work<double>().za, nullptr, partials, st,
+                             tol * tol);
+        }
         prof_tag = 0;
-        g = apply(r, z, partials, st.done);
+        int g = apply(r, z, partials, st.done, !prof_on);
         if (!resum()) {
             finish(s, partials, g, FIN_RZ, nullptr, st);
             cg_direction(s, n, z, p, st);
@@ -1511,47 +1515,62 @@ struct aux_handle {
         // and iterations past the stop return at once); not used while kernel
         // timing records events
         hipGraphExec_t gexec = use_graph ? iteration_graph(st) : nullptr;
-        int issued = 0, iter = 0, done = 0, chunk = 2;
-        bool first_check = true;
+        // The host watches the report and keeps a few iterations enqueued
+        // ahead of the running one, so the device does not wait for it (a
+        // copy and a wait every few iterations left it idle for 20 to 30 us
+        // each time): at least kAhead until the contraction is known, then
+        // as many as it predicts; a wrong guess costs launches that return
+        // at once (2 us each) or one round trip.
+        int issued = 0, iter = 0, done = 0, limit = kAhead;
+        double seen_ratio = 0.0;
+        int seen_iter = -1;
         while (true) {
-            for (int c = 0; c < chunk && issued < maxit;) {
+            while (issued < std::min(limit, maxit)) {
+                prof_tag = issued + 1;
                 if (gexec) {
-                    prof_tag = issued + 1;
                     HIPCHECK(hipGraphLaunch(gexec, s));
                     issued += 2;
-                    c += 2;
                 } else {
-                    prof_tag = issued + 1;
                     cg_iteration(st, partials, issued % 2 != 0);
                     issued++;
-                    c++;
                 }
             }
-            // one round trip per check: the status, the r.r values of the last
-            // three issued iterations (unless the solve stopped, every issued
-            // iteration ran, so they are those of iterations iter-2..iter) and,
-            // on the first check, the stopping target, all into pinned memory
-            HIPCHECK(hipMemcpyAsync(host_state, istate, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-            const int win = std::min(issued, maxit);
-            if (win >= 2)
-                HIPCHECK(hipMemcpyAsync(host_scal, st.rr + win - 2, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-            if (first_check)
-                HIPCHECK(hipMemcpyAsync(host_scal + 3, st.scal + 2, sizeof(double), hipMemcpyDeviceToHost, s));
-            HIPCHECK(hipStreamSynchronize(s));
-            first_check = false;
-            iter = host_state[0];
-            done = host_state[1];
-            if (done || issued >= maxit) break;
-            // predict the remaining iterations from the observed contraction
-            chunk = 2;
-            if (iter >= 2 && iter == win) {
-                const double *rr = host_scal, target = host_scal[3];
-                if (rr[2] > 0 && rr[0] > rr[2] && target > 0) {
-                    double rate = std::sqrt(rr[2] / rr[0]);
-                    double need = std::log(target / rr[2]) / std::log(rate);
-                    chunk = (int)std::ceil(std::max(1.0, std::min(need, 16.0)));
+            // wait for the stop, or until only two enqueued iterations are left
+            const int most = std::min(issued, maxit);
+            double ratio = 0.0;
+            for (int spin = 1;; spin++) {
+                const unsigned long long w = __atomic_load_n(&cg_report->word, __ATOMIC_RELAXED);
+                iter = (int)(w >> 32 & 0xfffffff);
+                done = (int)(w >> 60);
+                const unsigned bits = (unsigned)w;
+                float fr;
+                std::memcpy(&fr, &bits, sizeof(fr));
+                ratio = fr;
+                if (done || (iter > seen_iter && iter >= std::min(most, limit - 2))) break;
+                if (spin % 4096 == 0) {
+                    const hipError_t e = hipStreamQuery(s);
+                    if (e == hipSuccess) {              // drained: the report is complete
+                        const unsigned long long v = __atomic_load_n(&cg_report->word, __ATOMIC_RELAXED);
+                        iter = (int)(v >> 32 & 0xfffffff);
+                        done = (int)(v >> 60);
+                        if (!done && iter < most) throw AuxError(AUX_EHIP, "the CG iterations ended without a report");
+                        break;
+                    }
+                    if (e != hipErrorNotReady) HIPCHECK(e);
                 }
             }
+            if (done || iter >= maxit) break;
+            limit = iter + kAhead;
+            if (iter > seen_iter && seen_iter >= 0 && seen_ratio > ratio && ratio > 1.0) {
+                const double rate = std::log(seen_ratio / ratio) / (iter - seen_iter);
+                const double need = std::log(ratio) / rate;
+                limit = iter + (int)std::ceil(std::max(1.0, std::min(need, 16.0)));
+            }
+            if (iter > 0) {
+                seen_iter = iter;
+                seen_ratio = ratio;
+            }
+            limit = std::max(limit, iter >= most ? issued + 1 : limit);
         }
         vec_scatter(s, n, perm, xi, u);
         prof_tag = -1;
@@ -1561,12 +1580,10 @@ struct aux_handle {
             sell_residual64(s, A.view<double>(), fi, xi, r);
             const int g2 = vec_dot(s, n, r, r, partials);
             finish(s, partials, g2, FIN_PLAIN, scal + 3, st);
-            HIPCHECK(hipMemcpyAsync(host_scal + 6, scal + 3, sizeof(double), hipMemcpyDeviceToHost, s));
+            HIPCHECK(hipMemcpyAsync(host_scal, scal + 3, sizeof(double), hipMemcpyDeviceToHost, s));
         }
-        HIPCHECK(hipMemcpyAsync(host_scal + 4, st.rr + iter, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHECK(hipMemcpyAsync(host_scal + 5, scal + 0, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHECK(hipStreamSynchronize(s));
-        const double rrv = host_scal[4], ffv = host_scal[5];
+        const double rrv = cg_report->rr, ffv = cg_report->ff;
         last_rr = st.rr;
         last_iters = iter;
         last_ff = ffv;
@@ -1579,7 +1596,7 @@ struct aux_handle {
             info->status = status;
             info->rel_residual = ffv > 0 ? std::sqrt(rrv / ffv) : 0.0;
             info->seconds = seconds_since(t0);
-            info->true_rel_residual = !opt.true_residual ? -1.0 : ffv > 0 ? std::sqrt(host_scal[6] / ffv) : 0.0;
+            info->true_rel_residual = !opt.true_residual ? -1.0 : ffv > 0 ? std::sqrt(host_scal[0] / ffv) : 0.0;
         }
         return status;
     }
@@ -3057,8 +3074,8 @@ struct aux_handle {
         alloc_size.clear();
         for (hipEvent_t e : ev_pool) hipEventDestroy(e);
         ev_pool.clear();
-        if (host_state) hipHostFree(host_state);
-        host_state = nullptr;
+        if (cg_report) hipHostFree(cg_report);
+        cg_report = nullptr;
         if (host_scal) hipHostFree(host_scal);
         host_scal = nullptr;
         if (fg_host) hipHostFree(fg_host);
