@@ -601,8 +601,6 @@ __device__ __forceinline__ void cg_state_init(const CgState &st, double f2, doub
     else if (st.report) st.report->rr = r2;
 }
 
-__global__ void k_cg_init(CgState st, double tol2) { cg_state_init(st, st.scal[0], st.scal[1], tol2); }
-
 __global__ __launch_bounds__(kBlock) void k_cg_init_sums(const double *__restrict__ partials, int nparts, CgState st,
                                                          double tol2)
 {
@@ -985,11 +983,6 @@ int vec_dot(hipStream_t s, int n, const double *a, const double *b, double *part
 void finish(hipStream_t s, const double *partials, int nparts, FinishMode mode, double *out, const CgState &st)
 {
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(kBlock), 0, s, partials, nparts, (int)mode, out, st);
-}
-
-void cg_init(hipStream_t s, const CgState &st, double tol2)
-{
-    hipLaunchKernelGGL(k_cg_init, dim3(1), dim3(1), 0, s, st, tol2);
 }
 
 template <typename T>

@@ -164,7 +164,6 @@ int vec_dot(hipStream_t s, int n, const double *a, const double *b, double *part
 // sum nparts partials; FIN_PLAIN writes out[0]; the others write the CG slot of
 // the current iteration and update the state (see kernels.hip)
 void finish(hipStream_t s, const double *partials, int nparts, FinishMode mode, double *out, const CgState &st);
-void cg_init(hipStream_t s, const CgState &st, double tol2);
 // x += alpha p ; r -= alpha q ; partial r.r; also the preconditioner's first
 // sweep from zero, z0 = D^-1 r, and (rT non-null) r in the preconditioner's
 // type.  pq_n > 0: p.q is summed from its partials here, else read from st.

@@ -1805,7 +1805,7 @@ struct aux_handle {
         std::vector<int32_t> pkeys;  // [np][k-1] pressure node keys
         DevOp Bi, BTi, M;            // FP64 device operators, internal velocity order
         double *mdinv = nullptr;     // 1 / diag(M_p)
-        double *mx = nullptr, *mr = nullptr, *mz = nullptr, *mp = nullptr, *mq = nullptr;
+        double *mx = nullptr, *mr = nullptr, *mz = nullptr, *mp = nullptr, *mp2 = nullptr, *mq = nullptr;
         double *t3 = nullptr;        // velocity scratch [3 n_h]
         double *bi = nullptr, *xi = nullptr;   // internal right-hand side and iterate
         double *part = nullptr, *scal = nullptr, *hist = nullptr;
@@ -1852,11 +1852,11 @@ struct aux_handle {
             for (int e = sk.Mp.ptr[i]; e < sk.Mp.ptr[i + 1]; e++)
                 if (sk.Mp.col[e] == i) dinv[i] = 1.0 / sk.Mp.val[e];
         sk.mdinv = upload(dinv);
-        for (double **v : {&sk.mx, &sk.mr, &sk.mz, &sk.mp, &sk.mq}) *v = dnew<double>(np);
+        for (double **v : {&sk.mx, &sk.mr, &sk.mz, &sk.mp, &sk.mp2, &sk.mq}) *v = dnew<double>(np);
         sk.t3 = dnew<double>((size_t)3 * n);
         sk.bi = dnew<double>((size_t)3 * n + np);
         sk.xi = dnew<double>((size_t)3 * n + np);
-        sk.part = dnew<double>(2 * (size_t)kMaxBlocks);
+        sk.part = dnew<double>(3 * (size_t)kMaxBlocks);
         sk.scal = dnew<double>(8);
         sk.hist = dnew<double>(3 * (size_t)(kMassMaxit + 2));
         sk.istate = (int *)dnew<double>(2);
@@ -1869,44 +1869,24 @@ struct aux_handle {
 
     // sk.mx = M_p^{-1} b (device b [n_p]) by diagonal PCG from zero, stopped
     // at ||r|| <= 1e-6 ||b|| or 200 steps.  The steps run with their state in
-    // device memory, five launches each (product, p.q, update, r.r and r.z,
-    // direction); the host enqueues as many as the last solve took (plus
-    // one) and then two at a time until the stop flag is set.  Returns the
-    // step count.
-    // count steps of the mass-matrix CG, enqueued on the handle's stream
-    void mass_steps(int count, const CgState &st)
-    {
-        hipStream_t s = stream;
-        const DevCsrView Mv = sk.M.view<double>();
-        for (int c = 0; c < count; c++) {
-            int g = mass_product(s, Mv, sk.mp, sk.mq, sk.part, st);
-            finish(s, sk.part, g, FIN_PQ, nullptr, st);
-            g = mass_update(s, sk.np, sk.mx, sk.mr, sk.mp, sk.mq, sk.mdinv, sk.mz, sk.part, st);
-            mass_finish(s, sk.part, g, st);
-            cg_direction(s, sk.np, sk.mz, sk.mp, st);
-        }
-    }
-
+    // device memory; the host enqueues as many as the last solve took (plus
+    // the one whose head sees the stop) and then two at a time until the stop
+    // flag is set.  Returns the step count.
     int mass_solve(const double *b)
     {
         hipStream_t s = stream;
-        const int np = sk.np;
-        CgState st = cg_state(CgBufs{sk.part, sk.scal, sk.istate, sk.hist, kMassMaxit + 2}, kMassMaxit);
-        double *part_rz = sk.part + kMaxBlocks;
-        int g = mass_start(s, np, b, sk.mdinv, sk.mx, sk.mr, sk.mz, sk.part);
-        finish(s, sk.part, g, FIN_PLAIN, sk.scal + 0, st);
-        finish(s, sk.part, g, FIN_PLAIN, sk.scal + 1, st);
-        cg_init(s, st, kMassTol * kMassTol);
-        finish(s, part_rz, g, FIN_RZ, nullptr, st);
-        cg_direction(s, np, sk.mz, sk.mp, st);
+        const CgState st = cg_state(CgBufs{sk.part, sk.scal, sk.istate, sk.hist, kMassMaxit + 2}, kMassMaxit);
+        const MassBufs v{sk.mx, sk.mr, sk.mz, sk.mp, sk.mp2, sk.mq, sk.mdinv, sk.part, sk.part + 2 * kMaxBlocks};
+        int parts = mass_start(s, sk.np, b, sk.mdinv, sk.mx, sk.mr, sk.mz, sk.part, st);
+        const DevCsrView Mv = sk.M.view<double>();
         int issued = 0, chunk = sk.mass_chunk;
         while (true) {
-            const int cnt = std::min(chunk, kMassMaxit - issued);
-            mass_steps(cnt, st);
-            issued += cnt;
+            // (the head of step kMassMaxit stops at the limit)
+            for (int c = 0; c < chunk && issued <= kMassMaxit; c++, issued++)
+                parts = mass_step(s, Mv, issued, kMassTol * kMassTol, v, parts, st);
             HIPCHECK(hipMemcpyAsync(sk.host_state, sk.istate, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
             HIPCHECK(hipStreamSynchronize(s));
-            if (sk.host_state[1] || issued >= kMassMaxit) break;
+            if (sk.host_state[1] || issued > kMassMaxit) break;
             chunk = 2;
         }
         const int steps = sk.host_state[0];

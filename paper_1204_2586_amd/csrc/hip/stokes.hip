@@ -1,10 +1,14 @@
 // Pressure mass-matrix CG of the Stokes preconditioner Q_t (Sec. 5, the
 // Schur complement replaced by the pressure mass matrix, solved by
 // diagonally preconditioned CG as in the paper's Stokes experiments).  FP64.
+//
 // The mass matrix is a few per cent of the velocity work of one Q_t
-// application: the product runs a few lanes per row, the vector steps are
-// grid-stride passes; their reductions write one partial per workgroup that
-// the CG's finish kernel sums in a fixed order.
+// application, but a solve takes 15 to 30 steps, so its launches count.  The
+// reductions write one partial per workgroup, and every workgroup of the
+// kernel that needs a sum adds the partials up itself, in the same order; the
+// step number comes with the launch, so no kernel waits for a bookkeeping
+// launch.  A step is three launches (direction, product, update), or two
+// where the product forms the direction from both gathered vectors.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -15,10 +19,17 @@ namespace auxp {
 
 namespace {
 
+// partial sums per reduction at most: every workgroup of the next kernel reads
+// them all (16 KB from L2), and 2048 workgroups fill the chip
+constexpr int kMassParts = 2048;
+// rows up to which the product forms the direction itself: there a step is
+// bound by its launches
+constexpr int kMassGatherRows = 32768;
+
 inline int mass_grid(int n)
 {
     int g = (n + kBlock - 1) / kBlock;
-    return g < 1 ? 1 : (g > kMaxBlocks ? kMaxBlocks : g);
+    return g < 1 ? 1 : (g > kMassParts ? kMassParts : g);
 }
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -28,8 +39,8 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// partials[blockIdx.x] (and partials2[blockIdx.x]) = the workgroup's sums
-__device__ __forceinline__ void write_pair(double a, double *pa, double b, double *pb)
+// the workgroup's sums of a and b in every thread, in a fixed order
+__device__ __forceinline__ void block_pair(double &a, double &b)
 {
     __shared__ double red[2][kBlock / 64];
     a = wave_sum(a);
@@ -40,23 +51,69 @@ __device__ __forceinline__ void write_pair(double a, double *pa, double b, doubl
         red[1][w] = b;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s0 = 0.0, s1 = 0.0;
-        for (int k = 0; k < kBlock / 64; k++) {
-            s0 += red[0][k];
-            s1 += red[1][k];
-        }
-        pa[blockIdx.x] = s0;
-        if (pb) pb[blockIdx.x] = s1;
+    a = b = 0.0;
+    for (int k = 0; k < kBlock / 64; k++) {
+        a += red[0][k];
+        b += red[1][k];
     }
+    __syncthreads();
+}
+// partials[blockIdx.x] = the workgroup's sum of a, and of b kMaxBlocks further on
+__device__ __forceinline__ void write_pair(double a, double b, double *partials, bool two)
+{
+    block_pair(a, b);
+    if (threadIdx.x == 0) {
+        partials[blockIdx.x] = a;
+        if (two) partials[kMaxBlocks + blockIdx.x] = b;
+    }
+}
+// the sums of n partials (and of the second set) in every thread
+__device__ __forceinline__ void sum_pair(const double *__restrict__ partials, int n, bool two, double &a, double &b)
+{
+    a = b = 0.0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += kBlock) {
+        a += partials[i];
+        if (two) b += partials[kMaxBlocks + i];
+    }
+    block_pair(a, b);
+}
+
+// The head of step k by every workgroup alike: r.r and r.z of the residual
+// after k steps from the partials of the update (or the start), the stop test
+// (tolerance, limit, a non-finite or non-positive sum) and beta.  The first
+// workgroup records them.  True: go on.
+__device__ __forceinline__ bool mass_head(const double *__restrict__ partials, int n, int k, double tol2,
+                                          const CgState &st, double &beta)
+{
+    if (*st.done) return false;
+    double rr, rz;
+    sum_pair(partials, n, true, rr, rz);
+    const double target = k > 0 ? st.scal[2] : tol2 * rr;
+    int d = 0;
+    if (!std::isfinite(rr)) d = 4;
+    else if (rr <= target) d = 1;              // includes b = 0
+    else if (k >= st.maxit) d = 2;
+    else if (!std::isfinite(rz)) d = 4;
+    else if (!(rz > 0.0)) d = 3;
+    beta = k > 0 && !d ? rz / st.rz[k - 1] : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (k == 0) st.scal[2] = target;
+        st.rr[k] = rr;
+        st.rz[k] = rz;
+        *st.iter = k;
+        if (d) *st.done = d;
+    }
+    return d == 0;
 }
 
 __global__ __launch_bounds__(kBlock) void k_mass_start(int n, const double *__restrict__ b,
                                                        const double *__restrict__ dinv, double *__restrict__ x,
                                                        double *__restrict__ r, double *__restrict__ z,
-                                                       double *__restrict__ partials)
+                                                       double *__restrict__ partials, CgState st)
 {
     double bb = 0.0, rz = 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *st.done = 0;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         const double bi = b[i], zi = dinv[i] * bi;
         x[i] = 0.0;
@@ -65,22 +122,45 @@ __global__ __launch_bounds__(kBlock) void k_mass_start(int n, const double *__re
         bb += bi * bi;
         rz += bi * zi;
     }
-    write_pair(bb, partials, rz, partials + kMaxBlocks);
+    write_pair(bb, rz, partials, true);
+}
+
+// p = z + beta p
+__global__ __launch_bounds__(kBlock) void k_mass_direction(int n, const double *__restrict__ z, double *__restrict__ p,
+                                                           const double *__restrict__ partials, int nparts, int k,
+                                                           double tol2, CgState st)
+{
+    double beta;
+    if (!mass_head(partials, nparts, k, tol2, st, beta)) return;
+    if (k == 0) {
+        for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = z[i];
+        return;
+    }
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = z[i] + beta * p[i];
 }
 
 // q = M p with LPR lanes per row (rows of M_p hold 15 entries at P1 and
 // about 40 at P2 on the benchmark meshes; one lane per row left each lane a
 // chain of dependent loads over the whole row, 241 us per product at P2
-// 32^3) and the partial sums of p.q.  (Forming p = z + beta p_old inside the
-// product, from both vectors gathered, measured slower than the separate
-// direction pass: 43.8 against 30.7 + 3.8 us at P2 32^3.)
-template <int LPR>
+// 32^3) and the partial sums of p.q.  DIR: the step's head comes first and
+// p = z + beta p_old is formed for every gathered entry (p and p_old are
+// different buffers).
+template <int LPR, bool DIR>
 __global__ __launch_bounds__(kBlock) void k_mass_product(int n, const int *__restrict__ ptr,
                                                          const int *__restrict__ col, const double *__restrict__ val,
-                                                         const double *__restrict__ p, double *__restrict__ q,
-                                                         double *__restrict__ partials, CgState st)
+                                                         const double *__restrict__ z, const double *__restrict__ p_old,
+                                                         double *__restrict__ p, double *__restrict__ q,
+                                                         const double *__restrict__ head_parts, int nparts, int k,
+                                                         double tol2, double *__restrict__ pq_parts, CgState st)
 {
-    if (*st.done) return;
+    double beta = 0.0;
+    if (DIR) {
+        if (!mass_head(head_parts, nparts, k, tol2, st, beta)) return;
+    } else if (*st.done) {
+        return;
+    }
+    const double *__restrict__ po = k > 0 ? p_old : z;
+    auto at = [&](int j) { return DIR ? z[j] + beta * po[j] : p_old[j]; };
     double pq = 0.0;
     const int sub = threadIdx.x % LPR;
     for (int base = blockIdx.x * (kBlock / LPR); base < n; base += gridDim.x * (kBlock / LPR)) {
@@ -89,26 +169,38 @@ __global__ __launch_bounds__(kBlock) void k_mass_product(int n, const int *__res
         if (row < n) {
             const int e1 = ptr[row + 1];
 #pragma unroll 4
-            for (int e = ptr[row] + sub; e < e1; e += LPR) s += val[e] * p[col[e]];
+            for (int e = ptr[row] + sub; e < e1; e += LPR) s += val[e] * at(col[e]);
         }
 #pragma unroll
         for (int off = LPR / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, LPR);
         if (row < n && sub == 0) {
+            const double pr = at(row);
+            if (DIR) p[row] = pr;
             q[row] = s;
-            pq += p[row] * s;
+            pq += pr * s;
         }
     }
-    write_pair(pq, partials, 0.0, nullptr);
+    write_pair(pq, 0.0, pq_parts, false);
 }
 
+// alpha = rz[k] / p.q: x += alpha p, r -= alpha q, z = D^-1 r, the partials of
+// r.r and r.z
 __global__ __launch_bounds__(kBlock) void k_mass_update(int n, double *__restrict__ x, double *__restrict__ r,
                                                         const double *__restrict__ p, const double *__restrict__ q,
                                                         const double *__restrict__ dinv, double *__restrict__ z,
+                                                        const double *__restrict__ pq_parts, int nparts, int k,
                                                         double *__restrict__ partials, CgState st)
 {
     if (*st.done) return;
-    const int k = *st.iter;
-    const double alpha = st.rz[k] / st.pq[k];
+    double pq, none;
+    sum_pair(pq_parts, nparts, false, pq, none);
+    const int bad = !std::isfinite(pq) ? 4 : !(pq > 0.0) ? 3 : 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st.pq[k] = pq;
+        if (bad) *st.done = bad;
+    }
+    if (bad) return;
+    const double alpha = st.rz[k] / pq;
     double rr = 0.0, rz = 0.0;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         x[i] += alpha * p[i];
@@ -118,48 +210,7 @@ __global__ __launch_bounds__(kBlock) void k_mass_update(int n, double *__restric
         rr += ri * ri;
         rz += ri * zi;
     }
-    write_pair(rr, partials, rz, partials + kMaxBlocks);
-}
-
-// One workgroup: the sums of the r.r and r.z partials (each in a fixed
-// order), then the two finish steps of a CG iteration: r.r closes iteration
-// k (k + 1 recorded, stop on the tolerance, the limit or a non-finite sum),
-// r.z is recorded for k + 1 (stop when not positive) unless the solve stopped.
-__global__ __launch_bounds__(kBlock) void k_mass_finish(const double *__restrict__ partials, int nparts, CgState st)
-{
-    if (*st.done) return;
-    __shared__ double red[2][kBlock / 64];
-    double a = 0.0, b = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += kBlock) {
-        a += partials[i];
-        b += partials[kMaxBlocks + i];
-    }
-    a = wave_sum(a);
-    b = wave_sum(b);
-    if (threadIdx.x % 64 == 0) {
-        red[0][threadIdx.x / 64] = a;
-        red[1][threadIdx.x / 64] = b;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    double rr = 0.0, rz = 0.0;
-    for (int w = 0; w < kBlock / 64; w++) {
-        rr += red[0][w];
-        rz += red[1][w];
-    }
-    const int k = *st.iter;
-    st.rr[k + 1] = rr;
-    *st.iter = k + 1;
-    int d = 0;
-    if (!std::isfinite(rr)) d = 4;
-    else if (rr <= st.scal[2]) d = 1;
-    else if (k + 1 >= st.maxit) d = 2;
-    if (!d) {
-        st.rz[k + 1] = rz;
-        if (!std::isfinite(rz)) d = 4;
-        else if (!(rz > 0.0)) d = 3;
-    }
-    if (d) *st.done = d;
+    write_pair(rr, rz, partials, true);
 }
 
 __global__ __launch_bounds__(kBlock) void k_negate(int n, const double *__restrict__ x, double *__restrict__ y)
@@ -170,40 +221,39 @@ __global__ __launch_bounds__(kBlock) void k_negate(int n, const double *__restri
 }  // namespace
 
 int mass_start(hipStream_t s, int n, const double *b, const double *dinv, double *x, double *r, double *z,
-               double *partials)
+               double *partials, const CgState &st)
 {
     const int g = mass_grid(n);
-    hipLaunchKernelGGL(k_mass_start, dim3(g), dim3(kBlock), 0, s, n, b, dinv, x, r, z, partials);
+    hipLaunchKernelGGL(k_mass_start, dim3(g), dim3(kBlock), 0, s, n, b, dinv, x, r, z, partials, st);
     return g;
 }
 
-int mass_product(hipStream_t s, const DevCsrView &M, const double *p, double *q, double *partials,
-                 const CgState &st)
+int mass_step(hipStream_t s, const DevCsrView &M, int k, double tol2, const MassBufs &v, int nparts, const CgState &st)
 {
-    const int lpr = M.lpr >= 16 ? 16 : (M.lpr >= 8 ? 8 : 4);
-    long long g = ((long long)M.n * lpr + kBlock - 1) / kBlock;
-    g = g < 1 ? 1 : (g > kMaxBlocks ? kMaxBlocks : g);
-    const double *v = (const double *)M.val;
-    if (lpr == 16)
-        hipLaunchKernelGGL(k_mass_product<16>, dim3(g), dim3(kBlock), 0, s, M.n, M.ptr, M.col, v, p, q, partials, st);
-    else if (lpr == 8)
-        hipLaunchKernelGGL(k_mass_product<8>, dim3(g), dim3(kBlock), 0, s, M.n, M.ptr, M.col, v, p, q, partials, st);
-    else
-        hipLaunchKernelGGL(k_mass_product<4>, dim3(g), dim3(kBlock), 0, s, M.n, M.ptr, M.col, v, p, q, partials, st);
-    return (int)g;
-}
-
-void mass_finish(hipStream_t s, const double *partials, int nparts, const CgState &st)
-{
-    hipLaunchKernelGGL(k_mass_finish, dim3(1), dim3(kBlock), 0, s, partials, nparts, st);
-}
-
-int mass_update(hipStream_t s, int n, double *x, double *r, const double *p, const double *q, const double *dinv,
-                double *z, double *partials, const CgState &st)
-{
-    const int g = mass_grid(n);
-    hipLaunchKernelGGL(k_mass_update, dim3(g), dim3(kBlock), 0, s, n, x, r, p, q, dinv, z, partials, st);
-    return g;
+    const int n = M.n, lpr = M.lpr >= 16 ? 16 : (M.lpr >= 8 ? 8 : 4);
+    long long need = ((long long)n * lpr + kBlock - 1) / kBlock;
+    const int g = (int)(need < 1 ? 1 : (need > kMassParts ? kMassParts : need)), gv = mass_grid(n);
+    const bool dir = M.n <= kMassGatherRows;
+    double *p = dir && k % 2 ? v.p2 : v.p;
+    const double *po = !dir ? v.p : k % 2 ? v.p : v.p2;
+    if (!dir)
+        hipLaunchKernelGGL(k_mass_direction, dim3(gv), dim3(kBlock), 0, s, n, v.z, v.p, v.partials, nparts, k, tol2, st);
+#define PRODUCT(L, D)                                                                                               \
+    hipLaunchKernelGGL((k_mass_product<L, D>), dim3(g), dim3(kBlock), 0, s, n, M.ptr, M.col, (const double *)M.val, \
+                       v.z, po, p, v.q, v.partials, nparts, k, tol2, v.pq_parts, st)
+    if (dir) {
+        if (lpr == 16) PRODUCT(16, true);
+        else if (lpr == 8) PRODUCT(8, true);
+        else PRODUCT(4, true);
+    } else {
+        if (lpr == 16) PRODUCT(16, false);
+        else if (lpr == 8) PRODUCT(8, false);
+        else PRODUCT(4, false);
+    }
+#undef PRODUCT
+    hipLaunchKernelGGL(k_mass_update, dim3(gv), dim3(kBlock), 0, s, n, v.x, v.r, p, v.q, v.dinv, v.z, v.pq_parts, g, k,
+                       v.partials, st);
+    return gv;
 }
 
 void vec_negate(hipStream_t s, int n, const double *x, double *y)

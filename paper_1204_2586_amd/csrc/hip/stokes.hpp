@@ -11,22 +11,21 @@
 
 namespace auxp {
 
-// x = 0, r = b, z = D^-1 b (dinv = 1 / diag M); partials[0 .. g) receive
-// the workgroups' shares of b.b and partials[kMaxBlocks + 0 .. g) those of
-// r.z.  Returns g.
+// the vectors of a mass-matrix CG solve, and its partials: two sets, the
+// second kMaxBlocks after the first, and one for p.q
+struct MassBufs {
+    double *x, *r, *z, *p, *p2, *q;
+    const double *dinv;      // 1 / diag M
+    double *partials, *pq_parts;
+};
+// x = 0, r = b, z = D^-1 b, the stop flag cleared; the workgroups' shares of
+// b.b and r.z in the two sets of partials.  Returns their number.
 int mass_start(hipStream_t s, int n, const double *b, const double *dinv, double *x, double *r, double *z,
-               double *partials);
-// q = M p (CSR, a few lanes per row) with the shares of p.q in partials;
-// returns the grid size (skipped once the solve stopped).
-int mass_product(hipStream_t s, const DevCsrView &M, const double *p, double *q, double *partials,
-                 const CgState &st);
-// one workgroup: r.r (partials[0 ..)) closes the step (iteration count, stop
-// test), then r.z (partials[kMaxBlocks ..)) is recorded for the next step
-void mass_finish(hipStream_t s, const double *partials, int nparts, const CgState &st);
-// alpha = rz[k] / pq[k]: x += alpha p, r -= alpha q, z = D^-1 r; shares of
-// r.r in partials[0 .. g) and of r.z in partials[kMaxBlocks ..).  Returns g.
-int mass_update(hipStream_t s, int n, double *x, double *r, const double *p, const double *q, const double *dinv,
-                double *z, double *partials, const CgState &st);
+               double *partials, const CgState &st);
+// Step k (from 0): the stop test on ||r|| (against sqrt(tol2) ||b||), the
+// direction, the product, x, r and z.  nparts: what the call before returned
+// (mass_start's for k = 0).  Every launch after the stop returns at once.
+int mass_step(hipStream_t s, const DevCsrView &M, int k, double tol2, const MassBufs &v, int nparts, const CgState &st);
 // y = -x
 void vec_negate(hipStream_t s, int n, const double *x, double *y);
 
