@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cmath>
 #include <stdexcept>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -42,6 +43,26 @@ __device__ __forceinline__ A group_sum(A v)
 #pragma unroll
     for (int off = LPR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, LPR);
     return v;
+}
+template <int LPR, typename T>
+__device__ __forceinline__ Vec3<T> group_sum(Vec3<T> v)
+{
+    return {group_sum<LPR>(v.a), group_sum<LPR>(v.b), group_sum<LPR>(v.c)};
+}
+
+// an element in another precision
+template <typename X, typename Y>
+struct Cast {
+    static __device__ __forceinline__ X of(const Y &y) { return (X)y; }
+};
+template <typename T, typename S>
+struct Cast<Vec3<T>, Vec3<S>> {
+    static __device__ __forceinline__ Vec3<T> of(const Vec3<S> &y) { return {(T)y.a, (T)y.b, (T)y.c}; }
+};
+template <typename X, typename Y>
+__device__ __forceinline__ X cast(const Y &y)
+{
+    return Cast<X, Y>::of(y);
 }
 
 // sum over the block (BS threads) in a fixed order; valid in thread 0
@@ -180,11 +201,11 @@ __device__ __forceinline__ void load4(const double *p, double v[4])
 
 // Groups h, h + W, ... of a slice (m its meta) for the row of this lane; four
 // accumulators, one per entry of a group.
-template <typename T, int W, typename XF>
-__device__ __forceinline__ T sell_part(const DevSellView &A, const int4 m, int lane, int h, XF x)
+template <typename T, typename X, int W, typename XF>
+__device__ __forceinline__ X sell_part(const DevSellView &A, const int4 m, int lane, int h, XF x)
 {
     const T *__restrict__ val = (const T *)A.val + (size_t)m.x * (4 * kSlice) + 4 * lane;
-    T s0 = T(0), s1 = T(0), s2 = T(0), s3 = T(0);
+    X s0{}, s1{}, s2{}, s3{};
     if (m.z < 0) {
         const unsigned short *__restrict__ off = A.off + (size_t)m.x * (4 * kSlice) + 4 * lane;
         const int2 *__restrict__ base = A.base + (size_t)m.x * 4;
@@ -227,7 +248,7 @@ constexpr int sell_per_block() { return sell_block<W>() / (64 * W); }
 // requested, so the two loads overlap).  With W > 1 the other wavefronts' sums
 // pass through LDS and are added in a fixed order; every thread of the block
 // then runs the same number of steps, so the barriers are uniform.
-template <typename T, int W, typename XF, typename PRE, typename EPI>
+template <typename T, typename X, int W, typename XF, typename PRE, typename EPI>
 __device__ __forceinline__ void sell_rows(const DevSellView &A, int grid, int halt, XF x, PRE pre, EPI epi)
 {
     constexpr int S = sell_per_block<W>();
@@ -243,21 +264,21 @@ __device__ __forceinline__ void sell_rows(const DevSellView &A, int grid, int ha
             if (sl != (int)blockIdx.x * S + q) m = A.meta[sl];
             const int row = sl * kSlice + lane;
             const auto in = pre(min(row, A.n - 1));
-            const T s = sell_part<T, W>(A, m, lane, 0, x);
+            const X s = sell_part<T, X, W>(A, m, lane, 0, x);
             if (row < A.n) epi(row, s, in);
         }
     } else {
-        __shared__ T part[S][W - 1][64];
+        __shared__ X part[S][W - 1][64];
         const int per_step = S * grid;
         const int steps = (A.nslices + per_step - 1) / per_step;
         for (int it = 0; it < steps; it++, sl += per_step) {
             const int row = sl * kSlice + lane;
             decltype(pre(0)) in = {};
-            T s = T(0);
+            X s{};
             if (sl < A.nslices) {
                 if (it > 0) m = A.meta[sl];
                 if (h == 0) in = pre(min(row, A.n - 1));
-                s = sell_part<T, W>(A, m, lane, h, x);
+                s = sell_part<T, X, W>(A, m, lane, h, x);
             }
             if (it > 0) __syncthreads();           // the previous step's sums are consumed
             if (h > 0) part[q][h - 1][lane] = s;
@@ -289,10 +310,10 @@ inline int sell_grid(const DevSellView &A)
 // r.r reduction of the CG update before (nothing here waits for its result;
 // a stop flag it sets is read by the kernels that follow).  operm: row r goes
 // to zout[operm[r]].
-template <typename T, typename TR, typename TZ, bool DOT, bool FIN, int W>
+template <typename T, typename X, typename XR, typename XZ, bool DOT, bool FIN, int W>
 __global__ __launch_bounds__(sell_block<W>()) void k_sell_sweep(DevSellView A, const T *__restrict__ dinv,
-                                                                const TR *__restrict__ rhs, const T *__restrict__ zin,
-                                                                TZ *__restrict__ zout, const double *__restrict__ rdot,
+                                                                const XR *__restrict__ rhs, const X *__restrict__ zin,
+                                                                XZ *__restrict__ zout, const double *__restrict__ rdot,
                                                                 double *partials, const int *done,
                                                                 const int *__restrict__ operm, RrFinish fin)
 {
@@ -304,19 +325,20 @@ __global__ __launch_bounds__(sell_block<W>()) void k_sell_sweep(DevSellView A, c
     const int halt = stop_word(done);
     double acc = 0.0;
     struct In {
-        T z, d, b;
+        X z, b;
+        T d;
         double r;
         int o;
     };
-    sell_rows<T, W>(
+    sell_rows<T, X, W>(
         A, grid, halt, [&](int j) { return at32(zin, j); },
         [&](int row) {
-            return In{zin[row], dinv[row], (T)rhs[row], DOT ? rdot[row] : 0.0, operm ? operm[row] : row};
+            return In{zin[row], cast<X>(rhs[row]), dinv[row], DOT ? rdot[row] : 0.0, operm ? operm[row] : row};
         },
-        [&](int row, T s, const In &in) {
-            T zi = in.z + in.d * (in.b - s);
-            zout[in.o] = (TZ)zi;
-            if (DOT) acc += in.r * (double)(TZ)zi;
+        [&](int row, const X &s, const In &in) {
+            const XZ zi = cast<XZ>(in.z + in.d * (in.b - s));
+            zout[in.o] = zi;
+            if constexpr (DOT) acc += in.r * (double)zi;
         });
     if (DOT) write_partial<sell_block<W>()>(partials, acc);
 }
@@ -326,7 +348,7 @@ __global__ __launch_bounds__(sell_block<W>()) void k_sell_resid(DevSellView A, c
                                                                 const T *__restrict__ z, T *__restrict__ res,
                                                                 const int *done)
 {
-    sell_rows<T, W>(A, (int)gridDim.x, stop_word(done), [&](int j) { return at32(z, j); },
+    sell_rows<T, T, W>(A, (int)gridDim.x, stop_word(done), [&](int j) { return at32(z, j); },
                     [&](int row) { return rhs[row]; }, [&](int row, T s, T b) { res[row] = b - s; });
 }
 
@@ -342,13 +364,22 @@ __global__ __launch_bounds__(sell_block<W>()) void k_sell_spmv64(DevSellView A, 
         double x;
         int o;
     };
-    sell_rows<double, W>(A, (int)gridDim.x, halt, [&](int j) { return at32(x, j); },
+    sell_rows<double, double, W>(A, (int)gridDim.x, halt, [&](int j) { return at32(x, j); },
                          [&](int row) { return In{DOT ? x[row] : 0.0, operm ? operm[row] : row}; },
                          [&](int row, double s, const In &in) {
                              y[in.o] = s;
                              if (DOT) acc += in.x * s;
                          });
     if (DOT) write_partial<sell_block<W>()>(partials, acc);
+}
+
+// y = A x for three vectors
+template <int W>
+__global__ __launch_bounds__(sell_block<W>()) void k_sell_spmv64x3(DevSellView A, const Vec3<double> *__restrict__ x,
+                                                                   Vec3<double> *__restrict__ y)
+{
+    sell_rows<double, Vec3<double>, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(x, j); }, [&](int) { return 0; },
+                                       [&](int row, const Vec3<double> &s, int) { y[row] = s; });
 }
 
 // The CG product with the direction formed on the way: p = z + beta p_old
@@ -374,7 +405,7 @@ __global__ __launch_bounds__(sell_block<W>()) void k_cg_product(DevSellView A, c
     const double beta = k > 0 ? rz / st.rz[k - 1] : 0.0;
     const double *__restrict__ po = k > 0 ? p_old : z;
     double acc = 0.0;
-    sell_rows<double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(z, j) + beta * at32(po, j); },
+    sell_rows<double, double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(z, j) + beta * at32(po, j); },
                          [&](int row) { return z[row] + beta * po[row]; },
                          [&](int row, double s, double pr) {
                              p[row] = pr;
@@ -389,17 +420,17 @@ __global__ __launch_bounds__(sell_block<W>()) void k_sell_residual64(DevSellView
                                                                      const double *__restrict__ u,
                                                                      double *__restrict__ r)
 {
-    sell_rows<double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(u, j); }, [&](int row) { return f[row]; },
+    sell_rows<double, double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(u, j); }, [&](int row) { return f[row]; },
                          [&](int row, double s, double b) { r[row] = b - s; });
 }
 
-template <typename T, typename TR>
-__global__ __launch_bounds__(kBlock) void k_jacobi0(int n, const T *__restrict__ dinv, const TR *__restrict__ r,
-                                                    T *__restrict__ z, T *__restrict__ rT, const int *done)
+template <typename T, typename X, typename XR>
+__global__ __launch_bounds__(kBlock) void k_jacobi0(int n, const T *__restrict__ dinv, const XR *__restrict__ r,
+                                                    X *__restrict__ z, X *__restrict__ rT, const int *done)
 {
     if (stop(done)) return;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-        T ri = (T)r[i];
+        const X ri = cast<X>(r[i]);
         z[i] = dinv[i] * ri;
         if (rT) rT[i] = ri;
     }
@@ -428,27 +459,27 @@ __global__ __launch_bounds__(kBlock) void k_gather_jacobi0(int n, const int *__r
     for (int base_ = blockIdx.x * (kBlock / (LPR)); base_ < (n); base_ += gridDim.x * (kBlock / (LPR)))     \
         for (int row = base_ + threadIdx.x / (LPR), once_ = 1; once_; once_ = 0)
 
-template <int LPR, typename T, typename XF>
-__device__ __forceinline__ T csr_row(const int *__restrict__ ptr, const int *__restrict__ col,
+template <int LPR, typename X, typename T, typename XF>
+__device__ __forceinline__ X csr_row(const int *__restrict__ ptr, const int *__restrict__ col,
                                      const T *__restrict__ val, int row, int sub, XF x)
 {
-    T s = T(0);
+    X s{};
     const int e1 = ptr[row + 1];
 #pragma unroll 8
     for (int e = ptr[row] + sub; e < e1; e += LPR) s += val[e] * x(col[e]);
     return group_sum<LPR>(s);
 }
 
-template <typename T, int LPR, bool ADD>
+template <typename T, typename X, int LPR, bool ADD>
 __global__ __launch_bounds__(kBlock) void k_csr_matvec(int n, const int *__restrict__ ptr, const int *__restrict__ col,
-                                                       const T *__restrict__ val, const T *__restrict__ x,
-                                                       T *__restrict__ y, const int *done)
+                                                       const T *__restrict__ val, const X *__restrict__ x,
+                                                       X *__restrict__ y, const int *done)
 {
     if (stop(done)) return;
     FOR_ROWS(LPR, n)
     {
         if (row < n) {
-            T s = csr_row<LPR>(ptr, col, val, row, sub_, [&](int j) { return x[j]; });
+            const X s = csr_row<LPR, X>(ptr, col, val, row, sub_, [&](int j) { return x[j]; });
             if (sub_ == 0) y[row] = ADD ? y[row] + s : s;
         }
     }
@@ -458,10 +489,10 @@ __global__ __launch_bounds__(kBlock) void k_csr_matvec(int n, const int *__restr
 // MODE 0: y = M x1; 1: y += M x1; 2: y = M [x1; x2] (columns below split
 // index x1).  Every slot is one coalesced load of 64 values and 64 columns;
 // the slot count is uniform over the wavefront.
-template <typename T, int L, int MODE>
+template <typename T, typename X, int L, int MODE>
 __global__ __launch_bounds__(kBlock) void k_ell_matvec(int n, const int *__restrict__ off, const int *__restrict__ col,
-                                                       const T *__restrict__ val, const T *__restrict__ x1,
-                                                       const T *__restrict__ x2, int split, T *__restrict__ y,
+                                                       const T *__restrict__ val, const X *__restrict__ x1,
+                                                       const X *__restrict__ x2, int split, X *__restrict__ y,
                                                        const int *done)
 {
     if (stop(done)) return;
@@ -470,7 +501,7 @@ __global__ __launch_bounds__(kBlock) void k_ell_matvec(int n, const int *__restr
     const int nsl = (n + C - 1) / C;
     for (int sl = blockIdx.x * (kBlock / 64) + (int)(threadIdx.x / 64); sl < nsl; sl += gridDim.x * (kBlock / 64)) {
         const int e1 = off[sl + 1];
-        T acc = T(0);
+        X acc{};
 #pragma unroll 8
         for (int e = off[sl] + lane; e < e1; e += 64) {
             const int j = col[e];
@@ -486,17 +517,17 @@ __global__ __launch_bounds__(kBlock) void k_ell_matvec(int n, const int *__restr
 }
 
 // y = M [x1; x2]: columns below `split` index x1, the others x2
-template <typename T, int LPR>
+template <typename T, typename X, int LPR>
 __global__ __launch_bounds__(kBlock) void k_csr_matvec2(int n, const int *__restrict__ ptr, const int *__restrict__ col,
-                                                        const T *__restrict__ val, const T *__restrict__ x1,
-                                                        const T *__restrict__ x2, int split, T *__restrict__ y,
+                                                        const T *__restrict__ val, const X *__restrict__ x1,
+                                                        const X *__restrict__ x2, int split, X *__restrict__ y,
                                                         const int *done)
 {
     if (stop(done)) return;
     FOR_ROWS(LPR, n)
     {
         if (row < n) {
-            T s = csr_row<LPR>(ptr, col, val, row, sub_, [&](int j) { return j < split ? x1[j] : x2[j - split]; });
+            const X s = csr_row<LPR, X>(ptr, col, val, row, sub_, [&](int j) { return j < split ? x1[j] : x2[j - split]; });
             if (sub_ == 0) y[row] = s;
         }
     }
@@ -512,7 +543,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_vpre(int n, const int *__restric
     FOR_ROWS(LPR, n)
     {
         if (row < n) {
-            T s = csr_row<LPR>(ptr, col, val, row, sub_, [&](int j) { return dinv[j] * b[j]; });
+            const T s = csr_row<LPR, T>(ptr, col, val, row, sub_, [&](int j) { return dinv[j] * b[j]; });
             if (sub_ == 0) {
                 x[row] = dinv[row] * b[row];
                 r[row] = b[row] - s;
@@ -531,7 +562,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_sweep(int n, const int *__restri
     FOR_ROWS(LPR, n)
     {
         if (row < n) {
-            T s = csr_row<LPR>(ptr, col, val, row, sub_, [&](int j) { return x[j]; });
+            const T s = csr_row<LPR, T>(ptr, col, val, row, sub_, [&](int j) { return x[j]; });
             if (sub_ == 0) y[row] = x[row] + dinv[row] * (b[row] - s);
         }
     }
@@ -541,28 +572,28 @@ __global__ __launch_bounds__(kBlock) void k_csr_sweep(int n, const int *__restri
 // at once (at most n / 256 per lane), then a workgroup sum; the rows of the
 // dense cycle (at most 8192) are short enough that one wavefront per row
 // leaves each lane a chain of dependent load rounds.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_dense_gemv(int n, const T *__restrict__ Ainv, const T *__restrict__ b,
-                                                       T *__restrict__ x, const int *done)
+template <typename T, typename X>
+__global__ __launch_bounds__(kBlock) void k_dense_gemv(int n, const T *__restrict__ Ainv, const X *__restrict__ b,
+                                                       X *__restrict__ x, const int *done)
 {
     if (stop(done)) return;
-    __shared__ T red[kBlock / 64];
+    __shared__ X red[kBlock / 64];
     const int w = threadIdx.x / 64, l = threadIdx.x % 64;
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
         const T *__restrict__ row = Ainv + (size_t)i * n;
-        T s0 = T(0), s1 = T(0);
+        X s0{}, s1{};
         int j = threadIdx.x;
         for (; j + kBlock < n; j += 2 * kBlock) {
             s0 += row[j] * b[j];
             s1 += row[j + kBlock] * b[j + kBlock];
         }
         if (j < n) s0 += row[j] * b[j];
-        T s = group_sum<64>(s0 + s1);
+        const X s = group_sum<64>(s0 + s1);
         __syncthreads();                           // red of the previous row is consumed
         if (l == 0) red[w] = s;
         __syncthreads();
         if (threadIdx.x == 0) {
-            T t = T(0);
+            X t{};
             for (int q = 0; q < kBlock / 64; q++) t += red[q];
             x[i] = t;
         }
@@ -634,7 +665,7 @@ __global__ __launch_bounds__(sell_block<W>()) void k_cg_first(DevSellView A, con
         double f;
         T d;
     };
-    sell_rows<double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(u, j); },
+    sell_rows<double, double, W>(A, (int)gridDim.x, 0, [&](int j) { return at32(u, j); },
                          [&](int row) { return In{f[row], dinv[row]}; },
                          [&](int row, double s, const In &in) {
                              const double v = in.f - s;
@@ -713,6 +744,27 @@ __global__ __launch_bounds__(kBlock) void k_cg_direction(int n, const double *__
     }
     const double beta = rz / st.rz[k - 1];
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = z[i] + beta * p[i];
+}
+
+__global__ __launch_bounds__(kBlock) void k_interleave3(int n, const int *__restrict__ idx,
+                                                        const double *__restrict__ x, Vec3<double> *__restrict__ y)
+{
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        const size_t j = idx ? idx[i] : i;
+        y[i] = {x[j], x[j + n], x[j + 2 * (size_t)n]};
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_split3(int n, const int *__restrict__ idx,
+                                                   const Vec3<double> *__restrict__ x, double *__restrict__ y)
+{
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        const size_t j = idx ? idx[i] : i;
+        const Vec3<double> v = x[i];
+        y[j] = v.a;
+        y[j + n] = v.b;
+        y[j + 2 * (size_t)n] = v.c;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_gather(int n, const int *__restrict__ idx, const double *__restrict__ x,
@@ -832,11 +884,11 @@ int pick_lpr(double avg)
 static int vec_grid(long long n) { return grid_cap((n + kBlock - 1) / kBlock); }
 static int rows_grid(int n, int lpr) { return grid_cap(((long long)n * lpr + kBlock - 1) / kBlock); }
 
-template <typename T>
-int vec_jacobi0(hipStream_t s, int n, const T *dinv, const double *r, T *z, T *rT, const int *done)
+template <typename T, typename X, typename XR>
+int vec_jacobi0(hipStream_t s, int n, const T *dinv, const XR *r, X *z, X *rT, const int *done)
 {
     int g = vec_grid(n);
-    hipLaunchKernelGGL((k_jacobi0<T, double>), dim3(g), dim3(kBlock), 0, s, n, dinv, r, z, rT, done);
+    hipLaunchKernelGGL((k_jacobi0<T, X, XR>), dim3(g), dim3(kBlock), 0, s, n, dinv, r, z, rT, done);
     return g;
 }
 
@@ -849,23 +901,34 @@ void vec_gather_jacobi0(hipStream_t s, int n, const int *perm, const T *dinv, co
 template <typename T>
 void vec_jacobi0_t(hipStream_t s, int n, const T *dinv, const T *r, T *z, const int *done)
 {
-    hipLaunchKernelGGL((k_jacobi0<T, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, dinv, r, z, nullptr, done);
+    hipLaunchKernelGGL((k_jacobi0<T, T, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, dinv, r, z, nullptr, done);
 }
 
-template <typename T, typename TR, typename TZ>
-int sell_sweep(hipStream_t s, const DevSellView &A, const T *dinv, const TR *rhs, const T *zin, TZ *zout,
+template <typename T, typename X, typename XR, typename XZ>
+int sell_sweep(hipStream_t s, const DevSellView &A, const T *dinv, const XR *rhs, const X *zin, XZ *zout,
                const double *rdot, double *partials, const int *done, const int *operm, const RrFinish *fin)
 {
     int g = 0;
-#define SWEEP(DOT, FIN)                                                                                             \
-    hipLaunchKernelGGL((k_sell_sweep<T, TR, TZ, DOT, FIN, W>), dim3(g + (FIN ? 1 : 0)), dim3(sell_block<W>()), 0, s, \
-                       A, dinv, rhs, zin, zout, rdot, partials, done, operm, fin ? *fin : RrFinish())
-    WAVES_SWITCH(A, g = sell_grid<W>(A);
-                 if (partials) SWEEP(true, false);
-                 else if (fin) SWEEP(false, true);
-                 else SWEEP(false, false));
+#define SWEEP(DOT, FIN)                                                                                    \
+    hipLaunchKernelGGL((k_sell_sweep<T, X, XR, XZ, DOT, FIN, W>), dim3(g + (FIN ? 1 : 0)),                 \
+                       dim3(sell_block<W>()), 0, s, A, dinv, rhs, zin, zout, rdot, partials, done, operm, \
+                       fin ? *fin : RrFinish())
+    if constexpr (std::is_same<T, X>::value) {
+        WAVES_SWITCH(A, g = sell_grid<W>(A);
+                     if (partials) SWEEP(true, false);
+                     else if (fin) SWEEP(false, true);
+                     else SWEEP(false, false));
+    } else {
+        if (partials || fin) throw std::invalid_argument("sell_sweep: reductions of single vectors only");
+        WAVES_SWITCH(A, g = sell_grid<W>(A); SWEEP(false, false));
+    }
 #undef SWEEP
     return g;
+}
+
+void sell_spmv64x3(hipStream_t s, const DevSellView &A, const Vec3<double> *x, Vec3<double> *y)
+{
+    WAVES_SWITCH(A, hipLaunchKernelGGL((k_sell_spmv64x3<W>), dim3(sell_grid<W>(A)), dim3(sell_block<W>()), 0, s, A, x, y));
 }
 
 template <typename T>
@@ -920,35 +983,35 @@ static int ell_grid(int n, int lanes)
     return grid_cap((slices + kBlock / 64 - 1) / (kBlock / 64));
 }
 
-template <typename T, int MODE>
-void ell_matvec(hipStream_t s, const DevCsrView &M, const T *x1, const T *x2, int split, T *y, const int *done)
+template <typename T, typename X, int MODE>
+void ell_matvec(hipStream_t s, const DevCsrView &M, const X *x1, const X *x2, int split, X *y, const int *done)
 {
-    LPR_SWITCH(M.ell_lanes, hipLaunchKernelGGL((k_ell_matvec<T, L, MODE>), dim3(ell_grid(M.n, L)), dim3(kBlock), 0, s,
+    LPR_SWITCH(M.ell_lanes, hipLaunchKernelGGL((k_ell_matvec<T, X, L, MODE>), dim3(ell_grid(M.n, L)), dim3(kBlock), 0, s,
                                                M.n, M.ell_off, M.ell_col, (const T *)M.ell_val, x1, x2, split, y,
                                                done));
 }
 
-template <typename T>
-void csr_matvec(hipStream_t s, const DevCsrView &M, const T *x, T *y, const int *done)
+template <typename T, typename X>
+void csr_matvec(hipStream_t s, const DevCsrView &M, const X *x, X *y, const int *done)
 {
-    if (M.ell_lanes > 0) return ell_matvec<T, 0>(s, M, x, nullptr, 0, y, done);
-    LPR_SWITCH(M.lpr, hipLaunchKernelGGL((k_csr_matvec<T, L, false>), dim3(rows_grid(M.n, L)), dim3(kBlock), 0, s,
+    if (M.ell_lanes > 0) return ell_matvec<T, X, 0>(s, M, x, nullptr, 0, y, done);
+    LPR_SWITCH(M.lpr, hipLaunchKernelGGL((k_csr_matvec<T, X, L, false>), dim3(rows_grid(M.n, L)), dim3(kBlock), 0, s,
                                          M.n, M.ptr, M.col, (const T *)M.val, x, y, done));
 }
 
-template <typename T>
-void csr_matvec_add(hipStream_t s, const DevCsrView &M, const T *e, T *x, const int *done)
+template <typename T, typename X>
+void csr_matvec_add(hipStream_t s, const DevCsrView &M, const X *e, X *x, const int *done)
 {
-    if (M.ell_lanes > 0) return ell_matvec<T, 1>(s, M, e, nullptr, 0, x, done);
-    LPR_SWITCH(M.lpr, hipLaunchKernelGGL((k_csr_matvec<T, L, true>), dim3(rows_grid(M.n, L)), dim3(kBlock), 0, s,
+    if (M.ell_lanes > 0) return ell_matvec<T, X, 1>(s, M, e, nullptr, 0, x, done);
+    LPR_SWITCH(M.lpr, hipLaunchKernelGGL((k_csr_matvec<T, X, L, true>), dim3(rows_grid(M.n, L)), dim3(kBlock), 0, s,
                                          M.n, M.ptr, M.col, (const T *)M.val, e, x, done));
 }
 
-template <typename T>
-void csr_matvec2(hipStream_t s, const DevCsrView &M, const T *x1, const T *x2, int split, T *y, const int *done)
+template <typename T, typename X>
+void csr_matvec2(hipStream_t s, const DevCsrView &M, const X *x1, const X *x2, int split, X *y, const int *done)
 {
-    if (M.ell_lanes > 0) return ell_matvec<T, 2>(s, M, x1, x2, split, y, done);
-    LPR_SWITCH(M.lpr, hipLaunchKernelGGL((k_csr_matvec2<T, L>), dim3(rows_grid(M.n, L)), dim3(kBlock), 0, s, M.n,
+    if (M.ell_lanes > 0) return ell_matvec<T, X, 2>(s, M, x1, x2, split, y, done);
+    LPR_SWITCH(M.lpr, hipLaunchKernelGGL((k_csr_matvec2<T, X, L>), dim3(rows_grid(M.n, L)), dim3(kBlock), 0, s, M.n,
                                          M.ptr, M.col, (const T *)M.val, x1, x2, split, y, done));
 }
 
@@ -966,11 +1029,11 @@ void csr_sweep(hipStream_t s, const DevCsrView &A, const T *dinv, const T *b, co
                                          A.ptr, A.col, (const T *)A.val, dinv, b, x, y, done));
 }
 
-template <typename T>
-void dense_gemv(hipStream_t s, int n, const T *Ainv, const T *b, T *x, const int *done)
+template <typename T, typename X>
+void dense_gemv(hipStream_t s, int n, const T *Ainv, const X *b, X *x, const int *done)
 {
     // one workgroup per row
-    hipLaunchKernelGGL(k_dense_gemv<T>, dim3(grid_cap(n)), dim3(kBlock), 0, s, n, Ainv, b, x, done);
+    hipLaunchKernelGGL((k_dense_gemv<T, X>), dim3(grid_cap(n)), dim3(kBlock), 0, s, n, Ainv, b, x, done);
 }
 
 int vec_dot(hipStream_t s, int n, const double *a, const double *b, double *partials)
@@ -1030,6 +1093,16 @@ template void cg_start<double>(hipStream_t, const DevSellView &, const int *, co
                                double *, double *, const double *, double *, double *, double *, const CgState &,
                                double);
 
+void vec_interleave3(hipStream_t s, int n, const int *idx, const double *x, Vec3<double> *y)
+{
+    hipLaunchKernelGGL(k_interleave3, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, idx, x, y);
+}
+
+void vec_split3(hipStream_t s, int n, const int *idx, const Vec3<double> *x, double *y)
+{
+    hipLaunchKernelGGL(k_split3, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, idx, x, y);
+}
+
 void vec_gather(hipStream_t s, int n, const int *idx, const double *x, double *y)
 {
     hipLaunchKernelGGL(k_gather, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, idx, x, y);
@@ -1057,25 +1130,32 @@ void kappa_grad(hipStream_t s, int nt, int nloc, const int *dofs, const double *
 }
 
 #define INST(T)                                                                                              \
-    template int vec_jacobi0<T>(hipStream_t, int, const T *, const double *, T *, T *, const int *);         \
     template void vec_jacobi0_t<T>(hipStream_t, int, const T *, const T *, T *, const int *);               \
     template int sell_resid<T>(hipStream_t, const DevSellView &, const T *, const T *, T *, const int *);    \
     template void vec_gather_jacobi0<T>(hipStream_t, int, const int *, const T *, const double *, double *, T *, \
                                         T *);                                                                \
-    template int sell_sweep<T, T, T>(hipStream_t, const DevSellView &, const T *, const T *, const T *, T *, \
-                                     const double *, double *, const int *, const int *, const RrFinish *);  \
-    template void csr_matvec<T>(hipStream_t, const DevCsrView &, const T *, T *, const int *);               \
-    template void csr_matvec_add<T>(hipStream_t, const DevCsrView &, const T *, T *, const int *);           \
-    template void csr_matvec2<T>(hipStream_t, const DevCsrView &, const T *, const T *, int, T *, const int *); \
     template void csr_vpre<T>(hipStream_t, const DevCsrView &, const T *, const T *, T *, T *, const int *); \
     template void csr_sweep<T>(hipStream_t, const DevCsrView &, const T *, const T *, const T *, T *,        \
-                               const int *);                                                                 \
-    template void dense_gemv<T>(hipStream_t, int, const T *, const T *, T *, const int *);
-
+                               const int *);
 INST(double)
 INST(float)
-template int sell_sweep<float, double, double>(hipStream_t, const DevSellView &, const float *, const double *,
-                                               const float *, double *, const double *, double *, const int *,
-                                               const int *, const RrFinish *);
+#define INSTX(T, X, XR)                                                                                        \
+    template int vec_jacobi0<T, X, XR>(hipStream_t, int, const T *, const XR *, X *, X *, const int *);        \
+    template int sell_sweep<T, X, X, X>(hipStream_t, const DevSellView &, const T *, const X *, const X *, X *, \
+                                        const double *, double *, const int *, const int *, const RrFinish *); \
+    template void csr_matvec<T, X>(hipStream_t, const DevCsrView &, const X *, X *, const int *);              \
+    template void csr_matvec_add<T, X>(hipStream_t, const DevCsrView &, const X *, X *, const int *);          \
+    template void csr_matvec2<T, X>(hipStream_t, const DevCsrView &, const X *, const X *, int, X *, const int *); \
+    template void dense_gemv<T, X>(hipStream_t, int, const T *, const X *, X *, const int *);
+INSTX(double, double, double)
+INSTX(float, float, double)
+INSTX(double, Vec3<double>, Vec3<double>)
+INSTX(float, Vec3<float>, Vec3<double>)
+#define INSTM(X, XZ)                                                                                            \
+    template int sell_sweep<float, X, XZ, XZ>(hipStream_t, const DevSellView &, const float *, const XZ *,      \
+                                              const X *, XZ *, const double *, double *, const int *,           \
+                                              const int *, const RrFinish *);
+INSTM(float, double)
+INSTM(Vec3<float>, Vec3<double>)
 
 }  // namespace auxp

@@ -65,6 +65,38 @@ struct DevSellView {
     const int *die_off = nullptr;
 };
 
+// Three values side by side: an element of an interleaved block of three
+// vectors (the velocity components of a Stokes vector).  The kernels written
+// for a scalar element run on it as they are: an operator is read once for
+// the three, and a gathered entry is one load of 12 or 24 bytes.
+template <typename T>
+struct Vec3 {
+    T a, b, c;
+};
+template <typename T>
+__host__ __device__ __forceinline__ Vec3<T> operator+(const Vec3<T> &x, const Vec3<T> &y)
+{
+    return {x.a + y.a, x.b + y.b, x.c + y.c};
+}
+template <typename T>
+__host__ __device__ __forceinline__ Vec3<T> operator-(const Vec3<T> &x, const Vec3<T> &y)
+{
+    return {x.a - y.a, x.b - y.b, x.c - y.c};
+}
+template <typename T>
+__host__ __device__ __forceinline__ Vec3<T> operator*(T s, const Vec3<T> &y)
+{
+    return {s * y.a, s * y.b, s * y.c};
+}
+template <typename T>
+__host__ __device__ __forceinline__ Vec3<T> &operator+=(Vec3<T> &x, const Vec3<T> &y)
+{
+    x.a += y.a;
+    x.b += y.b;
+    x.c += y.c;
+    return x;
+}
+
 // State of a CG solve in device memory.
 struct CgState {
     int *iter;           // completed iterations
@@ -98,9 +130,12 @@ enum FinishMode { FIN_PLAIN = 0, FIN_PQ = 1, FIN_RZ = 2, FIN_RR = 3 };
 // ---- P^k level (SELL).  Kernels that reduce write one partial per
 // workgroup to `partials` (if non-null) and return the grid size used.
 
+// Vectors of the functions below are arrays of elements: T, or Vec3<T> (X, XR
+// and XZ; the operators stay scalar of type T).
+
 // z = D^{-1} r (one sweep from zero); rT = (T) r if rT
-template <typename T>
-int vec_jacobi0(hipStream_t s, int n, const T *dinv, const double *r, T *z, T *rT, const int *done);
+template <typename T, typename X, typename XR>
+int vec_jacobi0(hipStream_t s, int n, const T *dinv, const XR *r, X *z, X *rT, const int *done);
 // z = D^{-1} r for r in the working precision
 template <typename T>
 void vec_jacobi0_t(hipStream_t s, int n, const T *dinv, const T *r, T *z, const int *done);
@@ -110,8 +145,9 @@ void vec_gather_jacobi0(hipStream_t s, int n, const int *perm, const T *dinv, co
 // zout = zin + D^{-1} (rhs - A zin); with partials, also sum_i rdot_i zout_i;
 // with operm, row r's result goes to zout[operm[r]]; with fin (and no
 // partials) one more workgroup finishes that r.r reduction
-template <typename T, typename TR, typename TZ>
-int sell_sweep(hipStream_t s, const DevSellView &A, const T *dinv, const TR *rhs, const T *zin, TZ *zout,
+// (inner products and fin for scalar elements only)
+template <typename T, typename X, typename XR, typename XZ>
+int sell_sweep(hipStream_t s, const DevSellView &A, const T *dinv, const XR *rhs, const X *zin, XZ *zout,
                const double *rdot, double *partials, const int *done, const int *operm = nullptr,
                const RrFinish *fin = nullptr);
 // res = rhs - A z
@@ -120,6 +156,8 @@ int sell_resid(hipStream_t s, const DevSellView &A, const T *rhs, const T *z, T 
 // y = A x (FP64); with partials also x.y; with operm, row r's result goes to y[operm[r]]
 int sell_spmv64(hipStream_t s, const DevSellView &A, const double *x, double *y, double *partials, const int *done,
                 const int *operm = nullptr);
+// the same for three vectors
+void sell_spmv64x3(hipStream_t s, const DevSellView &A, const Vec3<double> *x, Vec3<double> *y);
 // workgroups (so partials) of a pass over A
 int sell_parts(const DevSellView &A);
 // p = z + beta p_old and q = A p in one pass, with the p.q partials; beta from
@@ -137,17 +175,17 @@ void cg_start(hipStream_t s, const DevSellView &A, const int *perm, const double
 int sell_residual64(hipStream_t s, const DevSellView &A, const double *f, const double *u, double *r);
 
 // ---- CSR (AMG levels, transfers)
-template <typename T>
-void csr_matvec(hipStream_t s, const DevCsrView &M, const T *x, T *y, const int *done);
-template <typename T>
-void csr_matvec_add(hipStream_t s, const DevCsrView &M, const T *e, T *x, const int *done);
+template <typename T, typename X>
+void csr_matvec(hipStream_t s, const DevCsrView &M, const X *x, X *y, const int *done);
+template <typename T, typename X>
+void csr_matvec_add(hipStream_t s, const DevCsrView &M, const X *e, X *x, const int *done);
 // z += M e for M with at most w (1..4) entries per row in w column-major
 // slots (slot k of row i at k n + i, padding value 0 at column 0)
-template <typename T>
-void fixed_matvec_add(hipStream_t s, int n, int w, const int *col, const T *val, const T *e, T *z, const int *done);
+template <typename T, typename X>
+void fixed_matvec_add(hipStream_t s, int n, int w, const int *col, const T *val, const X *e, X *z, const int *done);
 // y = M [x1; x2] (columns below split index x1, the rest x2)
-template <typename T>
-void csr_matvec2(hipStream_t s, const DevCsrView &M, const T *x1, const T *x2, int split, T *y, const int *done);
+template <typename T, typename X>
+void csr_matvec2(hipStream_t s, const DevCsrView &M, const X *x1, const X *x2, int split, X *y, const int *done);
 
 // x = D^{-1} b, r = b - A x (V-cycle presmoothing from zero fused with the residual)
 template <typename T>
@@ -156,8 +194,8 @@ void csr_vpre(hipStream_t s, const DevCsrView &A, const T *dinv, const T *b, T *
 template <typename T>
 void csr_sweep(hipStream_t s, const DevCsrView &A, const T *dinv, const T *b, const T *x, T *y, const int *done);
 // x = Ainv b, dense row-major n x n (one workgroup)
-template <typename T>
-void dense_gemv(hipStream_t s, int n, const T *Ainv, const T *b, T *x, const int *done);
+template <typename T, typename X>
+void dense_gemv(hipStream_t s, int n, const T *Ainv, const X *b, X *x, const int *done);
 
 // ---- vectors and CG bookkeeping (FP64)
 int vec_dot(hipStream_t s, int n, const double *a, const double *b, double *partials);
@@ -174,6 +212,10 @@ int cg_update_prep(hipStream_t s, int n, double *x, double *r, const double *p, 
 // summed from its partials here
 void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st,
                   const double *rz_parts = nullptr, int rz_n = 0);
+// three component blocks of n (stride n) to or from n interleaved elements:
+// y[i].c = x[c n + idx[i]], and y[c n + idx[i]] = x[i].c (idx null: i)
+void vec_interleave3(hipStream_t s, int n, const int *idx, const double *x, Vec3<double> *y);
+void vec_split3(hipStream_t s, int n, const int *idx, const Vec3<double> *x, double *y);
 // y[i] = x[idx[i]]
 void vec_gather(hipStream_t s, int n, const int *idx, const double *x, double *y);
 // y[idx[i]] = x[i]

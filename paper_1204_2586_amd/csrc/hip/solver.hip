@@ -259,6 +259,8 @@ struct aux_handle {
 
     Work<double> w64;
     Work<float> w32;
+    Work<Vec3<double>> w64x3;
+    Work<Vec3<float>> w32x3;
 
     // CG buffers (internal order)
     double *r = nullptr, *z = nullptr, *p = nullptr, *p2 = nullptr, *q = nullptr, *xi = nullptr, *fi = nullptr;
@@ -388,7 +390,7 @@ struct aux_handle {
             mf_apply<T>(stream, v, zin, mf_Y<T>(), done);
             return mf_sweep<T, TR, TZ>(stream, v, mf_Y<T>(), zin, d, rhs, zout, rdot, partials, done);
         }
-        return sell_sweep<T, TR, TZ>(stream, A.view<T>(), d, rhs, zin, zout, rdot, partials, done, operm, fin);
+        return sell_sweep<T, T, TR, TZ>(stream, A.view<T>(), d, rhs, zin, zout, rdot, partials, done, operm, fin);
     }
     template <typename T>
     void pk_resid(const T *rhs, const T *z, T *res, const int *done)
@@ -509,8 +511,8 @@ struct aux_handle {
         hipEvent_t a = take_event(), b = take_event();
         auto measure = [&]() {
             auto run = [&]() {
-                if (split > 0) csr_matvec2<T>(stream, op.view<T>(), x, x + split, split, y, nullptr);
-                else csr_matvec<T>(stream, op.view<T>(), x, y, nullptr);
+                if (split > 0) csr_matvec2<T, T>(stream, op.view<T>(), x, x + split, split, y, nullptr);
+                else csr_matvec<T, T>(stream, op.view<T>(), x, y, nullptr);
             };
             run();
             double total = 0.0;
@@ -1085,6 +1087,27 @@ struct aux_handle {
         return *w;
     }
 
+    // vectors of apply3
+    template <typename T>
+    Work<Vec3<T>> &work3()
+    {
+        Work<Vec3<T>> *w;
+        if constexpr (std::is_same<T, float>::value) w = &w32x3;
+        else w = &w64x3;
+        if (!w->ready) {
+            const size_t n = disc.ndof;
+            w->za = dnew<Vec3<T>>(n);
+            w->zb = dnew<Vec3<T>>(n);
+            if (std::is_same<T, float>::value) w->rT = dnew<Vec3<T>>(n);
+            for (auto &L : lev) {
+                w->b.push_back(dnew<Vec3<T>>(L.A.n));
+                w->y.push_back(dnew<Vec3<T>>(L.A.n));
+            }
+            w->ready = true;
+        }
+        return *w;
+    }
+
     template <typename T>
     const T *dinv() const
     {
@@ -1154,32 +1177,41 @@ struct aux_handle {
         else return dcyc64;
     }
 
+    // the composite cycle (fuse_cycle) on elements X of the work w
+    template <typename T, typename X>
+    const X *fused_cycle(Work<X> &w, size_t l, const int *done)
+    {
+        hipStream_t s = stream;
+        const Lev &L = lev[l];
+        if (l + 1 == lev.size()) {
+            dense_gemv<T, X>(s, L.A.n, cinv<T>(), w.b[l], w.y[l], done);
+        } else if (l == dense_first) {
+            dense_gemv<T, X>(s, L.A.n, dcyc<T>(), w.b[l], w.y[l], done);
+        } else {
+            // b' = P^T (I - A D^-1) b; recurse; y = (2 D^-1 - D^-1 A D^-1) b + (P - D^-1 A P) e
+            csr_matvec<T, X>(s, L.down.view<T>(), w.b[l], w.b[l + 1], done);
+            const X *e = fused_cycle<T, X>(w, l + 1, done);
+            csr_matvec2<T, X>(s, L.up.view<T>(), w.b[l], e, L.A.n, w.y[l], done);
+        }
+        return w.y[l];
+    }
+
     template <typename T>
     const T *vcycle(size_t l, const int *done)
     {
         Work<T> &w = work<T>();
+        if (opt.fuse_cycle) return fused_cycle<T, T>(w, l, done);
         hipStream_t s = stream;
         const Lev &L = lev[l];
         if (l + 1 == lev.size()) {
-            dense_gemv<T>(s, L.A.n, cinv<T>(), w.b[l], w.x[l], done);
+            dense_gemv<T, T>(s, L.A.n, cinv<T>(), w.b[l], w.x[l], done);
             return w.x[l];
-        }
-        if (opt.fuse_cycle && l == dense_first) {
-            dense_gemv<T>(s, L.A.n, dcyc<T>(), w.b[l], w.y[l], done);
-            return w.y[l];
-        }
-        if (opt.fuse_cycle) {
-            // b' = P^T (I - A D^-1) b; recurse; y = (2 D^-1 - D^-1 A D^-1) b + (P - D^-1 A P) e
-            csr_matvec<T>(s, L.down.view<T>(), w.b[l], w.b[l + 1], done);
-            const T *e = vcycle<T>(l + 1, done);
-            csr_matvec2<T>(s, L.up.view<T>(), w.b[l], e, L.A.n, w.y[l], done);
-            return w.y[l];
         }
         DevCsrView Av = L.A.view<T>();
         csr_vpre<T>(s, Av, ldinv<T>(l), w.b[l], w.x[l], w.r[l], done);
-        csr_matvec<T>(s, L.R.view<T>(), w.r[l], w.b[l + 1], done);
+        csr_matvec<T, T>(s, L.R.view<T>(), w.r[l], w.b[l + 1], done);
         const T *e = vcycle<T>(l + 1, done);
-        csr_matvec_add<T>(s, L.P.view<T>(), e, w.x[l], done);
+        csr_matvec_add<T, T>(s, L.P.view<T>(), e, w.x[l], done);
         csr_sweep<T>(s, Av, ldinv<T>(l), w.b[l], w.x[l], w.y[l], done);
         return w.y[l];
     }
@@ -1205,7 +1237,7 @@ struct aux_handle {
         int pk = -1;
         if (!prepped) {
             pk = pbeg(AUX_PROF_PK_FIRST);
-            vec_jacobi0<T>(s, disc.ndof, d, rin, zc, rTbuf, done);
+            vec_jacobi0<T, T, double>(s, disc.ndof, d, rin, zc, rTbuf, done);
             pend(pk);
         }
         const T *rT = rTbuf ? (const T *)rTbuf : (const T *)(const void *)rin;
@@ -1242,16 +1274,16 @@ struct aux_handle {
         if (child) {
             int pk = pbeg(AUX_PROF_PK_RESID);
             if (opt.fuse_cycle) {
-                csr_matvec2<T>(s, RF2.view<T>(), rT, zc, disc.ndof, w.nb, done);
+                csr_matvec2<T, T>(s, RF2.view<T>(), rT, zc, disc.ndof, w.nb, done);
             } else {
                 pk_resid<T>(rT, zc, w.res, done);
-                csr_matvec<T>(s, I2Td.view<T>(), w.res, w.nb, done);
+                csr_matvec<T, T>(s, I2Td.view<T>(), w.res, w.nb, done);
             }
             pend(pk);
             pk = pbeg(AUX_PROF_COARSE);
             child->stream = s;
             child->apply_inner<T>(w.nb, w.ne, done);
-            csr_matvec_add<T>(s, I2d.view<T>(), w.ne, zc, done);
+            csr_matvec_add<T, T>(s, I2d.view<T>(), w.ne, zc, done);
             pend(pk);
             return;
         }
@@ -1259,25 +1291,60 @@ struct aux_handle {
         int pk = pbeg(AUX_PROF_PK_RESID);
         if (opt.fuse_cycle) {
             // r_H = I_R r - (I_R A_h) z in one pass
-            csr_matvec2<T>(s, RF.view<T>(), rT, zc, disc.ndof, w.b[0], done);
+            csr_matvec2<T, T>(s, RF.view<T>(), rT, zc, disc.ndof, w.b[0], done);
             pend(pk);
             pk = pbeg(AUX_PROF_COARSE);
         } else {
             pk_resid<T>(rT, zc, w.res, done);
             pend(pk);
             pk = pbeg(AUX_PROF_COARSE);
-            csr_matvec<T>(s, IR.view<T>(), w.res, w.b[0], done);
+            csr_matvec<T, T>(s, IR.view<T>(), w.res, w.b[0], done);
         }
-        const T *e0 = vcycle<T>(0, done);
+        prolongate<T, T>(vcycle<T>(0, done), zc, done);
+        pend(pk);
+    }
+    // z += I_P e
+    template <typename T, typename X>
+    void prolongate(const X *e, X *z, const int *done)
+    {
         if (IPf.w) {
             const T *v;
             if constexpr (std::is_same<T, float>::value) v = IPf.v32;
             else v = IPf.v64;
-            fixed_matvec_add<T>(s, IPf.n, IPf.w, IPf.col, v, e0, zc, done);
+            fixed_matvec_add<T, X>(stream, IPf.n, IPf.w, IPf.col, v, e, z, done);
         } else {
-            csr_matvec_add<T>(s, IP.view<T>(), e0, zc, done);
+            csr_matvec_add<T, X>(stream, IP.view<T>(), e, z, done);
         }
-        pend(pk);
+    }
+
+    // zout = B rin for three interleaved vectors (the velocity components of
+    // a Stokes vector): the passes of apply_B, each operator read once.  Only
+    // where takes3() holds.
+    bool takes3() const { return opt.fuse_cycle && !child && !use_mf() && !lev.empty() && !prof_on; }
+    template <typename T>
+    void apply3(const Vec3<double> *rin, Vec3<double> *zout)
+    {
+        using X = Vec3<T>;
+        Work<X> &w = work3<T>();
+        hipStream_t s = stream;
+        const T *d = dinv<T>();
+        const DevSellView Av = A.view<T>();
+        X *zc = w.za, *zn = w.zb;
+        vec_jacobi0<T, X, Vec3<double>>(s, disc.ndof, d, rin, zc, w.rT, nullptr);
+        const X *rT;
+        if constexpr (std::is_same<T, float>::value) rT = w.rT;
+        else rT = rin;
+        auto sweeps = [&]() {
+            for (int k = 1; k < opt.nu; k++) {
+                sell_sweep<T, X, X, X>(s, Av, d, rT, zc, zn, nullptr, nullptr, nullptr);
+                std::swap(zc, zn);
+            }
+        };
+        sweeps();
+        csr_matvec2<T, X>(s, RF.view<T>(), rT, zc, disc.ndof, w.b[0], nullptr);
+        prolongate<T, X>(fused_cycle<T, X>(w, 0, nullptr), zc, nullptr);
+        sweeps();
+        sell_sweep<T, X, Vec3<double>, Vec3<double>>(s, Av, d, rin, zc, zout, nullptr, nullptr, nullptr);
     }
 
     // zout = B rin with both vectors in the working precision T and no
@@ -1794,8 +1861,13 @@ struct aux_handle {
     // M_p and A^{-1} by the auxiliary-space preconditioner B per component:
     //   y_p = -M_p^{-1} r_p  (diagonal PCG from zero to a relative 1e-6, at
     //   most 200 steps),  y_c = B (r_c - (B^T y_p)_c).
-    // Internal layout of a Stokes vector: the three velocity components, each
-    // in the internal dof order, then the pressure in its key order.
+    // Internal layout of a Stokes vector: the velocity in the internal dof
+    // order with its three components side by side, then the pressure in its
+    // key order.  The passes of the velocity block then read A_h and the
+    // hierarchy once for the three components and gather a dof's components
+    // with one load; handles whose passes do not take three vectors (the
+    // matrix-free operator, the intermediate space, the step-by-step cycle)
+    // split and join the components around them.
     static constexpr double kMassTol = 1e-6;
     static constexpr int kMassMaxit = 200;
     struct StokesData {
@@ -1807,6 +1879,7 @@ struct aux_handle {
         double *mdinv = nullptr;     // 1 / diag(M_p)
         double *mx = nullptr, *mr = nullptr, *mz = nullptr, *mp = nullptr, *mp2 = nullptr, *mq = nullptr;
         double *t3 = nullptr;        // velocity scratch [3 n_h]
+        double *c3 = nullptr, *d3 = nullptr;   // split components [3 n_h], where the passes take single vectors
         double *bi = nullptr, *xi = nullptr;   // internal right-hand side and iterate
         double *part = nullptr, *scal = nullptr, *hist = nullptr;
         int *istate = nullptr;
@@ -1834,7 +1907,7 @@ struct aux_handle {
         const int n = disc.ndof, np = sk.np;
         std::vector<int> map3((size_t)3 * n);
         for (int c = 0; c < 3; c++)
-            for (int i = 0; i < n; i++) map3[(size_t)c * n + i] = c * n + sell.iperm[i];
+            for (int i = 0; i < n; i++) map3[(size_t)c * n + i] = 3 * sell.iperm[i] + c;
         Csr Bi = renumber_cols(sk.B, map3, 3 * n), BTi = transpose(Bi);
         sk.Bi = upload_op(Bi);
         sk.BTi = upload_op(BTi);
@@ -1896,13 +1969,24 @@ struct aux_handle {
         return steps;
     }
 
+    // y_u = f(x_u) per velocity component, through split copies
+    template <typename F>
+    void per_component(const double *x, double *y, F f)
+    {
+        const size_t n = disc.ndof;
+        vec_split3(stream, (int)n, nullptr, (const Vec3<double> *)x, sk.c3);
+        for (int c = 0; c < 3; c++) f(sk.c3 + c * n, sk.d3 + c * n);
+        vec_interleave3(stream, (int)n, nullptr, sk.d3, (Vec3<double> *)y);
+    }
+
     // y = F x (internal layout)
     void stokes_product(const double *x, double *y)
     {
         const size_t n = disc.ndof;
-        for (int c = 0; c < 3; c++) op_product(x + c * n, y + c * n);
-        csr_matvec_add<double>(stream, sk.BTi.view<double>(), x + 3 * n, y, nullptr);   // y_u += B^T x_p
-        csr_matvec<double>(stream, sk.Bi.view<double>(), x, y + 3 * n, nullptr);        // y_p = B x_u
+        if (use_mf()) per_component(x, y, [&](const double *a, double *b) { op_product(a, b); });
+        else sell_spmv64x3(stream, A.view<double>(), (const Vec3<double> *)x, (Vec3<double> *)y);
+        csr_matvec_add<double, double>(stream, sk.BTi.view<double>(), x + 3 * n, y, nullptr);   // y_u += B^T x_p
+        csr_matvec<double, double>(stream, sk.Bi.view<double>(), x, y + 3 * n, nullptr);        // y_p = B x_u
     }
 
     // y = Q_t r (internal layout)
@@ -1912,22 +1996,24 @@ struct aux_handle {
         mass_solve(r + nu);                                   // mx = M_p^{-1} r_p
         vec_negate(stream, sk.np, sk.mx, y + nu);             // y_p = -M_p^{-1} r_p
         HIPCHECK(hipMemcpyAsync(sk.t3, r, nu * sizeof(double), hipMemcpyDeviceToDevice, stream));
-        csr_matvec_add<double>(stream, sk.BTi.view<double>(), sk.mx, sk.t3, nullptr);   // r_u - B^T y_p
-        for (int c = 0; c < 3; c++) apply(sk.t3 + c * n, y + c * n, nullptr, nullptr);
+        csr_matvec_add<double, double>(stream, sk.BTi.view<double>(), sk.mx, sk.t3, nullptr);   // r_u - B^T y_p
+        if (!takes3()) per_component(sk.t3, y, [&](const double *a, double *b) { apply(a, b, nullptr, nullptr); });
+        else if (opt.precision == AUX_MIXED) apply3<float>((const Vec3<double> *)sk.t3, (Vec3<double> *)y);
+        else apply3<double>((const Vec3<double> *)sk.t3, (Vec3<double> *)y);
     }
 
     // external <-> internal Stokes vectors
     void stokes_in(const double *ext, double *in)
     {
         const size_t n = disc.ndof;
-        for (int c = 0; c < 3; c++) vec_gather(stream, (int)n, perm, ext + c * n, in + c * n);
+        vec_interleave3(stream, (int)n, perm, ext, (Vec3<double> *)in);
         HIPCHECK(hipMemcpyAsync(in + 3 * n, ext + 3 * n, (size_t)sk.np * sizeof(double), hipMemcpyDeviceToDevice,
                                 stream));
     }
     void stokes_out(const double *in, double *ext)
     {
         const size_t n = disc.ndof;
-        for (int c = 0; c < 3; c++) vec_scatter(stream, (int)n, perm, in + c * n, ext + c * n);
+        vec_split3(stream, (int)n, perm, (const Vec3<double> *)in, ext);
         HIPCHECK(hipMemcpyAsync(ext + 3 * n, in + 3 * n, (size_t)sk.np * sizeof(double), hipMemcpyDeviceToDevice,
                                 stream));
     }
@@ -1935,6 +2021,10 @@ struct aux_handle {
     void stokes_prepare()
     {
         stokes_setup();
+        if (!takes3() && !sk.c3) {
+            sk.c3 = dnew<double>((size_t)3 * disc.ndof);
+            sk.d3 = dnew<double>((size_t)3 * disc.ndof);
+        }
         if (use_mf()) ensure_mf();
         if (opt.precision == AUX_MIXED) ensure_fp32();
     }
@@ -2874,6 +2964,8 @@ struct aux_handle {
         fused_pre = false;
         release_work(w64);
         release_work(w32);
+        release_work(w64x3);
+        release_work(w32x3);
         // batched forms: rebuilt on their next use
         release_batch();
         auto free_bop = [&](BOp &b) {
