@@ -100,7 +100,7 @@ typedef struct aux_options {
                                 restricted residual as I_R r - (I_R A_h) z; the same linear
                                 operator B as the step-by-step cycle (0), up to rounding */
     int batch_tiles;         /* block products of A_h in the batched solve: 0 one workgroup per
-                                64-row slice; 2 tiles of 16/32/64 consecutive rows whose
+                                64-row slice; 2 tiles of up to 32, 64 or 128 neighbouring rows whose
                                 gathered block rows are staged in LDS (the largest that fits);
                                 1 (default) the faster of the two, timed per block width and
                                 precision (slices when sell_window > 0).  The products are
@@ -186,7 +186,7 @@ typedef struct aux_info {
     int64_t nnz_restrict;    /* entries of the fused restriction [I_R, -I_R A_h] (0 if not fused) */
     int64_t level_nnz_down[32]; /* entries of the fused down operator of level l */
     int64_t level_nnz_up[32];   /* entries of the fused up operator of level l */
-    int32_t batch_tile_rows[2]; /* block products of the last batch width, FP32 and FP64: rows
+    int32_t batch_tile_rows[2]; /* block products of the last batch width, FP32 and FP64: most rows
                                 per LDS tile the batched autotuner chose, 0 = 64-row slices */
     double sell_tune_ms[4];  /* autotuner's time (one FP64 plus one FP32 product, ms) of the
                                 candidate layouts: global sort with 16-bit columns, global

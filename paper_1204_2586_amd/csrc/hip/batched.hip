@@ -34,6 +34,11 @@ inline int grid_cap(long long need)
          row += gridDim.x * (kBlock / (NR)))
 
 inline int brows_grid(int n, int NR) { return grid_cap(((long long)n * NR + kBlock - 1) / kBlock); }
+// Workgroups of the vector passes that end in per-column sums: as many as are
+// resident (8 per compute unit).  Their partials are summed by one workgroup,
+// which reads 512 KB at 32 columns; from 4096 workgroups it took 18 us.
+constexpr int kBatchParts = 2048;
+inline int bsum_grid(int n, int NR) { return std::min(brows_grid(n, NR), kBatchParts); }
 
 // per-column partial sums of a block of BS threads: partials[blockIdx.x * NR + c]
 template <int NR, int BS = kBlock>
@@ -224,112 +229,294 @@ __global__ __launch_bounds__(kBlock) void kb_spmv64(DevSellView A, const double 
 }
 
 // ------------------------------------------------------------------ tiles
-// One workgroup per tile of consecutive (original-order) rows: the tile's
-// distinct gathered block rows (NR words each), its values, column
-// positions and row offsets are staged in LDS with coalesced loads, then
-// each group of NR lanes accumulates its rows from LDS.  A gathered block
-// row crosses L2 once per tile instead of once per entry (5x fewer for P2,
-// 8x for P3 at 64-row tiles).
+// One workgroup per tile of rows along a space-filling curve.  Gathering a
+// block row through L1 for every entry moves nnz * NR words per product (14.7
+// GB in FP64 at P2 64^3 with 32 columns, for 1.7 GB of data); a tile of 64
+// rows has about 270 distinct columns for 1800 entries (P2), so its block
+// rows are staged in LDS once, in pieces of 128 bytes per row, and the
+// entries read them there: LDS delivers 128 bytes per cycle and compute unit,
+// one entry's piece.  Eight lanes take a row (16 bytes each; four lanes for
+// pieces of at most 64 bytes, but in tiles of 32 rows, whose groups are then
+// one per wavefront), a group of eight rows is one or half a
+// wavefront, and a quad loads eight entries of its row at once (two a lane)
+// and broadcasts them by DPP, so values and positions need no LDS.  Rows are
+// sorted by length within a tile and the wavefronts take its groups in a
+// zigzag, which evens their work.  Each die walks its own contiguous range of
+// tiles: neighbouring tiles share most of their block rows in its L2.
+// Measured at P2 64^3 with 32 columns (slices): FP32 sweep 350 us (635), FP64
+// product 720 us (1230), 1.4 and 2.7 GB that cannot be left out, so 4.0 and
+// 3.8 TB/s; the rest is the tiles' shared columns (each is read by four tiles
+// on average) and the turn from one tile to the next.
 
-constexpr int kTileBlock = 512;
+template <typename T, int NR, int TS>
+struct TileShape {
+    static constexpr int RB = NR * (int)sizeof(T);            // bytes of a block row
+    static constexpr int CB = RB < 128 ? RB : 128;            // staged at a time
+    static constexpr int NCH = RB / CB;
+    static constexpr int LPR = CB >= 128 || TS == 32 ? 8 : 4; // lanes per row
+    static constexpr int VL = CB / LPR / (int)sizeof(T);      // columns per lane
+    static constexpr int GP = 8 / LPR;                        // groups a wavefront takes at once
+    // columns whose block rows are requested together (all of a tile up to 64 rows)
+    static constexpr int COLS = TS == 32 ? 160 : 320;
+};
 
-template <typename T>
-__host__ __device__ inline size_t tile_lds_bytes(int max_cols, int max_entries, int tile, int nr)
+template <int Q>
+__device__ __forceinline__ int quad_get(int v)                // lane Q of the quad
 {
-    size_t b = (size_t)max_cols * nr * sizeof(T) + (size_t)max_entries * sizeof(T);
-    b += (size_t)(tile + 1) * sizeof(int) + (size_t)max_cols * sizeof(int);
-    b += (size_t)max_entries * sizeof(unsigned short);
-    return (b + 15) & ~(size_t)15;
+    return __builtin_amdgcn_mov_dpp(v, Q * 0x55, 0xf, 0xf, true);
+}
+template <int Q>
+__device__ __forceinline__ float quad_get(float v)
+{
+    return __int_as_float(quad_get<Q>(__float_as_int(v)));
+}
+template <int Q>
+__device__ __forceinline__ double quad_get(double v)
+{
+    return __hiloint2double(quad_get<Q>(__double2hiint(v)), quad_get<Q>(__double2loint(v)));
 }
 
-// Staging happens in two steps so that no load waits on another global
-// load: the tile's column list, values, positions and row offsets first
-// (coalesced), then the gathered block rows, whose addresses now come from
-// LDS, unrolled so that many rows are in flight per thread.
-template <typename T, int NR, typename XT, typename BODY>
-__device__ __forceinline__ void btile_rows(const DevTilesView &A, const XT *__restrict__ X, BODY body)
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// VL values of a lane
+template <typename T, int VL>
+struct alignas(sizeof(T) * VL) Piece {
+    T v[VL];
+};
+
+template <typename T, int VL, int Q>
+__device__ __forceinline__ void quad_step(const T (&val)[2], const int (&at)[2], const unsigned char *xs, T (&acc)[VL])
 {
-    constexpr int BS = kTileBlock, RG = BS / NR;   // row groups of NR lanes
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const T v = quad_get<Q>(val[k]);
+        const Piece<T, VL> x = *(const Piece<T, VL> *)(xs + quad_get<Q>(at[k]));
+#pragma unroll
+        for (int c = 0; c < VL; c++) acc[c] += v * x.v[c];
+    }
+}
+
+
+// epi(row, first column, chunk, sums, in) for every row and column piece of
+// A X, with in = pre(row, first column) the piece's other inputs.  A tile is a
+// chain of dependent loads (its column list, the block rows, then the row's
+// own words), and few workgroups fit beside each other, so everything that
+// can be is requested ahead: the next tile's column list while this one is
+// computed; group offsets, rows, the first entries and the rows' other inputs
+// before the block rows are waited for; AH blocks of values and positions
+// while the AH before them are used.
+template <typename T, int NR, int TS, int AH, typename PRE, typename EPI>
+__device__ __forceinline__ void btile_rows(const DevTilesView &A, const T *__restrict__ X, PRE pre, EPI epi)
+{
+    using S = TileShape<T, NR, TS>;
+    constexpr int VL = S::VL, SL = S::CB / 16, RS = kBlock / SL;     // staging: lanes per row, rows per step
+    constexpr int U = (S::COLS + RS - 1) / RS;                       // rows in flight per thread
+    constexpr int groups = TS / 8, P = groups / (4 * S::GP);         // passes of a wavefront
     extern __shared__ __align__(16) unsigned char lds_[];
-    T *Xs = (T *)lds_;
-    T *Vs = Xs + (size_t)A.max_cols * NR;
-    int *Rp = (int *)(Vs + A.max_entries);
-    int *Us = Rp + A.tile + 1;
-    unsigned short *Ls = (unsigned short *)(Us + A.max_cols);
     const T *__restrict__ val = (const T *)A.val;
-    const int c = threadIdx.x % NR, g = threadIdx.x / NR;
-    for (int t = blockIdx.x; t < A.ntiles; t += gridDim.x) {
-        const int c0 = A.col_off[t], nc = A.col_off[t + 1] - c0;
-        const int e0 = A.row_ptr[(size_t)t * A.tile], ne = A.row_ptr[(size_t)(t + 1) * A.tile] - e0;
-        __syncthreads();                               // the previous tile is consumed
-        for (int k = threadIdx.x; k < nc; k += BS) Us[k] = A.ucols[c0 + k];
-        for (int k = threadIdx.x; k < ne; k += BS) {
-            Vs[k] = val[e0 + k];
-            Ls[k] = A.lidx[e0 + k];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int l = lane % S::LPR, r = (lane / S::LPR) % 8, half = lane / (8 * S::LPR), q = lane & 3;
+    const int sl = threadIdx.x % SL, su = threadIdx.x / SL;
+    // die d = b % 8 takes tiles [d per, (d + 1) per) (fewer workgroups than dies: all tiles)
+    const int nb = (int)gridDim.x, b = (int)blockIdx.x;
+    int t = b, t_end = A.ntiles, t_step = nb;
+    if (nb >= 8) {
+        const int d = b % 8, per = (A.ntiles + 7) / 8;
+        t = d * per + b / 8;
+        t_end = min(A.ntiles, (d + 1) * per);
+        t_step = (nb - d + 7) / 8;
+    }
+    if (t >= t_end) return;
+    // the values and positions of AH blocks (of the last ones again past the end)
+    struct Ahead {
+        Piece<T, 2> v[AH];
+        ushort2 i[AH];
+    };
+    const int last = A.grp_off[(size_t)A.ntiles * groups] - 1;
+    auto ahead = [&](int blk) {
+        Ahead a;
+#pragma unroll
+        for (int k = 0; k < AH; k++) {
+            const size_t e = (size_t)min(blk + k, last) * 64 + 8 * r + 2 * q;
+            a.v[k] = *(const Piece<T, 2> *)(val + e);
+            a.i[k] = *(const ushort2 *)(A.lidx + e);
         }
-        for (int k = threadIdx.x; k <= A.tile; k += BS) Rp[k] = A.row_ptr[(size_t)t * A.tile + k] - e0;
-        __syncthreads();
-#pragma unroll 8
-        for (int u = g; u < nc; u += RG) Xs[u * NR + c] = (T)X[(size_t)Us[u] * NR + c];
-        __syncthreads();
-        for (int i = g; i < A.tile; i += RG) {
-            const int row = A.rows[(size_t)t * A.tile + i];
-            if (row < 0) continue;
-            T s = T(0);
-            const int k1 = Rp[i + 1];
-#pragma unroll 4
-            for (int k = Rp[i]; k < k1; k++) s += Vs[k] * Xs[(int)Ls[k] * NR + c];
-            body(row, c, s);
+        return a;
+    };
+    Ahead nx;
+    int c0 = A.col_off[t], nc = A.col_off[t + 1] - c0, at[U];
+#pragma unroll
+    for (int k = 0; k < U; k++) at[k] = A.ucols[c0 + min(su + k * RS, nc - 1)];
+    for (; t < t_end; t += t_step) {
+        int b0[P], b1[P], row[P];
+#pragma unroll
+        for (int p = 0; p < P; p++) {
+            const int gi = S::GP * (p * 4 + (p % 2 ? 3 - w : w)) + half;
+            b0[p] = A.grp_off[(size_t)t * groups + gi];
+            b1[p] = A.grp_off[(size_t)t * groups + gi + 1];
+            row[p] = A.rows[(size_t)t * TS + 8 * gi + r];
+        }
+#pragma unroll
+        for (int ch = 0; ch < S::NCH; ch++) {
+            const unsigned char *__restrict__ src = (const unsigned char *)X + ch * S::CB + 16 * sl;
+            u32x4 x[U];
+#pragma unroll
+            for (int k = 0; k < U; k++) x[k] = *(const u32x4 *)(src + (size_t)(unsigned)at[k] * S::RB);
+            nx = ahead(b0[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();                           // the previous pieces are consumed
+            // past the end the last row again (the same words to the same
+            // place), so nothing is conditional and the loads stay together
+#pragma unroll
+            for (int k = 0; k < U; k++) *(u32x4 *)(lds_ + min(su + k * RS, nc - 1) * S::CB + 16 * sl) = x[k];
+            for (int u = su + U * RS; u < nc; u += RS)  // a tile of more columns
+                *(u32x4 *)(lds_ + u * S::CB + 16 * sl) = *(const u32x4 *)(src + (size_t)(unsigned)A.ucols[c0 + u] * S::RB);
+            // (not before: with the block rows' registers they would cost a
+            // wavefront per SIMD in FP64)
+            decltype(pre(0, 0)) in[P];
+#pragma unroll
+            for (int p = 0; p < P; p++) in[p] = pre(max(row[p], 0), ch * (S::CB / (int)sizeof(T)) + l * VL);
+            __syncthreads();
+            if (ch == S::NCH - 1 && t + t_step < t_end) {
+                c0 = A.col_off[t + t_step];
+                nc = A.col_off[t + t_step + 1] - c0;
+#pragma unroll
+                for (int k = 0; k < U; k++) at[k] = A.ucols[c0 + min(su + k * RS, nc - 1)];
+            }
+            const unsigned char *xs = lds_ + l * VL * (int)sizeof(T);
+#pragma unroll
+            for (int p = 0; p < P; p++) {
+                T acc[VL];
+#pragma unroll
+                for (int c = 0; c < VL; c++) acc[c] = T(0);
+                for (int blk = b0[p]; blk < b1[p]; blk += AH) {
+                    const Ahead cur = nx;
+                    nx = ahead(blk + AH < b1[p] ? blk + AH : b0[(p + 1) % P]);
+#pragma unroll
+                    for (int k = 0; k < AH; k++)
+                        if (blk + k < b1[p]) {
+                            const int pos[2] = {(int)cur.i[k].x * S::CB, (int)cur.i[k].y * S::CB};
+                            quad_step<T, VL, 0>(cur.v[k].v, pos, xs, acc);
+                            quad_step<T, VL, 1>(cur.v[k].v, pos, xs, acc);
+                            quad_step<T, VL, 2>(cur.v[k].v, pos, xs, acc);
+                            quad_step<T, VL, 3>(cur.v[k].v, pos, xs, acc);
+                        }
+                }
+                if (b0[p] >= b1[p] && p + 1 < P) nx = ahead(b0[(p + 1) % P]);   // an empty group: the next pass's
+                if (row[p] >= 0) epi(row[p], ch * (S::CB / (int)sizeof(T)) + l * VL, ch, acc, in[p]);
+            }
         }
     }
 }
 
-template <typename T, typename TR, typename TZ, int NR, bool DOT>
-__global__ __launch_bounds__(kTileBlock) void kt_sweep(DevTilesView A, const T *__restrict__ dinv,
-                                                       const TR *__restrict__ RHS, const T *__restrict__ Zin,
-                                                       TZ *__restrict__ Zout, const double *__restrict__ Rdot,
-                                                       double *partials, const int *all_done)
-{
-    if (stop_all(all_done)) return;
-    double acc = 0.0;
-    btile_rows<T, NR>(A, Zin, [&](int row, int c, T s) {
-        size_t o = (size_t)row * NR + c;
-        T zi = Zin[o] + dinv[row] * ((T)RHS[o] - s);
-        Zout[o] = (TZ)zi;
-        if (DOT) acc += Rdot[o] * (double)(TZ)zi;
-    });
-    if (DOT) write_col_partials<NR, kTileBlock>(partials, acc);
-}
+// wavefronts per SIMD the tile kernels' registers leave room for: four FP32
+// workgroups of 64-row tiles fill a compute unit's LDS (a register more than
+// 128 costs one of them: 106 -> 133 us for the last sweep at P2 40^3 with 32
+// columns); in FP64 the limit would only bring scratch memory
+template <typename T, int NR, int TS>
+constexpr int tile_waves() { return TS <= 64 && sizeof(T) == 4 && TileShape<T, NR, TS>::NCH == 1 ? 4 : 1; }
 
-template <typename T, int NR>
-__global__ __launch_bounds__(kTileBlock) void kt_resid(DevTilesView A, const T *__restrict__ RHS,
-                                                       const T *__restrict__ Z, T *__restrict__ Res,
-                                                       const int *all_done)
+// per-column partial sums of a tile kernel: dot[chunk][column of the lane]
+template <typename T, int NR, int TS>
+__device__ __forceinline__ void btile_partials(double *partials, double (&dot)[TileShape<T, NR, TS>::NCH][TileShape<T, NR, TS>::VL])
 {
-    if (stop_all(all_done)) return;
-    btile_rows<T, NR>(A, Z, [&](int row, int c, T s) {
-        size_t o = (size_t)row * NR + c;
-        Res[o] = RHS[o] - s;
-    });
-}
-
-template <int NR, bool DOT, bool RESID>
-__global__ __launch_bounds__(kTileBlock) void kt_spmv64(DevTilesView A, const double *__restrict__ X,
-                                                        double *__restrict__ Y, const double *__restrict__ F,
-                                                        double *partials, const int *all_done)
-{
-    if (stop_all(all_done)) return;
-    double acc = 0.0;
-    btile_rows<double, NR>(A, X, [&](int row, int c, double s) {
-        size_t o = (size_t)row * NR + c;
-        if (RESID) {
-            Y[o] = F[o] - s;
-        } else {
-            Y[o] = s;
-            if (DOT) acc += X[o] * s;
+    using S = TileShape<T, NR, TS>;
+    __shared__ double red[kBlock / 64][NR];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l = lane % S::LPR;
+#pragma unroll
+    for (int ch = 0; ch < S::NCH; ch++)
+#pragma unroll
+        for (int c = 0; c < S::VL; c++) {
+            double v = dot[ch][c];
+#pragma unroll
+            for (int off = 32; off >= S::LPR; off >>= 1) v += __shfl_xor(v, off, 64);
+            if (lane < S::LPR) red[w][ch * (S::CB / (int)sizeof(T)) + l * S::VL + c] = v;
         }
-    });
-    if (DOT) write_col_partials<NR, kTileBlock>(partials, acc);
+    __syncthreads();
+    if (threadIdx.x < NR) {
+        double v = 0.0;
+        for (int k = 0; k < kBlock / 64; k++) v += red[k][threadIdx.x];
+        partials[(size_t)blockIdx.x * NR + threadIdx.x] = v;
+    }
+}
+
+// DOT: the partials of RHS . Zout
+template <typename T, typename TR, typename TZ, int NR, int TS, bool DOT>
+__global__ __launch_bounds__(kBlock, (tile_waves<T, NR, TS>())) void kt_sweep(
+    DevTilesView A, const T *__restrict__ dinv, const TR *__restrict__ RHS, const T *__restrict__ Zin,
+    TZ *__restrict__ Zout, double *partials, const int *all_done)
+{
+    if (stop_all(all_done)) return;
+    using S = TileShape<T, NR, TS>;
+    constexpr int VL = S::VL;
+    double dot[S::NCH][VL] = {};
+    struct In {
+        Piece<T, VL> z;
+        Piece<TR, VL> b;
+        T d;
+    };
+    btile_rows<T, NR, TS, DOT && sizeof(T) == 4 ? 3 : 4>(
+        A, Zin,
+        [&](int row, int col) {
+            const size_t o = (size_t)row * NR + col;
+            return In{*(const Piece<T, VL> *)(Zin + o), *(const Piece<TR, VL> *)(RHS + o), dinv[row]};
+        },
+        [&](int row, int col, int ch, const T (&s)[VL], const In &in) {
+            const size_t o = (size_t)row * NR + col;
+            Piece<TZ, VL> out;
+#pragma unroll
+            for (int c = 0; c < VL; c++) out.v[c] = (TZ)(in.z.v[c] + in.d * ((T)in.b.v[c] - s[c]));
+            *(Piece<TZ, VL> *)(Zout + o) = out;
+            if constexpr (DOT)
+#pragma unroll
+                for (int c = 0; c < VL; c++) dot[ch][c] += (double)in.b.v[c] * (double)out.v[c];
+        });
+    if constexpr (DOT) btile_partials<T, NR, TS>(partials, dot);
+}
+
+template <typename T, int NR, int TS>
+__global__ __launch_bounds__(kBlock, (tile_waves<T, NR, TS>())) void kt_resid(
+    DevTilesView A, const T *__restrict__ RHS, const T *__restrict__ Z, T *__restrict__ Res, const int *all_done)
+{
+    if (stop_all(all_done)) return;
+    constexpr int VL = TileShape<T, NR, TS>::VL;
+    btile_rows<T, NR, TS, 4>(
+        A, Z, [&](int row, int col) { return *(const Piece<T, VL> *)(RHS + (size_t)row * NR + col); },
+        [&](int row, int col, int, const T (&s)[VL], Piece<T, VL> out) {
+#pragma unroll
+            for (int c = 0; c < VL; c++) out.v[c] -= s[c];
+            *(Piece<T, VL> *)(Res + (size_t)row * NR + col) = out;
+        });
+}
+
+// RESID: Y = F - A X, else Y = A X (DOT: with the partials of X . Y)
+template <int NR, int TS, bool DOT, bool RESID>
+__global__ __launch_bounds__(kBlock) void kt_spmv64(DevTilesView A, const double *__restrict__ X,
+                                                    double *__restrict__ Y, const double *__restrict__ F,
+                                                    double *partials, const int *all_done)
+{
+    if (stop_all(all_done)) return;
+    using S = TileShape<double, NR, TS>;
+    constexpr int VL = S::VL;
+    double dot[S::NCH][VL] = {};
+    using In = Piece<double, VL>;
+    btile_rows<double, NR, TS, 4>(
+        A, X,
+        [&](int row, int col) {
+            In in = {};
+            if (DOT || RESID) in = *(const In *)((RESID ? F : X) + (size_t)row * NR + col);
+            return in;
+        },
+        [&](int row, int col, int ch, const double (&s)[VL], const In &in) {
+            In out;
+#pragma unroll
+            for (int c = 0; c < VL; c++) out.v[c] = RESID ? in.v[c] - s[c] : s[c];
+            *(In *)(Y + (size_t)row * NR + col) = out;
+            if constexpr (DOT)
+#pragma unroll
+                for (int c = 0; c < VL; c++) dot[ch][c] += in.v[c] * s[c];
+        });
+    if constexpr (DOT) btile_partials<double, NR, TS>(partials, dot);
 }
 
 // ------------------------------------------------------- AMG levels, transfers
@@ -528,33 +715,8 @@ __global__ void kb_cg_init(BCgState st, double tol2, const double *ff, const dou
     }
 }
 
-template <int NR>
-__global__ __launch_bounds__(kBlock) void kb_cg_update(int n, double *__restrict__ X, double *__restrict__ R,
-                                                       const double *__restrict__ P, const double *__restrict__ Q,
-                                                       BCgState st, double *partials)
-{
-    if (*st.all_done) return;
-    const int k = *st.k;
-    const int c = threadIdx.x % NR;
-    const bool active = st.done[c] == 0;
-    const double alpha = active ? st.rz[(size_t)k * NR + c] / st.pq[(size_t)k * NR + c] : 0.0;
-    double acc = 0.0;
-    FOR_BROWS(NR, n)
-    {
-        size_t o = (size_t)row * NR + c_;
-        double ri = R[o];
-        if (active) {
-            X[o] += alpha * P[o];
-            ri -= alpha * Q[o];
-            R[o] = ri;
-        }
-        acc += ri * ri;
-    }
-    write_col_partials<NR>(partials, acc);
-}
-
-// the update fused with the preconditioner's first sweep from zero (the
-// expressions of kb_jacobi0): Z0 = D^-1 R and RT = R in the type T
+// X += alpha P, R -= alpha Q with the partials of R . R, and the
+// preconditioner's first sweep from zero (the expressions of kb_jacobi0): Z0 = D^-1 R and RT = R in the type T
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void kb_cg_update_prep(int n, double *__restrict__ X, double *__restrict__ R,
                                                             const double *__restrict__ P,
@@ -633,29 +795,38 @@ __global__ __launch_bounds__(kBlock) void kb_scatter(int n, int ld, const int *_
     default: { constexpr int NR = 64; CALL; } break;   \
     }
 
-constexpr size_t kTileLdsMax = 40 * 1024;   // leaves room for several workgroups per CU
+// two workgroups per compute unit
+constexpr size_t kTileLdsMax = 64 * 1024;
 
 size_t btile_lds(const DevTilesView &A, int nr, int s)
 {
-    size_t b = s == 8 ? tile_lds_bytes<double>(A.max_cols, A.max_entries, A.tile, nr)
-                      : tile_lds_bytes<float>(A.max_cols, A.max_entries, A.tile, nr);
-    return b <= kTileLdsMax ? b : 0;
+    if (A.ntiles == 0) return 0;                        // not built for this operator
+    const size_t b = (size_t)A.max_cols * std::min(128, nr * s);
+    return b <= kTileLdsMax ? std::max<size_t>(b, 16) : 0;
 }
 
-inline int btile_grid(const DevTilesView &A) { return grid_cap(A.ntiles); }
+// A tile kernel's workgroups walk several tiles each: at most 1024, as many
+// as are resident with 40 KB of LDS each, so the per-column partial sums of a
+// reduction stay few
+inline int btile_grid(const DevTilesView &A) { return std::max(1, std::min(A.ntiles, 1024)); }
+
+#define TILE_SWITCH(A, CALL)                              \
+    if ((A).tile == 32) { constexpr int TS = 32; CALL; }        \
+    else if ((A).tile == 64) { constexpr int TS = 64; CALL; }   \
+    else { constexpr int TS = 128; CALL; }
 
 template <typename T, typename TR, typename TZ>
 int btile_sweep(hipStream_t s, int nr, const DevTilesView &A, const T *dinv, const TR *RHS, const T *Zin, TZ *Zout,
-                const double *Rdot, double *partials, const int *all_done)
+                double *partials, const int *all_done)
 {
     const int g = btile_grid(A);
     const size_t lds = btile_lds(A, nr, sizeof(T));
     if (partials) {
-        NR_SWITCH(nr, hipLaunchKernelGGL((kt_sweep<T, TR, TZ, NR, true>), dim3(g), dim3(kTileBlock), lds, s, A, dinv, RHS,
-                                         Zin, Zout, Rdot, partials, all_done));
+        NR_SWITCH(nr, TILE_SWITCH(A, hipLaunchKernelGGL((kt_sweep<T, TR, TZ, NR, TS, true>), dim3(g), dim3(kBlock), lds, s,
+                                                        A, dinv, RHS, Zin, Zout, partials, all_done)));
     } else {
-        NR_SWITCH(nr, hipLaunchKernelGGL((kt_sweep<T, TR, TZ, NR, false>), dim3(g), dim3(kTileBlock), lds, s, A, dinv,
-                                         RHS, Zin, Zout, Rdot, partials, all_done));
+        NR_SWITCH(nr, TILE_SWITCH(A, hipLaunchKernelGGL((kt_sweep<T, TR, TZ, NR, TS, false>), dim3(g), dim3(kBlock), lds,
+                                                        s, A, dinv, RHS, Zin, Zout, partials, all_done)));
     }
     return g;
 }
@@ -665,7 +836,8 @@ int btile_resid(hipStream_t s, int nr, const DevTilesView &A, const T *RHS, cons
 {
     const int g = btile_grid(A);
     const size_t lds = btile_lds(A, nr, sizeof(T));
-    NR_SWITCH(nr, hipLaunchKernelGGL((kt_resid<T, NR>), dim3(g), dim3(kTileBlock), lds, s, A, RHS, Z, Res, all_done));
+    NR_SWITCH(nr, TILE_SWITCH(A, hipLaunchKernelGGL((kt_resid<T, NR, TS>), dim3(g), dim3(kBlock), lds, s, A, RHS, Z, Res,
+                                                    all_done)));
     return g;
 }
 
@@ -675,11 +847,11 @@ int btile_spmv64(hipStream_t s, int nr, const DevTilesView &A, const double *X, 
     const int g = btile_grid(A);
     const size_t lds = btile_lds(A, nr, 8);
     if (partials) {
-        NR_SWITCH(nr, hipLaunchKernelGGL((kt_spmv64<NR, true, false>), dim3(g), dim3(kTileBlock), lds, s, A, X, Y,
-                                         (const double *)nullptr, partials, all_done));
+        NR_SWITCH(nr, TILE_SWITCH(A, hipLaunchKernelGGL((kt_spmv64<NR, TS, true, false>), dim3(g), dim3(kBlock), lds, s, A,
+                                                        X, Y, (const double *)nullptr, partials, all_done)));
     } else {
-        NR_SWITCH(nr, hipLaunchKernelGGL((kt_spmv64<NR, false, false>), dim3(g), dim3(kTileBlock), lds, s, A, X, Y,
-                                         (const double *)nullptr, partials, all_done));
+        NR_SWITCH(nr, TILE_SWITCH(A, hipLaunchKernelGGL((kt_spmv64<NR, TS, false, false>), dim3(g), dim3(kBlock), lds, s,
+                                                        A, X, Y, (const double *)nullptr, partials, all_done)));
     }
     return g;
 }
@@ -688,8 +860,8 @@ int btile_residual64(hipStream_t s, int nr, const DevTilesView &A, const double 
 {
     const int g = btile_grid(A);
     const size_t lds = btile_lds(A, nr, 8);
-    NR_SWITCH(nr, hipLaunchKernelGGL((kt_spmv64<NR, false, true>), dim3(g), dim3(kTileBlock), lds, s, A, U, R, F,
-                                     (double *)nullptr, (const int *)nullptr));
+    NR_SWITCH(nr, TILE_SWITCH(A, hipLaunchKernelGGL((kt_spmv64<NR, TS, false, true>), dim3(g), dim3(kBlock), lds, s, A, U,
+                                                    R, F, (double *)nullptr, (const int *)nullptr)));
     return g;
 }
 
@@ -813,7 +985,7 @@ void bdense(hipStream_t s, int nr, int n, const T *Ainv, const T *B, T *X, const
 
 int bvec_dot(hipStream_t s, int nr, int n, const double *a, const double *b, double *partials)
 {
-    int g = brows_grid(n, nr);
+    int g = bsum_grid(n, nr);
     NR_SWITCH(nr, hipLaunchKernelGGL((kb_dot<NR>), dim3(g), dim3(kBlock), 0, s, n, a, b, partials));
     return g;
 }
@@ -830,19 +1002,11 @@ void bcg_init(hipStream_t s, int nr, const BCgState &st, double tol2, const doub
     NR_SWITCH(nr, hipLaunchKernelGGL((kb_cg_init<NR>), dim3(1), dim3(64), 0, s, st, tol2, ff, rr0));
 }
 
-int bcg_update(hipStream_t s, int nr, int n, double *X, double *R, const double *P, const double *Q,
-               const BCgState &st, double *partials)
-{
-    int g = brows_grid(n, nr);
-    NR_SWITCH(nr, hipLaunchKernelGGL((kb_cg_update<NR>), dim3(g), dim3(kBlock), 0, s, n, X, R, P, Q, st, partials));
-    return g;
-}
-
 template <typename T>
 int bcg_update_prep(hipStream_t s, int nr, int n, double *X, double *R, const double *P, const double *Q,
                     const BCgState &st, double *partials, const T *dinv, T *Z0, T *RT)
 {
-    int g = brows_grid(n, nr);
+    int g = bsum_grid(n, nr);
     NR_SWITCH(nr, hipLaunchKernelGGL((kb_cg_update_prep<T, NR>), dim3(g), dim3(kBlock), 0, s, n, X, R, P, Q, st,
                                      partials, dinv, Z0, RT));
     return g;
@@ -873,7 +1037,7 @@ void bscatter(hipStream_t s, int nr, int n, int ld, const int *perm, const doubl
 
 #define BINST(T)                                                                                                   \
     template int btile_sweep<T, T, T>(hipStream_t, int, const DevTilesView &, const T *, const T *, const T *, T *, \
-                                      const double *, double *, const int *);                                      \
+                                      double *, const int *);                                      \
     template int btile_resid<T>(hipStream_t, int, const DevTilesView &, const T *, const T *, T *, const int *);    \
     template void bjacobi0<T>(hipStream_t, int, int, const T *, const double *, T *, T *, const int *);            \
     template int bsell_sweep<T, T, T>(hipStream_t, int, const DevSellView &, const T *, const T *, const T *, T *, \
@@ -896,6 +1060,6 @@ template void bcg_direction<float>(hipStream_t, int, int, const float *, double 
 template int bsell_sweep<float, double, float>(hipStream_t, int, const DevSellView &, const float *, const double *,
                                                const float *, float *, const double *, double *, const int *);
 template int btile_sweep<float, double, float>(hipStream_t, int, const DevTilesView &, const float *, const double *,
-                                               const float *, float *, const double *, double *, const int *);
+                                                const float *, float *, double *, const int *);
 
 }  // namespace auxp

@@ -19,8 +19,8 @@ struct BCgState {
 // Row tiles of the P^k operator for block products (see Tiles in the host
 // setup): per tile the distinct gathered block rows are staged in LDS.
 struct DevTilesView {
-    int n, tile, ntiles, max_cols, max_entries;
-    const int *rows, *row_ptr, *col_off, *ucols;
+    int n, tile, ntiles, max_cols;
+    const int *rows, *grp_off, *col_off, *ucols;
     const unsigned short *lidx;
     const void *val;     // double or float
 };
@@ -28,9 +28,10 @@ struct DevTilesView {
 // tiles cannot be used: more than 64 KiB)
 size_t btile_lds(const DevTilesView &A, int nr, int s);
 
+// Zout = Zin + D^-1 (RHS - A Zin); partials (or null): of RHS . Zout
 template <typename T, typename TR, typename TZ>
 int btile_sweep(hipStream_t s, int nr, const DevTilesView &A, const T *dinv, const TR *RHS, const T *Zin, TZ *Zout,
-                const double *Rdot, double *partials, const int *all_done);
+                double *partials, const int *all_done);
 template <typename T>
 int btile_resid(hipStream_t s, int nr, const DevTilesView &A, const T *RHS, const T *Z, T *Res, const int *all_done);
 int btile_spmv64(hipStream_t s, int nr, const DevTilesView &A, const double *X, double *Y, double *partials,
@@ -73,8 +74,6 @@ int bvec_dot(hipStream_t s, int nr, int n, const double *a, const double *b, dou
 void bfinish(hipStream_t s, int nr, const double *partials, int nparts, FinishMode mode, double *out,
              const BCgState &st);
 void bcg_init(hipStream_t s, int nr, const BCgState &st, double tol2, const double *ff, const double *rr0);
-int bcg_update(hipStream_t s, int nr, int n, double *X, double *R, const double *P, const double *Q,
-               const BCgState &st, double *partials);
 // the same, also writing the preconditioner's first sweep from zero
 // (Z0 = D^-1 R) and, with RT non-null, R in the preconditioner's type
 template <typename T>

@@ -115,15 +115,15 @@ struct DevSell {
 };
 
 struct DevTiles {
-    int n = 0, tile = 0, ntiles = 0, max_cols = 0, max_entries = 0;
-    int *rows = nullptr, *row_ptr = nullptr, *col_off = nullptr, *ucols = nullptr;
+    int n = 0, tile = 0, ntiles = 0, max_cols = 0;
+    int *rows = nullptr, *grp_off = nullptr, *col_off = nullptr, *ucols = nullptr;
     unsigned short *lidx = nullptr;
     double *v64 = nullptr;
     float *v32 = nullptr;
     template <typename T>
     DevTilesView view() const
     {
-        return {n, tile, ntiles, max_cols, max_entries, rows, row_ptr, col_off, ucols, lidx,
+        return {n, tile, ntiles, max_cols, rows, grp_off, col_off, ucols, lidx,
                 std::is_same<T, float>::value ? (const void *)v32 : (const void *)v64};
     }
 };
@@ -2114,14 +2114,7 @@ struct aux_handle {
             bo.ready = true;
             return;
         }
-        std::vector<double> pos((size_t)3 * n);
-        for (int i = 0; i < n; i++)
-            for (int c = 0; c < 3; c++) {
-                double t = 0.0;
-                for (int p = 0; p < disc.k; p++) t += disc.xyz[3 * (size_t)disc.keys[(size_t)i * disc.k + p] + c];
-                pos[3 * (size_t)i + c] = t / disc.k;
-            }
-        const std::vector<int> mo = morton_order(pos, n);     // Morton position -> external dof
+        const std::vector<int> mo = dof_curve();
         std::vector<int> imo(n);
         for (int r = 0; r < n; r++) imo[mo[r]] = r;
         bo.Am = permute_symmetric(disc.A, mo, imo);
@@ -2237,7 +2230,7 @@ struct aux_handle {
         if (!opt.batch_tiles || (opt.batch_tiles == 1 && opt.sell_window > 0)) return;
         ensure_tiles();
         if (opt.batch_tiles == 2) {                    // the largest tile whose LDS fits
-            for (int k = 0; k < kTileSizes; k++) {
+            for (int k = kTileSizes - 1; k >= 0; k--) {
                 if (btile_lds(tiles[k].view<float>(), bt.nr, 4)) bt.layout32 = k;
                 if (btile_lds(tiles[k].view<double>(), bt.nr, 8)) bt.layout64 = k;
             }
@@ -2258,7 +2251,7 @@ struct aux_handle {
             if (btile_lds(tiles[k].view<float>(), nr, 4)) {
                 double ms = time_block([&]() {
                     btile_sweep<float, float, float>(stream, nr, tiles[k].view<float>(), bo.dinv32, rh, z0, z1,
-                                                     nullptr, nullptr, nullptr);
+                                                     nullptr, nullptr);
                 });
                 if (ms < best32) {
                     best32 = ms;
@@ -2358,32 +2351,63 @@ struct aux_handle {
     BOp bIP, bIR, bRF;
     bool bops_ready = false;
 
-    // A_h as row tiles (16, 32 and 64 consecutive original rows) for the
-    // block products; a launch uses the largest tile whose LDS fits
+    // A_h as row tiles (up to 64 rows and 312 distinct columns, or 128 and
+    // 504, along the Morton curve of the node positions) for the block
+    // products: four or two workgroups per compute unit with pieces of 128
+    // bytes and a reduction's buffer.  With 32 columns 64 rows are the faster
+    // in FP32 and for P2 (P2 40^3: FP32 sweep 88 and 121 us, FP64 product 190
+    // and 205), 128 for the longer rows in FP64 (P3 20^3: 153 and 134); the
+    // first solve of a width times both and the slices (139 and 269; 160).
+    // Up to 32 rows and 156 columns where 64-row tiles are fewer than the 1024
+    // workgroups that are resident (FP64 solves, before: P2 8^3 with 8 columns
+    // 1.27 ms with 32-row and 1.38 with 64-row tiles, 3.47 -> 3.26 for P2 12^3
+    // with 32, 6.27 -> 4.07 for P3 8^3 with 16).
     static constexpr int kTileSizes = 3;
     DevTiles tiles[kTileSizes];
     bool tiles_ready = false;
 
+    // node positions' Morton order: place on the curve -> external dof
+    std::vector<int> dof_curve() const
+    {
+        const int n = disc.ndof;
+        std::vector<double> pos((size_t)3 * n);
+        for (int i = 0; i < n; i++)
+            for (int c = 0; c < 3; c++) {
+                double t = 0.0;
+                for (int p = 0; p < disc.k; p++) t += disc.xyz[3 * (size_t)disc.keys[(size_t)i * disc.k + p] + c];
+                pos[3 * (size_t)i + c] = t / disc.k;
+            }
+        return morton_order(pos, n);
+    }
+
     void ensure_tiles()
     {
         if (tiles_ready || !opt.batch_tiles) return;
-        const int sizes[kTileSizes] = {16, 32, 64};
+        const int sizes[kTileSizes] = {128, 64, 32}, caps[kTileSizes] = {504, 312, 156};
+        // rows of bo.Am along the curve: it is A_h in external or in Morton order
+        std::vector<int> order;
+        if (opt.batch_order) {
+            order.resize(disc.ndof);
+            std::iota(order.begin(), order.end(), 0);
+        } else {
+            order = dof_curve();
+        }
         for (int k = 0; k < kTileSizes; k++) {
+            if (sizes[k] == 32 && tiles[k - 1].ntiles >= 1024) continue;
             Tiles h;
-            build_tiles(bo.Am, bo.m2b, sizes[k], h);
+            build_tiles(bo.Am, order, bo.m2b, sizes[k], caps[k], h);
             DevTiles &d = tiles[k];
             d.n = h.n;
             d.tile = h.tile;
             d.ntiles = h.ntiles;
             d.max_cols = h.max_cols;
-            d.max_entries = h.max_entries;
             d.rows = upload(h.rows);
-            d.row_ptr = upload(h.row_ptr);
+            d.grp_off = upload(h.grp_off);
             d.col_off = upload(h.col_off);
             d.ucols = upload(h.ucols);
             d.lidx = upload(h.lidx);
             d.v64 = upload(h.val);
-            d.v32 = upload(to_f32(h.val));
+            d.v32 = rounded(d.v64, (int64_t)h.val.size());
         }
         tiles_ready = true;
         bo.Am = Csr();
@@ -2502,7 +2526,7 @@ struct aux_handle {
         const T *rT = rTbuf ? (const T *)rTbuf : (const T *)(const void *)Rin;
         for (int k = 1; k < nu; k++) {
             pk = pbeg(AUX_PROF_PK_SWEEP);
-            if (tl) btile_sweep<T, T, T>(s, nr, tl->view<T>(), d, rT, zc, zn, nullptr, nullptr, all_done);
+            if (tl) btile_sweep<T, T, T>(s, nr, tl->view<T>(), d, rT, zc, zn, nullptr, all_done);
             else bsell_sweep<T, T, T>(s, nr, Av, d, rT, zc, zn, nullptr, nullptr, all_done);
             pend(pk);
             std::swap(zc, zn);
@@ -2526,13 +2550,13 @@ struct aux_handle {
         }
         for (int k = 1; k < nu; k++) {
             pk = pbeg(AUX_PROF_PK_SWEEP);
-            if (tl) btile_sweep<T, T, T>(s, nr, tl->view<T>(), d, rT, zc, zn, nullptr, nullptr, all_done);
+            if (tl) btile_sweep<T, T, T>(s, nr, tl->view<T>(), d, rT, zc, zn, nullptr, all_done);
             else bsell_sweep<T, T, T>(s, nr, Av, d, rT, zc, zn, nullptr, nullptr, all_done);
             pend(pk);
             std::swap(zc, zn);
         }
         pk = pbeg(AUX_PROF_PK_LAST);
-        int g = tl ? btile_sweep<T, double, T>(s, nr, tl->view<T>(), d, Rin, zc, Zout, Rin, rz_partials, all_done)
+        int g = tl ? btile_sweep<T, double, T>(s, nr, tl->view<T>(), d, Rin, zc, Zout, rz_partials, all_done)
                    : bsell_sweep<T, double, T>(s, nr, Av, d, Rin, zc, Zout, Rin, rz_partials, all_done);
         pend(pk);
         pend(pb);
@@ -2981,7 +3005,7 @@ struct aux_handle {
         for (BOp *b : {&bIP, &bIR, &bRF}) free_bop(*b);
         bops_ready = false;
         for (DevTiles &d : tiles) {
-            for (void *q : {(void *)d.rows, (void *)d.row_ptr, (void *)d.col_off, (void *)d.ucols, (void *)d.lidx,
+            for (void *q : {(void *)d.rows, (void *)d.grp_off, (void *)d.col_off, (void *)d.ucols, (void *)d.lidx,
                             (void *)d.v64, (void *)d.v32})
                 dfree(q);
             d = DevTiles();

@@ -175,44 +175,102 @@ std::vector<int> sell_positions(const Csr &A, const Sell &s)
     return pos;
 }
 
-void build_tiles(const Csr &A, const std::vector<int> &iperm, int tile, Tiles &out)
+void build_tiles(const Csr &A, const std::vector<int> &order, const std::vector<int> &iperm, int tile, int cap,
+                 Tiles &out)
 {
-    const int n = A.n;
+    if (tile % 8) throw std::invalid_argument("build_tiles: tiles of a multiple of eight rows");
+    const int n = A.n, groups = tile / 8;
     out = Tiles();
     out.n = n;
     out.tile = tile;
-    out.ntiles = (n + tile - 1) / tile;
+    auto len = [&](int i) { return A.ptr[i + 1] - A.ptr[i]; };
+    // the tiles' first places on the curve: shares of it in parallel, each cut greedily
+    // (at most 64, each with a mark per column)
+    const int share = std::max(65536, (n + 63) / 64), shares = (int)(((int64_t)n + share - 1) / share);
+    std::vector<std::vector<int>> cut(shares);
+    run_tasks(std::max(shares, 1), [&](int sh) {
+        if (sh >= shares) return;
+        std::vector<int> seen(n, -1);
+        const int end = (int)std::min<int64_t>(n, (int64_t)(sh + 1) * share);
+        int rows = 0, count = 0, id = -1;
+        for (int r = sh * share; r < end; r++) {
+            const int i = order[r];
+            int more = 0;
+            for (int e = A.ptr[i]; e < A.ptr[i + 1]; e++) more += id < 0 || seen[A.col[e]] != id;
+            if (id < 0 || rows == tile || count + more > cap) {
+                id = r;
+                cut[sh].push_back(r);
+                rows = count = 0;
+            }
+            for (int e = A.ptr[i]; e < A.ptr[i + 1]; e++)
+                if (seen[A.col[e]] != id) {
+                    seen[A.col[e]] = id;
+                    count++;
+                }
+            rows++;
+        }
+    });
+    std::vector<int> first;
+    for (const std::vector<int> &c : cut) first.insert(first.end(), c.begin(), c.end());
+    out.ntiles = (int)first.size();
+    first.push_back(n);
     out.rows.assign((size_t)out.ntiles * tile, -1);
-    out.row_ptr.assign((size_t)out.ntiles * tile + 1, 0);
+    out.grp_off.assign((size_t)out.ntiles * groups + 1, 0);
     out.col_off.assign((size_t)out.ntiles + 1, 0);
-    std::vector<int> cols;
+    // the rows of each tile (of A, by decreasing length), its distinct columns and block counts
+    std::vector<int> arow((size_t)out.ntiles * tile, -1);
+    std::vector<std::vector<int>> cols(out.ntiles);
+    for_shares(out.ntiles, A.col.size() / 4, [&](int ta, int tb) {
+        for (int t = ta; t < tb; t++) {
+            int *r = &arow[(size_t)t * tile];
+            const int cnt = first[t + 1] - first[t];
+            std::copy(order.begin() + first[t], order.begin() + first[t + 1], r);
+            std::stable_sort(r, r + cnt, [&](int a, int b) { return len(a) > len(b); });
+            std::vector<int> &c = cols[t];
+            for (int i = 0; i < cnt; i++) {
+                out.rows[(size_t)t * tile + i] = iperm[r[i]];
+                for (int e = A.ptr[r[i]]; e < A.ptr[r[i] + 1]; e++) c.push_back(iperm[A.col[e]]);
+            }
+            std::sort(c.begin(), c.end());
+            c.erase(std::unique(c.begin(), c.end()), c.end());
+            for (int g = 0; g < groups; g++)
+                out.grp_off[(size_t)t * groups + g + 1] = 8 * g < cnt ? (len(r[8 * g]) + 7) / 8 : 0;
+        }
+    });
+    int64_t blocks = 0, ncols = 0;
+    for (size_t g = 1; g < out.grp_off.size(); g++) {
+        blocks += out.grp_off[g];
+        if (blocks > 0x7fffffff) throw std::invalid_argument("build_tiles: operator too large");
+        out.grp_off[g] = (int)blocks;
+    }
     for (int t = 0; t < out.ntiles; t++) {
-        const int r0 = t * tile, r1 = std::min(n, r0 + tile);
-        cols.clear();
-        for (int r = r0; r < r1; r++)
-            for (int e = A.ptr[r]; e < A.ptr[r + 1]; e++) cols.push_back(iperm[A.col[e]]);
-        std::sort(cols.begin(), cols.end());
-        cols.erase(std::unique(cols.begin(), cols.end()), cols.end());
-        if (cols.size() > 65535) throw std::invalid_argument("build_tiles: tile too wide for 16-bit positions");
-        out.ucols.insert(out.ucols.end(), cols.begin(), cols.end());
-        out.col_off[t + 1] = (int)out.ucols.size();
-        out.max_cols = std::max(out.max_cols, (int)cols.size());
-        const size_t first = out.val.size();
-        for (int i = 0; i < tile; i++) {
-            const int r = r0 + i;
-            if (r < r1) {
-                out.rows[(size_t)t * tile + i] = iperm[r];
-                for (int e = A.ptr[r]; e < A.ptr[r + 1]; e++) {
-                    const int c = iperm[A.col[e]];
-                    out.lidx.push_back((uint16_t)(std::lower_bound(cols.begin(), cols.end(), c) - cols.begin()));
-                    out.val.push_back(A.val[e]);
+        if (cols[t].size() > 65535) throw std::invalid_argument("build_tiles: tile too wide for 16-bit positions");
+        ncols += (int64_t)cols[t].size();
+        out.max_cols = std::max(out.max_cols, (int)cols[t].size());
+        out.col_off[t + 1] = (int)ncols;
+    }
+    out.ucols.resize((size_t)ncols);
+    out.lidx.resize((size_t)blocks * 64);
+    out.val.resize((size_t)blocks * 64);
+    for_shares(out.ntiles, A.col.size() / 4, [&](int ta, int tb) {
+        for (int t = ta; t < tb; t++) {
+            const std::vector<int> &c = cols[t];
+            std::copy(c.begin(), c.end(), out.ucols.begin() + out.col_off[t]);
+            const size_t e0 = (size_t)out.grp_off[(size_t)t * groups] * 64, e1 = (size_t)out.grp_off[(size_t)(t + 1) * groups] * 64;
+            std::fill(out.lidx.begin() + e0, out.lidx.begin() + e1, 0);
+            std::fill(out.val.begin() + e0, out.val.begin() + e1, 0.0);
+            for (int i = 0; i < tile; i++) {
+                const int r = arow[(size_t)t * tile + i];
+                if (r < 0) continue;
+                const size_t b0 = (size_t)out.grp_off[(size_t)t * groups + i / 8] * 64 + 8 * (i % 8);
+                for (int e = A.ptr[r], j = 0; e < A.ptr[r + 1]; e++, j++) {
+                    const size_t at = b0 + 64 * (size_t)(j / 8) + j % 8;
+                    out.lidx[at] = (uint16_t)(std::lower_bound(c.begin(), c.end(), iperm[A.col[e]]) - c.begin());
+                    out.val[at] = A.val[e];
                 }
             }
-            if (out.val.size() > 0x7fffffffu) throw std::invalid_argument("build_tiles: operator too large");
-            out.row_ptr[(size_t)t * tile + i + 1] = (int)out.val.size();
         }
-        out.max_entries = std::max(out.max_entries, (int)(out.val.size() - first));
-    }
+    });
 }
 
 Csr permute_symmetric(const Csr &A, const std::vector<int> &perm, const std::vector<int> &iperm)

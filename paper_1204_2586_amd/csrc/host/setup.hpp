@@ -176,22 +176,29 @@ struct Ell {
 void build_ell(const Csr &A, int lanes, Ell &out);
 
 // Row tiles for products with a block of vectors (batched solve).  Tile t
-// holds `tile` consecutive rows of A in the original order (neighbouring
-// dofs, which share most of their columns); ucols lists the distinct columns
-// of the tile (in the internal numbering), and each entry stores the 16-bit
-// position of its column in that list, so a workgroup can stage the gathered
-// block rows once per tile.  Rows and columns are renumbered with iperm.
+// holds up to `tile` consecutive rows of the given order (along a space-filling
+// curve: a compact region, whose rows share most of their columns), as many as
+// have at most `cap` distinct columns (a row with more takes a tile of its
+// own); ucols lists the distinct columns of the tile (in the internal
+// numbering), so a workgroup can stage the gathered block rows once per tile,
+// and each entry stores the 16-bit position of its column in that list.  A tile's rows are
+// sorted by length and taken in groups of eight, padded to blocks of eight
+// entries (value 0, position 0): entry e of row r of a group is entry
+// 64 (block of e / 8) + 8 r + e % 8.
 struct Tiles {
     int n = 0, tile = 0, ntiles = 0;
     std::vector<int> rows;        // [ntiles*tile] internal row of each tile row, -1 past the end
-    std::vector<int> row_ptr;     // [ntiles*tile + 1] entry offsets, tile rows in order
+    std::vector<int> grp_off;     // [ntiles*tile/8 + 1] first block of each group
     std::vector<uint16_t> lidx;   // per entry: position of its column in the tile's list
     std::vector<double> val;
     std::vector<int> col_off;     // [ntiles+1] offsets into ucols
     std::vector<int> ucols;       // distinct internal columns of each tile, sorted
-    int max_cols = 0, max_entries = 0;
+    int max_cols = 0;
 };
-void build_tiles(const Csr &A, const std::vector<int> &iperm, int tile, Tiles &out);
+// A in its own order; order[r] the row of A at place r of the curve; iperm:
+// row (and column) of A -> internal number
+void build_tiles(const Csr &A, const std::vector<int> &order, const std::vector<int> &iperm, int tile, int cap,
+                 Tiles &out);
 
 // Rows sorted by decreasing length (stably) within windows of `window` rows;
 // index16 = false stores every slice with plain 32-bit columns.  With
