@@ -95,8 +95,8 @@ def cycle_lanes(info):
 def index_bytes_per_entry(info):
     """Column-stream bytes per entry of the device A_h layout (16-bit offsets
     in some slices, 32-bit columns in the others), and the per-slice
-    metadata bytes (offset and mode words)."""
-    return info.sell_index_bytes / max(info.stored_A, 1), 8 * info.sell_slices
+    metadata bytes (one 16-byte word: offsets, groups, width)."""
+    return info.sell_index_bytes / max(info.stored_A, 1), 16 * info.sell_slices
 
 
 def algorithmic_bytes(cat, n, nnz, s, fmt):
@@ -119,12 +119,12 @@ def algorithmic_bytes(cat, n, nnz, s, fmt):
 
 
 def matfree_bytes(cat, n, nt, nloc, s):
-    """Bytes of one matrix-free product pass: the element kernel reads the
-    element map and slot indices (4 B each per tet node), six weights per
-    tet, each gathered dof value once, and writes one result per tet node;
-    the per-dof gather-sum reads the incidence offsets and those results
-    back, plus the vectors of the fused update (as in algorithmic_bytes)."""
-    op = nt * nloc * (4 + 4 + 2 * s) + nt * 6 * s + n * s + 4 * (n + 1)
+    """Bytes that one matrix-free product pass cannot do without: a 4 B word
+    per tet node (nodes padded to a multiple of four), six weights per tet and
+    each dof value once, plus the vectors of the fused update (as in
+    algorithmic_bytes).  The patches' dof lists and the partial sums of shared
+    dofs depend on the mesh and are not counted."""
+    op = nt * 16 * -(-nloc // 4) + nt * 6 * s + n * s
     if cat == "pk_sweep":
         return op + 3 * s * n
     if cat == "pk_last":

@@ -85,17 +85,19 @@ __global__ __launch_bounds__(kAsmBlock) void k_row_l1(int n, const int *__restri
     }
 }
 
-// matrix-free weights w[t][k] = -kappa_t G_t[p_k][q_k] over the six vertex
-// pairs (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
-__global__ __launch_bounds__(kAsmBlock) void k_mf_weights(int nt, const double *__restrict__ G,
+// matrix-free weights w[p][k] = -kappa_t G_t[p_k][q_k] of the tet t of place p
+// (0 at an empty place) over the six vertex pairs (0,1) (0,2) (0,3) (1,2)
+// (1,3) (2,3)
+__global__ __launch_bounds__(kAsmBlock) void k_mf_weights(int places, const int *__restrict__ tet,
+                                                          const double *__restrict__ G,
                                                           const double *__restrict__ kappa, double *__restrict__ w64,
                                                           float *__restrict__ w32)
 {
     const int pq[6] = {1, 2, 3, 6, 7, 11};
-    for (long long u = (long long)blockIdx.x * kAsmBlock + threadIdx.x; u < 6LL * nt;
+    for (long long u = (long long)blockIdx.x * kAsmBlock + threadIdx.x; u < 6LL * places;
          u += (long long)gridDim.x * kAsmBlock) {
-        const int t = (int)(u / 6), k = (int)(u % 6);
-        const double v = -kappa[t] * G[(size_t)t * 16 + pq[k]];
+        const int t = tet[u / 6], k = (int)(u % 6);
+        const double v = t >= 0 ? -kappa[t] * G[(size_t)t * 16 + pq[k]] : 0.0;
         w64[u] = v;
         w32[u] = (float)v;
     }
@@ -171,9 +173,9 @@ void row_l1(hipStream_t s, int n, const int *ptr, const double *val, double *l1)
     hipLaunchKernelGGL(k_row_l1, dim3(asm_grid(n)), dim3(kAsmBlock), 0, s, n, ptr, val, l1);
 }
 
-void mf_weights(hipStream_t s, int nt, const double *G, const double *kappa, double *w64, float *w32)
+void mf_weights(hipStream_t s, int places, const int *tet, const double *G, const double *kappa, double *w64, float *w32)
 {
-    hipLaunchKernelGGL(k_mf_weights, dim3(asm_grid(6LL * nt)), dim3(kAsmBlock), 0, s, nt, G, kappa, w64, w32);
+    hipLaunchKernelGGL(k_mf_weights, dim3(asm_grid(6LL * places)), dim3(kAsmBlock), 0, s, places, tet, G, kappa, w64, w32);
 }
 
 void restrict_values(hipStream_t s, int nrows, int n, const int *rf_ptr, const int *rf_col, const int *ir_ptr,

@@ -14,7 +14,7 @@ void gather_entries(hipStream_t s, long long nnz, const int *ptr, const int *idx
 // l1 row norms of a CSR operator
 void row_l1(hipStream_t s, int n, const int *ptr, const double *val, double *l1);
 // matrix-free weights -kappa_t G_t[p][q] over the six vertex pairs
-void mf_weights(hipStream_t s, int nt, const double *G, const double *kappa, double *w64, float *w32);
+void mf_weights(hipStream_t s, int places, const int *tet, const double *G, const double *kappa, double *w64, float *w32);
 // values of the block -I_R A_h of RF = [I_R, -I_R A_h] on its pattern (rows
 // nrows = n_H, n columns per block, internal numbering) from I_R (internal)
 // and A_h (external CSR, perm: internal -> external), in the order of the

@@ -13,10 +13,13 @@
 // B operand = Z formed in registers from the lane's gathered values and its
 // tet's weights).
 //
-// Each element result (K_t x_t)_a is written to the slot of (t, a) in an
-// array ordered by dof, so the contributions to one dof are contiguous; a
-// second pass sums each dof's range in a fixed order -- no atomics, so the
-// result is deterministic -- with the smoother or residual update fused in.
+// A workgroup takes a patch of neighbouring tets: it reads the patch's values
+// of x once into LDS, its wavefronts multiply tile by tile and put the element
+// results into LDS, ordered by dof, and the sums of dofs whose tets are all in
+// the patch are final: smoother, residual or product are written from there.
+// Only dofs shared with other patches go through memory, one partial sum per
+// patch, added in a fixed order by a second kernel -- no atomics, so the
+// result is deterministic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,282 +34,338 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-template <typename T>
-struct Acc;
-// Operand layouts (both 16x16x4 forms): lane l supplies A[l % 16][l / 16] and
+// Operand layouts (16x16x4, both types): lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16].  Result register v of lane l holds D[row][l % 16] with
 // row = 4 (l / 16) + v for FP32 and row = (l / 16) + 4 v for FP64.
+// The last rows go through the four-row forms with the same B operand: FP64
+// 4x4x4 (four blocks, A[l % 4][l / 16], D[l / 16][l % 16]); FP32 4x4x1 (sixteen
+// blocks: A[l % 4] of lane group l / 16 and B as above, so the registers hold
+// four partial sums over k, one per lane group, of rows v).
+template <typename T>
+struct Acc;
 template <>
 struct Acc<float> {
     using V = f32x4;
+    using V4 = f32x4;
     static __device__ __forceinline__ V mfma(float a, float b, V c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ int row(int grp, int v) { return 4 * grp + v; }
+    static __device__ __forceinline__ V4 mfma4(float a, float b, V4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+    }
+    // row grp of the four: the lane groups' partial sums added
+    static __device__ __forceinline__ float result4(const V4 &c, int grp)
+    {
+        const bool hi = grp & 2, odd = grp & 1;
+        const float k0 = (hi ? c[2] : c[0]) + __shfl_xor(hi ? c[0] : c[2], 32, 64);
+        const float k1 = (hi ? c[3] : c[1]) + __shfl_xor(hi ? c[1] : c[3], 32, 64);
+        return (odd ? k1 : k0) + __shfl_xor(odd ? k0 : k1, 16, 64);
+    }
+    static __host__ __device__ __forceinline__ int row(int grp, int v) { return 4 * grp + v; }
 };
 template <>
 struct Acc<double> {
     using V = f64x4;
+    using V4 = double;
     static __device__ __forceinline__ V mfma(double a, double b, V c)
     {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ int row(int grp, int v) { return grp + 4 * v; }
+    static __device__ __forceinline__ V4 mfma4(double a, double b, V4 c)
+    {
+        return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ double result4(const V4 &c, int) { return c; }
+    static __host__ __device__ __forceinline__ int row(int grp, int v) { return grp + 4 * v; }
 };
 
 __device__ __forceinline__ bool stop(const int *done) { return done != nullptr && *done != 0; }
 
-constexpr int kTetsPerWave = 16;
 constexpr int kDies = 8;
-constexpr int kWaves = kBlock / 64;
 
-// Y[slot(t, a)] = (K_t x_t)_a for all tets.
+// 16-row tiles, and a four-row one if that holds the remaining nodes (P3, P4)
+constexpr int tiles4(int nloc) { return nloc % 16 > 0 && nloc % 16 <= 4; }
+constexpr int tiles16(int nloc) { return (nloc + 15) / 16 - tiles4(nloc); }
+constexpr int table_size(int nloc) { return 6 * ((nloc + 3) / 4) * (64 * tiles16(nloc) + 16 * tiles4(nloc)); }
+
+// MF_RESID: out = rhs - Ax;  MF_SWEEP: out = x + dinv (rhs - Ax);  MF_PRODUCT: out = Ax
+enum { MF_RESID = 0, MF_SWEEP = 1, MF_PRODUCT = 2 };
+
+template <typename T, typename TR, int MODE>
+__device__ __forceinline__ T mf_result(T s, T x, T d, TR b)
+{
+    if constexpr (MODE == MF_RESID) return (T)b - s;
+    else if constexpr (MODE == MF_SWEEP) return x + d * ((T)b - s);
+    else return s;
+}
+
+__device__ __forceinline__ void mf_partial(double acc, double *partials)
+{
+    __shared__ double red[kBlock / 64];
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double b = 0.0;
+        for (int w = 0; w < kBlock / 64; w++) b += red[w];
+        *partials = b;
+    }
+}
+
+// A patch's complete dofs, and its partial sums of the shared ones.
 //
 // Contraction order: the 6 nloc terms (k, b) are split into steps of four,
 // step s covering k = s / NB and b = 4 (s % NB) + g for the four lane groups
 // g = lane / 16 (NB = ceil(nloc / 4); b >= nloc is padding).  So lane (g, c)
-// of a wave needs only the six weights of its tet c and its NB gathered
-// values b = g, g+4, ..., held in registers, from which it forms its B
-// operand per step; the A operand (the reference tables) comes from LDS,
-// filled once per workgroup before a barrier.  Every register index below is
-// a compile-time constant.
-template <typename T, int NLOC>
-__global__ __launch_bounds__(kBlock) void k_mf_element(MfView<T> op, const T *__restrict__ X, T *__restrict__ Yel,
-                                                       const int *done)
+// of a wave needs only the six weights of its tet c and its NB values b = g,
+// g+4, ..., held in registers, from which it forms its B operand per step; the
+// A operand (the reference tables) comes from LDS.  The tables' rows are
+// ordered so that the lane's results are those same nodes' (result v of tile m
+// is node 16 m + 4 v + g), and one word per node, read by the wave as one
+// contiguous load, gives its place in the patch's x and among its results.
+//
+// What bounds it (P3, 196 608 tets, FP32 sweep: 23.4 us and 6.3 for the shared
+// dofs; 26 and 9.4 with every element result through memory): 62 MB (85
+// before), 13 us at the rate of a large copy; 6 us of matrix-core time (9.6 if
+// the last 4 of the 20 rows took a 16-row tile); and the chain of a patch --
+// list, values, products, sums, each behind a barrier -- which the four to nine
+// workgroups of a compute unit hide only in part.  The FP64 product takes 32.2
+// and 7.2 us (37 and 13.5 before), 12 us of them on the matrix cores.
+// Requesting the sums' inputs before the products took 40 registers more and
+// was slower (P2 48^3 solve 5.47 -> 5.64 ms).
+template <typename T, typename TR, typename TZ, int NLOC, int MODE, bool DOT>
+__global__ __launch_bounds__(kBlock) void k_mf_patch(MfView<T> op, const T *__restrict__ X, const T *__restrict__ dinv,
+                                                 const TR *__restrict__ rhs, TZ *__restrict__ out, double *partials,
+                                                 const int *done)
 {
     if (stop(done)) return;
-    constexpr int NB = (NLOC + 3) / 4;           // gathered values per lane
+    constexpr int NB = (NLOC + 3) / 4;           // values per lane
     constexpr int KS = 6 * NB;                   // MFMA steps
-    constexpr int MT = (NLOC + 15) / 16;         // 16-row output tiles
-    const int lane = threadIdx.x & 63;
-    const int col = lane & 15, grp = lane >> 4;
-
-    // Output tiles of 16 rows handled per pass over the tets: all of them for
-    // P2/P3; one per pass for P4, whose 35-node tables (41.5 KB in FP32,
-    // 83 KB in FP64) would not leave room for enough workgroups per compute
-    // unit (the element map, weights and gathers are then read once per pass)
-    constexpr int MG = NLOC > 20 ? 1 : MT;
-    constexpr int NPASS = MT / MG;
-
-    // A operand: lane (i = lane % 16, g) of step s holds S[16 mt + i][k nloc + b],
-    // staged in LDS in that lane order (one conflict-free read per step; in
-    // registers the tables would take 60 (FP32) or 120 (FP64) VGPRs at P3 and
-    // cap the waves per SIMD at 4 or 2)
-    __shared__ T sA[MG * KS * 64];
+    constexpr int MT = tiles16(NLOC), M4 = tiles4(NLOC);   // output tiles of 16 and of 4 rows
+    constexpr int TBL = table_size(NLOC), PV = 16 / sizeof(T);
+    extern __shared__ __align__(16) unsigned char lds_[];
+    T *sA = (T *)lds_, *ys = sA + TBL, *xs = ys + op.tp * NLOC;
+    const T *s4 = sA + MT * KS * 64 + (threadIdx.x >> 4 & 3) * 4 + (threadIdx.x & 3);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    typedef T tv __attribute__((ext_vector_type(PV)));
+    for (int i = threadIdx.x; i < TBL / PV; i += kBlock) ((tv *)sA)[i] = ((const tv *)op.S)[i];
 
     // Each die (workgroups are dispatched round-robin over kDies dies, b to
-    // b % kDies) takes a contiguous range of tiles, so the slots of a dof,
-    // written by neighbouring tets, fill their cache lines in one L2 instead
-    // of being written back in pieces from every die.  Any grid visits every
-    // tile exactly once; placement affects only speed.
-    const int ntiles = (op.nt + kTetsPerWave - 1) / kTetsPerWave;
-    int first, end, step;
-    {
-        const int b = blockIdx.x, g = gridDim.x, w = (int)(threadIdx.x >> 6);
-        if (g < kDies) {
-            first = b * kWaves + w;
-            end = ntiles;
-            step = g * kWaves;
-        } else {
-            const int d = b % kDies, j = b / kDies;
-            const int gd = (g - d + kDies - 1) / kDies;          // workgroups on die d
-            const int per = (ntiles + kDies - 1) / kDies;
-            first = d * per + j * kWaves + w;
-            end = min(ntiles, (d + 1) * per);
-            step = gd * kWaves;
-        }
+    // b % kDies) takes a contiguous range of patches, so what neighbouring
+    // patches share meets in one L2.  Any grid visits every patch exactly
+    // once; placement affects only speed.
+    int p = blockIdx.x, p_end = op.npatch, p_step = gridDim.x;
+    if (p_step >= kDies) {
+        const int d = p % kDies, per = (op.npatch + kDies - 1) / kDies;
+        p_step = (p_step - d + kDies - 1) / kDies;
+        p = d * per + p / kDies;
+        p_end = min(op.npatch, (d + 1) * per);
     }
-    for (int pass = 0; pass < NPASS; pass++) {
-        if (pass > 0) __syncthreads();          // every wave is done with the previous tables
-        for (int i = threadIdx.x; i < MG * KS * 64; i += kBlock) {
-            const int l = i % 64, s = (i / 64) % KS, mt = pass * MG + i / (64 * KS);
-            const int row = 16 * mt + l % 16, k = s / NB, b = 4 * (s % NB) + l / 16;
-            sA[i] = (row < NLOC && b < NLOC) ? op.S[row * 6 * NLOC + k * NLOC + b] : T(0);
+    constexpr int U = 4;
+    const int tiles = op.tp / 16;
+    double acc_dot = 0.0;
+    for (; p < p_end; p += p_step) {
+        const int4 m = op.meta[p];
+        unsigned nw[NB];
+        T nv[6];
+        auto request = [&](int tile) {
+            const size_t t = (size_t)p * tiles + tile;
+#pragma unroll
+            for (int j = 0; j < NB; j++) nw[j] = op.word[(t * NB + j) * 64 + lane];
+#pragma unroll
+            for (int k = 0; k < 6; k++) nv[k] = op.w[(t * 16 + (lane & 15)) * 6 + k];
+        };
+        if (w < tiles) request(w);
+        __syncthreads();                         // the previous patch is done with xs and ys
+        const unsigned *__restrict__ range = op.range + m.x;
+        for (int i0 = threadIdx.x; i0 < m.y; i0 += U * kBlock) {
+            int id[U];
+            T x[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) id[u] = op.dof[m.x + min(i0 + u * kBlock, m.y - 1)];
+#pragma unroll
+            for (int u = 0; u < U; u++) x[u] = X[id[u]];
+#pragma unroll
+            for (int u = 0; u < U; u++) xs[min(i0 + u * kBlock, m.y - 1)] = x[u];
         }
+        if (threadIdx.x == 0) xs[m.y] = T(0);
         __syncthreads();
-        for (int tile = first; tile < end; tile += step) {
-            const int t = tile * kTetsPerWave + col;
-            const bool tv = t < op.nt;
-            const size_t tc = tv ? (size_t)t : 0;   // loads stay unconditional (clamped), so
-            T wv[6], xv[NB];                        // all of them are in flight together
-            int dv[NB];
+        for (int tile = w; tile < tiles; tile += kBlock / 64) {
+            unsigned word[NB];
+            T wv[6], xv[NB];
 #pragma unroll
-            for (int k = 0; k < 6; k++) wv[k] = op.w[tc * 6 + k];
+            for (int j = 0; j < NB; j++) word[j] = nw[j], xv[j] = xs[nw[j] & 0xffff];
 #pragma unroll
-            for (int j = 0; j < NB; j++) {
-                const int b = 4 * j + grp;
-                dv[j] = op.emap[tc * NLOC + (b < NLOC ? b : 0)];
-                if (!tv || b >= NLOC) dv[j] = -1;
-            }
-            // slots of this lane's results, loaded with the element map
-            int sv[MG][4];
+            for (int k = 0; k < 6; k++) wv[k] = nv[k];
+            if (tile + kBlock / 64 < tiles) request(tile + kBlock / 64);
+            // B operand: lane (g, c) holds Z[(k, b)][c] = w_c,k x_c,b, formed step by step
+            typename Acc<T>::V acc[MT];
+            typename Acc<T>::V4 acc4[M4 > 0 ? M4 : 1];
 #pragma unroll
-            for (int m = 0; m < MG; m++)
+            for (int i = 0; i < MT; i++) acc[i] = typename Acc<T>::V{0, 0, 0, 0};
 #pragma unroll
-                for (int v = 0; v < 4; v++) {
-                    const int a = 16 * (pass * MG + m) + Acc<T>::row(grp, v);
-                    sv[m][v] = op.slot[tc * NLOC + (a < NLOC ? a : 0)];
-                }
-#pragma unroll
-            for (int j = 0; j < NB; j++) xv[j] = X[dv[j] >= 0 ? dv[j] : 0];
-            // keep the scheduler from interleaving the loads with their uses (it
-            // would otherwise reuse one address register and wait on each)
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int m = 0; m < MG; m++)
-#pragma unroll
-                for (int v = 0; v < 4; v++)
-                    if (!tv || 16 * (pass * MG + m) + Acc<T>::row(grp, v) >= NLOC) sv[m][v] = -1;
-#pragma unroll
-            for (int j = 0; j < NB; j++)
-                if (dv[j] < 0) xv[j] = T(0);
-#pragma unroll
-            for (int k = 0; k < 6; k++)
-                if (!tv) wv[k] = T(0);
-
-            // B operand: lane (g, c) holds Z[(k, b)][c] = w_c,k x_c,b, formed step
-            // by step (the gathers above are all in flight before the first use)
-            typename Acc<T>::V acc[MG];
-#pragma unroll
-            for (int m = 0; m < MG; m++) acc[m] = typename Acc<T>::V{0, 0, 0, 0};
+            for (int i = 0; i < M4; i++) acc4[i] = typename Acc<T>::V4{};
 #pragma unroll
             for (int s = 0; s < KS; s++) {
                 const T bv = wv[s / NB] * xv[s % NB];
 #pragma unroll
-                for (int m = 0; m < MG; m++) acc[m] = Acc<T>::mfma(sA[(m * KS + s) * 64 + lane], bv, acc[m]);
+                for (int i = 0; i < MT; i++) acc[i] = Acc<T>::mfma(sA[(i * KS + s) * 64 + lane], bv, acc[i]);
+#pragma unroll
+                for (int i = 0; i < M4; i++) acc4[i] = Acc<T>::mfma4(s4[(i * KS + s) * 16], bv, acc4[i]);
             }
-            // D: register v of this lane holds row Acc<T>::row(grp, v) of column c
 #pragma unroll
-            for (int m = 0; m < MG; m++)
-#pragma unroll
-                for (int v = 0; v < 4; v++)
-                    if (sv[m][v] >= 0) Yel[sv[m][v]] = acc[m][v];
+            for (int j = 0; j < NB; j++) {
+                T y;
+                if (j < 4 * MT) y = acc[j / 4 < MT ? j / 4 : 0][j % 4];
+                else y = Acc<T>::result4(acc4[0], lane >> 4);
+                if (word[j] < 0xffff0000u) ys[word[j] >> 16] = y;
+            }
+        }
+        __syncthreads();
+        // d: the dof, or the place of its partial sum
+        auto finish = [&](int i, int d, unsigned r, TR rb, T rd) {
+            const int b0 = r & 0xffff, b1 = r >> 16;
+            // four results at a time (past the end into the words behind, unused)
+            T s = T(0);
+            for (int q = b0; q < b1; q += 4) {
+                const T y0 = ys[q], y1 = ys[q + 1], y2 = ys[q + 2], y3 = ys[q + 3];
+                s += y0;
+                s += q + 1 < b1 ? y1 : T(0);
+                s += q + 2 < b1 ? y2 : T(0);
+                s += q + 3 < b1 ? y3 : T(0);
+            }
+            if (i < m.z) {
+                const T xi = MODE == MF_SWEEP || DOT ? xs[i] : T(0);
+                const TZ z = (TZ)mf_result<T, TR, MODE>(s, xi, rd, rb);
+                out[d] = z;
+                if (DOT) acc_dot += (MODE == MF_PRODUCT ? (double)xi : (double)rb) * (double)z;
+            } else {
+                op.part[d] = s;
+            }
+        };
+        for (int i = threadIdx.x; i < m.y; i += kBlock) {
+            const int d = i < m.z ? op.dof[m.x + i] : op.pos[m.w + i - m.z];
+            TR rb{};
+            T rd{};
+            if (MODE != MF_PRODUCT && i < m.z) rb = rhs[d];
+            if (MODE == MF_SWEEP && i < m.z) rd = dinv[d];
+            finish(i, d, range[i], rb, rd);
         }
     }
+    if (DOT) mf_partial(acc_dot, partials + blockIdx.x);
 }
 
-// gather-sum of the element results per dof, fused with the update:
-// MF_RESID: out = rhs - Ax;  MF_SWEEP: out = xin + dinv (rhs - Ax);  MF_PRODUCT:
-// out = Ax (each + dot with rdot when DOT)
-enum { MF_RESID = 0, MF_SWEEP = 1, MF_PRODUCT = 2 };
-
+// the shared dofs: their partial sums, and the same results
 template <typename T, typename TR, typename TZ, int MODE, bool DOT>
-__global__ __launch_bounds__(kBlock) void k_mf_gather(MfView<T> op, const T *__restrict__ Yel,
-                                                      const T *__restrict__ xin, const T *__restrict__ dinv,
+__global__ __launch_bounds__(kBlock) void k_mf_shared(MfView<T> op, const T *__restrict__ X, const T *__restrict__ dinv,
                                                       const TR *__restrict__ rhs, TZ *__restrict__ out,
-                                                      const double *__restrict__ rdot, double *partials,
-                                                      const int *done)
+                                                      double *partials, const int *done)
 {
     if (stop(done)) return;
     double acc = 0.0;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < op.n; i += gridDim.x * kBlock) {
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < op.nshared; i += gridDim.x * kBlock) {
+        const int q0 = op.sh_ptr[i], q1 = op.sh_ptr[i + 1], d = op.sh_dof[i];
+        TR b{};
+        T dv{}, x{};
+        if (MODE != MF_PRODUCT) b = rhs[d];
+        if (MODE == MF_SWEEP) dv = dinv[d];
+        if (MODE == MF_SWEEP || DOT) x = X[d];
         T s = T(0);
-        for (int p = op.inc_ptr[i]; p < op.inc_ptr[i + 1]; p++) s += Yel[p];
-        T v;
-        if (MODE == MF_RESID) v = (T)rhs[i] - s;
-        else if (MODE == MF_PRODUCT) v = s;
-        else v = xin[i] + dinv[i] * ((T)rhs[i] - s);
-        out[i] = (TZ)v;
-        if (DOT) acc += rdot[i] * (double)(TZ)v;
+        for (int q = q0; q < q1; q++) s += op.part[q];
+        const TZ z = (TZ)mf_result<T, TR, MODE>(s, x, dv, b);
+        out[d] = z;
+        if (DOT) acc += (MODE == MF_PRODUCT ? (double)x : (double)b) * (double)z;
     }
-    if (DOT) {
-        __shared__ double red[kWaves];
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double b = 0.0;
-            for (int w = 0; w < kWaves; w++) b += red[w];
-            partials[blockIdx.x] = b;
-        }
-    }
+    if (DOT) mf_partial(acc, partials + blockIdx.x);
 }
 
-inline int cap_grid(long long need)
+template <typename T, typename TR, typename TZ, int NLOC, int MODE, bool DOT>
+int mf_launch(hipStream_t s, const MfView<T> &op, const T *x, const T *dinv, const TR *rhs, TZ *out, double *partials,
+              const int *done)
 {
-    if (need < 1) need = 1;
-    if (need > kMaxBlocks) need = kMaxBlocks;
-    return (int)need;
+    const size_t lds = mf_lds(NLOC, op.tp, op.max_dofs, sizeof(T));
+    // one patch per workgroup as far as the partial sums' places go
+    const int g = std::max(1, std::min(op.npatch, kMaxBlocks / 4 * 3));
+    const int h = std::max(1, std::min((op.nshared + kBlock - 1) / kBlock, kMaxBlocks / 4));
+    hipLaunchKernelGGL((k_mf_patch<T, TR, TZ, NLOC, MODE, DOT>), dim3(g), dim3(kBlock), lds, s, op, x, dinv, rhs, out,
+                       partials, done);
+    hipLaunchKernelGGL((k_mf_shared<T, TR, TZ, MODE, DOT>), dim3(h), dim3(kBlock), 0, s, op, x, dinv, rhs, out,
+                       DOT ? partials + g : nullptr, done);
+    return g + h;
+}
+
+template <typename T, typename TR, typename TZ, int MODE, bool DOT>
+int mf_run(hipStream_t s, const MfView<T> &op, const T *x, const T *dinv, const TR *rhs, TZ *out, double *partials,
+           const int *done)
+{
+    if (op.nloc == 10) return mf_launch<T, TR, TZ, 10, MODE, DOT>(s, op, x, dinv, rhs, out, partials, done);
+    if (op.nloc == 20) return mf_launch<T, TR, TZ, 20, MODE, DOT>(s, op, x, dinv, rhs, out, partials, done);
+    return mf_launch<T, TR, TZ, 35, MODE, DOT>(s, op, x, dinv, rhs, out, partials, done);
 }
 
 }  // namespace
 
-template <typename T>
-void mf_apply(hipStream_t s, const MfView<T> &op, const T *x, T *Yel, const int *done)
+size_t mf_table_size(int nloc) { return (size_t)table_size(nloc); }
+
+size_t mf_lds(int nloc, int tp, int max_dofs, size_t size)
 {
-    // (the element kernel's clamped loads read X[0]: nothing to do without unknowns)
-    if (op.n == 0 || op.nt == 0) return;
-    // persistent waves, a few tiles each (the operand tables are staged once
-    // per workgroup): up to 8 workgroups per compute unit at P2, 4 at P3 and
-    // P4.  Each wave loads its tile's map, weights, slots and gathers, waits,
-    // then runs its matrix-core chain (60 MFMA of 32 cycles at P3), so the
-    // waves of a SIMD overlap one another's phases; measured (P3 32^3, P4
-    // 24^3, P2 48^3 mixed solves): 1024 workgroups beat 2048 at P3 (8.77 ->
-    // 8.33 ms) and P4 (15.04 -> 14.29 ms) and lose at P2 (8.82 -> 8.97 ms);
-    // 512, 768 and 1536 were no better.  A software pipeline over each
-    // wave's tiles (the next tile's loads and gathers issued before the
-    // current contraction) was measured no faster.
-    const long long tiles = ((long long)op.nt + kTetsPerWave - 1) / kTetsPerWave;
-    const int cap = op.nloc == 10 ? 2048 : 1024;
-    int g = (int)std::min<long long>((tiles + kWaves - 1) / kWaves, cap);
-    if (g < 1) g = 1;
-    if (op.nloc == 10)
-        hipLaunchKernelGGL((k_mf_element<T, 10>), dim3(g), dim3(kBlock), 0, s, op, x, Yel, done);
-    else if (op.nloc == 20)
-        hipLaunchKernelGGL((k_mf_element<T, 20>), dim3(g), dim3(kBlock), 0, s, op, x, Yel, done);
-    else
-        hipLaunchKernelGGL((k_mf_element<T, 35>), dim3(g), dim3(kBlock), 0, s, op, x, Yel, done);
+    return ((size_t)table_size(nloc) + (size_t)tp * nloc + std::max(max_dofs + 1, 4)) * size;
 }
 
 template <typename T>
-void mf_resid(hipStream_t s, const MfView<T> &op, const T *Yel, const T *rhs, T *res, const int *done)
+void mf_tables(int nloc, const double *S, T *out)
 {
-    int g = cap_grid(((long long)op.n + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL((k_mf_gather<T, T, T, MF_RESID, false>), dim3(g), dim3(kBlock), 0, s, op, Yel, (const T *)nullptr,
-                       (const T *)nullptr, rhs, res, (const double *)nullptr, (double *)nullptr, done);
+    const int nb = (nloc + 3) / 4, ks = 6 * nb, mt = tiles16(nloc);
+    auto entry = [&](int a, int s, int g) {
+        const int b = 4 * (s % nb) + g;
+        return a < nloc && b < nloc ? (T)S[((size_t)6 * a + s / nb) * nloc + b] : T(0);
+    };
+    for (int i = 0; i < mt; i++)
+        for (int s = 0; s < ks; s++)
+            for (int g = 0; g < 4; g++)
+                // result v of group r is row Acc<T>::row(r, v): node 4 v + r of the tile
+                for (int r = 0; r < 4; r++)
+                    for (int v = 0; v < 4; v++)
+                        out[(i * ks + s) * 64 + 16 * g + Acc<T>::row(r, v)] = entry(16 * i + 4 * v + r, s, g);
+    T *o4 = out + (size_t)mt * ks * 64;
+    for (int i = 0; i < tiles4(nloc); i++)
+        for (int s = 0; s < ks; s++)
+            for (int g = 0; g < 4; g++)
+                for (int r = 0; r < 4; r++) o4[(i * ks + s) * 16 + 4 * g + r] = entry(16 * mt + 4 * i + r, s, g);
+}
+
+template <typename T>
+void mf_resid(hipStream_t s, const MfView<T> &op, const T *x, const T *rhs, T *res, const int *done)
+{
+    mf_run<T, T, T, MF_RESID, false>(s, op, x, nullptr, rhs, res, nullptr, done);
+}
+
+int mf_product(hipStream_t s, const MfView<double> &op, const double *x, double *out, double *partials, const int *done)
+{
+    if (partials)
+        return mf_run<double, double, double, MF_PRODUCT, true>(s, op, x, nullptr, nullptr, out, partials, done);
+    return mf_run<double, double, double, MF_PRODUCT, false>(s, op, x, nullptr, nullptr, out, nullptr, done);
 }
 
 template <typename T, typename TR, typename TZ>
-int mf_sweep(hipStream_t s, const MfView<T> &op, const T *Yel, const T *xin, const T *dinv, const TR *rhs, TZ *out,
-             const double *rdot, double *partials, const int *done)
+int mf_sweep(hipStream_t s, const MfView<T> &op, const T *x, const T *dinv, const TR *rhs, TZ *out, double *partials,
+             const int *done)
 {
-    int g = cap_grid(((long long)op.n + kBlock - 1) / kBlock);
-    if (partials)
-        hipLaunchKernelGGL((k_mf_gather<T, TR, TZ, MF_SWEEP, true>), dim3(g), dim3(kBlock), 0, s, op, Yel, xin, dinv,
-                           rhs, out, rdot, partials, done);
-    else
-        hipLaunchKernelGGL((k_mf_gather<T, TR, TZ, MF_SWEEP, false>), dim3(g), dim3(kBlock), 0, s, op, Yel, xin, dinv,
-                           rhs, out, rdot, partials, done);
-    return g;
+    if (partials) return mf_run<T, TR, TZ, MF_SWEEP, true>(s, op, x, dinv, rhs, out, partials, done);
+    return mf_run<T, TR, TZ, MF_SWEEP, false>(s, op, x, dinv, rhs, out, nullptr, done);
 }
 
-template <typename T>
-int mf_product(hipStream_t s, const MfView<T> &op, const T *Yel, T *out, const double *rdot, double *partials,
-               const int *done)
-{
-    int g = cap_grid(((long long)op.n + kBlock - 1) / kBlock);
-    if (partials)
-        hipLaunchKernelGGL((k_mf_gather<T, T, T, MF_PRODUCT, true>), dim3(g), dim3(kBlock), 0, s, op, Yel,
-                           (const T *)nullptr, (const T *)nullptr, (const T *)nullptr, out, rdot, partials, done);
-    else
-        hipLaunchKernelGGL((k_mf_gather<T, T, T, MF_PRODUCT, false>), dim3(g), dim3(kBlock), 0, s, op, Yel,
-                           (const T *)nullptr, (const T *)nullptr, (const T *)nullptr, out, rdot, partials, done);
-    return g;
-}
-
-#define MFINST(T)                                                                                             \
-    template void mf_apply<T>(hipStream_t, const MfView<T> &, const T *, T *, const int *);                   \
-    template void mf_resid<T>(hipStream_t, const MfView<T> &, const T *, const T *, T *, const int *);        \
-    template int mf_product<T>(hipStream_t, const MfView<T> &, const T *, T *, const double *, double *,       \
-                               const int *);                                                                  \
-    template int mf_sweep<T, T, T>(hipStream_t, const MfView<T> &, const T *, const T *, const T *, const T *, \
-                                   T *, const double *, double *, const int *);
+#define MFINST(T)                                                                                    \
+    template void mf_tables<T>(int, const double *, T *);                                            \
+    template void mf_resid<T>(hipStream_t, const MfView<T> &, const T *, const T *, T *, const int *); \
+    template int mf_sweep<T, T, T>(hipStream_t, const MfView<T> &, const T *, const T *, const T *, T *, double *, \
+                                   const int *);
 
 MFINST(float)
 MFINST(double)
 template int mf_sweep<float, double, double>(hipStream_t, const MfView<float> &, const float *, const float *,
-                                             const float *, const double *, double *, const double *, double *,
-                                             const int *);
+                                             const double *, double *, double *, const int *);
 
 }  // namespace auxp

@@ -285,9 +285,9 @@ struct aux_handle {
 
     // matrix-free element operator (internal dof numbering)
     bool mf_ready = false;
-    int *mf_emap = nullptr, *mf_inc_ptr = nullptr, *mf_inc = nullptr;   // mf_inc: slot of each (tet, node)
-    double *mf_w64 = nullptr, *mf_S64 = nullptr, *mf_Y64 = nullptr;
-    float *mf_w32 = nullptr, *mf_S32 = nullptr, *mf_Y32 = nullptr;
+    int mf_places = 0, *mf_tet = nullptr;      // tet of each place
+    MfView<double> mf64 = {};
+    MfView<float> mf32 = {};
 
     // the six vertex pairs k = (p, q) and their reference matrices S^k =
     // M^pp + M^qq - M^pq - M^qp, entry (a, b) at (6 a + k) nloc + b
@@ -322,59 +322,57 @@ struct aux_handle {
         });
     }
 
+    // Tets per patch.  Large ones have fewer shared dofs and fill the tables'
+    // LDS better; 512 patches are two per compute unit, and with fewer the
+    // chain of one patch shows.  Solves, ms, with 32 / 64 / 128 / 256: P2 48^3
+    // mixed 7.30, 6.03, 5.47, 5.35; P2 8^3 0.78, 0.78, 0.83, 1.24; P3 32^3 mixed
+    // 7.51, 6.30, 5.86; P3 24^3 FP64 5.34, 4.40, 4.12; P3 8^3 1.51, 1.57, 1.77;
+    // P4 18^3 mixed 7.55, 7.75, 9.48; P4 14^3 FP64 6.98, 6.82, 9.08.
+    static int patch_tets(int nt, int nloc)
+    {
+        int tp = nloc == 10 ? 256 : nloc == 20 ? 128 : 64;
+        const int least = nloc == 35 ? 32 : 64;
+        while (tp > least && nt / tp < 512) tp /= 2;
+        return tp;
+    }
+
     void ensure_mf()
     {
         if (mf_ready) return;
         const int nt = disc.nt, nl = disc.nloc, n = disc.ndof;
         const std::vector<double> S = pair_tables();
-        std::vector<double> w((size_t)nt * 6);
-        std::vector<int> emap((size_t)nt * nl), cnt((size_t)n + 1, 0);
-        for (int t = 0; t < nt; t++) {
-            const int *v = &disc.tets[4 * (size_t)t];
-            double Gt[4][4];
-            tet_metric(&disc.xyz[3 * (size_t)v[0]], &disc.xyz[3 * (size_t)v[1]], &disc.xyz[3 * (size_t)v[2]],
-                       &disc.xyz[3 * (size_t)v[3]], Gt);
-            for (int k = 0; k < 6; k++) w[(size_t)t * 6 + k] = -disc.kappa[t] * Gt[pairs[k][0]][pairs[k][1]];
-            for (int a = 0; a < nl; a++) {
-                int d = disc.tet_dof[(size_t)t * nl + a];
-                emap[(size_t)t * nl + a] = d >= 0 ? sell.iperm[d] : -1;
-                if (d >= 0) cnt[sell.iperm[d] + 1]++;
-            }
-        }
-        for (int i = 0; i < n; i++) cnt[i + 1] += cnt[i];
-        // slot of each (tet, local node) in the dof-ordered result array
-        std::vector<int> slot(emap.size(), -1), fill(cnt.begin(), cnt.end() - 1);
-        for (size_t s = 0; s < emap.size(); s++)
-            if (emap[s] >= 0) slot[s] = fill[emap[s]]++;
-        mf_emap = upload(emap);
-        mf_inc_ptr = upload(cnt);
-        mf_inc = upload(slot);
-        mf_w64 = upload(w);
-        mf_S64 = upload(S);
-        mf_w32 = upload(to_f32(w));
-        mf_S32 = upload(to_f32(S));
-        mf_Y64 = dnew<double>((size_t)nt * nl);
-        mf_Y32 = dnew<float>((size_t)nt * nl);
+        std::vector<double> cen((size_t)nt * 3);
+        for (int t = 0; t < nt; t++)
+            for (int c = 0; c < 3; c++)
+                for (int v = 0; v < 4; v++) cen[3 * (size_t)t + c] += 0.25 * disc.xyz[3 * (size_t)disc.tets[4 * (size_t)t + v] + c];
+        std::vector<int> emap((size_t)nt * nl);
+        for (size_t i = 0; i < emap.size(); i++) emap[i] = disc.tet_dof[i] >= 0 ? sell.iperm[disc.tet_dof[i]] : -1;
+        Patches h;
+        build_patches(n, nt, nl, emap, morton_order(cen, nt), patch_tets(nt, nl), h);
+        std::vector<double> wt((size_t)nt * 6), w(h.tet.size() * 6, 0.0);
+        for_metrics([&](int t, const double(&Gt)[4][4]) {
+            for (int k = 0; k < 6; k++) wt[(size_t)t * 6 + k] = -disc.kappa[t] * Gt[pairs[k][0]][pairs[k][1]];
+        });
+        for (size_t u = 0; u < w.size(); u++)
+            if (h.tet[u / 6] >= 0) w[u] = wt[(size_t)h.tet[u / 6] * 6 + u % 6];
+        std::vector<double> t64(mf_table_size(nl));
+        std::vector<float> t32(t64.size());
+        mf_tables<double>(nl, S.data(), t64.data());
+        mf_tables<float>(nl, S.data(), t32.data());
+        mf_places = (int)h.tet.size();
+        mf_tet = upload(h.tet);
+        mf64 = {n, nl, h.tp, h.npatch, h.max_dofs, (int)h.sh_dof.size(), (const int4 *)upload(h.meta), upload(h.dof),
+                upload(h.range), upload(h.word), upload(h.pos), upload(h.sh_dof), upload(h.sh_ptr), upload(w), upload(t64),
+                dnew<double>(h.sh_ptr.back())};
+        mf32 = {n, nl, h.tp, h.npatch, h.max_dofs, mf64.nshared, mf64.meta, mf64.dof, mf64.range, mf64.word, mf64.pos,
+                mf64.sh_dof, mf64.sh_ptr, upload(to_f32(w)), upload(t32), dnew<float>(h.sh_ptr.back())};
         mf_ready = true;
     }
     template <typename T>
-    MfView<T> mf_view() const
+    const MfView<T> &mf_view() const
     {
-        MfView<T> v{disc.ndof, disc.nt, disc.nloc, mf_emap, nullptr, nullptr, mf_inc_ptr, mf_inc};
-        if constexpr (std::is_same<T, float>::value) {
-            v.w = mf_w32;
-            v.S = mf_S32;
-        } else {
-            v.w = mf_w64;
-            v.S = mf_S64;
-        }
-        return v;
-    }
-    template <typename T>
-    T *mf_Y() const
-    {
-        if constexpr (std::is_same<T, float>::value) return mf_Y32;
-        else return mf_Y64;
+        if constexpr (std::is_same<T, float>::value) return mf32;
+        else return mf64;
     }
     bool use_mf() const { return opt.op == AUX_OP_MATFREE; }
 
@@ -385,20 +383,14 @@ struct aux_handle {
     int pk_sweep(const T *d, const TR *rhs, const T *zin, TZ *zout, const double *rdot, double *partials,
                  const int *done, const int *operm = nullptr, const RrFinish *fin = nullptr)
     {
-        if (use_mf()) {
-            MfView<T> v = mf_view<T>();
-            mf_apply<T>(stream, v, zin, mf_Y<T>(), done);
-            return mf_sweep<T, TR, TZ>(stream, v, mf_Y<T>(), zin, d, rhs, zout, rdot, partials, done);
-        }
+        if (use_mf()) return mf_sweep<T, TR, TZ>(stream, mf_view<T>(), zin, d, rhs, zout, partials, done);
         return sell_sweep<T, T, TR, TZ>(stream, A.view<T>(), d, rhs, zin, zout, rdot, partials, done, operm, fin);
     }
     template <typename T>
     void pk_resid(const T *rhs, const T *z, T *res, const int *done)
     {
         if (use_mf()) {
-            MfView<T> v = mf_view<T>();
-            mf_apply<T>(stream, v, z, mf_Y<T>(), done);
-            mf_resid<T>(stream, v, mf_Y<T>(), rhs, res, done);
+            mf_resid<T>(stream, mf_view<T>(), z, rhs, res, done);
             return;
         }
         sell_resid<T>(stream, A.view<T>(), rhs, z, res, done);
@@ -1449,9 +1441,7 @@ struct aux_handle {
             // q = A_h p by the element operator in FP64 (half the bytes of
             // the assembled product at P3), with the p . q part
             ensure_mf();
-            MfView<double> v = mf_view<double>();
-            mf_apply<double>(s, v, p, mf_Y64, st.done);
-            g = mf_product<double>(s, v, mf_Y64, q, p, part, st.done);
+            g = mf_product(s, mf64, p, q, part, st.done);
         } else if (rs) {
             g = cg_product(s, A.view<double>(), z, odd ? p : p2, pn, q, part, sell_parts(A.view<double>()), part_pq, st);
         } else {
@@ -1703,9 +1693,7 @@ struct aux_handle {
     {
         if (use_mf()) {
             ensure_mf();
-            MfView<double> v = mf_view<double>();
-            mf_apply<double>(stream, v, x, mf_Y64, nullptr);
-            mf_product<double>(stream, v, mf_Y64, y, nullptr, nullptr, nullptr);
+            mf_product(stream, mf64, x, y, nullptr, nullptr);
         } else {
             sell_spmv64(stream, A.view<double>(), x, y, nullptr, nullptr);
         }
@@ -3034,7 +3022,7 @@ struct aux_handle {
         gather_entries(s, (long long)nnzA, asmd.a_ptr, asmd.a_idx, Ke, nullptr, aval, asmd.a_pos, A.v64, A.v32);
         row_l1(s, n, asmd.a_rowptr, aval, l1e);
         if (nnzH) gather_entries(s, (long long)nnzH, asmd.h_ptr, asmd.h_idx, G, kappa_d, hval, nullptr, nullptr, nullptr);
-        if (mf_ready) mf_weights(s, nt, G, kappa_d, mf_w64, mf_w32);
+        if (mf_ready) mf_weights(s, mf_places, mf_tet, G, kappa_d, (double *)mf64.w, (float *)mf32.w);
         // the composite restriction's block -I_R A_h, in place (same pattern)
         if (RF.ptr)
             restrict_values(s, RF.n, n, RF.ptr, RF.col, IR.ptr, IR.col, IR.v64, asmd.a_rowptr, asmd.a_col, aval, perm,

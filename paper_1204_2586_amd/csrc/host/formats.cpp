@@ -309,6 +309,91 @@ Csr permute_rows(const Csr &A, const std::vector<int> &perm)
     return B;
 }
 
+void build_patches(int n, int nt, int nloc, const std::vector<int> &emap, const std::vector<int> &order, int tp,
+                   Patches &out)
+{
+    if (tp % 16 || (int64_t)tp * nloc >= 65535) throw std::invalid_argument("build_patches: places per patch");
+    const int nb = (nloc + 3) / 4;
+    out = Patches();
+    out.tp = tp;
+    const int np = out.npatch = (nt + tp - 1) / tp;
+    std::vector<int> first(np + 1);
+    for (int p = 0; p <= np; p++) first[p] = (int)std::min<int64_t>(nt, (int64_t)p * tp);
+    out.tet.assign((size_t)np * tp, -1);
+    std::vector<std::vector<int>> dofs(np);
+    std::vector<int> patches_of((size_t)n + 1, 0);
+    for_shares(np, (size_t)nt * 8, [&](int pa, int pb) {
+        for (int p = pa; p < pb; p++) {
+            std::copy(order.begin() + first[p], order.begin() + first[p + 1], out.tet.begin() + (size_t)p * tp);
+            std::vector<int> &d = dofs[p];
+            for (int r = first[p]; r < first[p + 1]; r++)
+                for (int a = 0; a < nloc; a++)
+                    if (const int i = emap[(size_t)order[r] * nloc + a]; i >= 0) d.push_back(i);
+            std::sort(d.begin(), d.end());
+            d.erase(std::unique(d.begin(), d.end()), d.end());
+        }
+    });
+    for (const std::vector<int> &d : dofs)
+        for (int i : d) patches_of[i]++;
+    // the shared dofs' partial sums
+    std::vector<int> next(n, -1);
+    out.sh_ptr.push_back(0);
+    for (int i = 0; i < n; i++)
+        if (patches_of[i] > 1) {
+            next[i] = out.sh_ptr.back();
+            out.sh_dof.push_back(i);
+            if (next[i] > 0x7fffffff - patches_of[i]) throw std::invalid_argument("build_patches: too many shared dofs");
+            out.sh_ptr.push_back(next[i] + patches_of[i]);
+        }
+    out.meta.resize((size_t)4 * np);
+    int64_t nd = 0;
+    for (int p = 0; p < np; p++) {
+        std::vector<int> &d = dofs[p];
+        std::stable_partition(d.begin(), d.end(), [&](int i) { return patches_of[i] == 1; });
+        int in = 0;
+        while (in < (int)d.size() && patches_of[d[in]] == 1) in++;
+        const int m[4] = {(int)nd, (int)d.size(), in, (int)out.pos.size()};
+        std::copy(m, m + 4, out.meta.begin() + 4 * (size_t)p);
+        for (size_t i = in; i < d.size(); i++) out.pos.push_back(next[d[i]]++);
+        nd += (int64_t)d.size();
+        if (nd > 0x7fffffff) throw std::invalid_argument("build_patches: too many patch dofs");
+        out.max_dofs = std::max(out.max_dofs, (int)d.size());
+    }
+    out.dof.resize((size_t)nd);
+    out.range.resize((size_t)nd);
+    out.word.resize((size_t)np * tp / 16 * nb * 64);
+    for_shares(np, (size_t)nt * 16, [&](int pa, int pb) {
+        std::vector<int> fill;
+        for (int p = pa; p < pb; p++) {
+            const std::vector<int> &d = dofs[p];
+            const int *m = &out.meta[4 * (size_t)p], cnt = m[1];
+            std::copy(d.begin(), d.end(), out.dof.begin() + m[0]);
+            auto local = [&](int i) {
+                const auto b = patches_of[i] == 1 ? d.begin() : d.begin() + m[2];
+                return (int)(std::lower_bound(b, patches_of[i] == 1 ? d.begin() + m[2] : d.end(), i) - d.begin());
+            };
+            fill.assign((size_t)cnt + 1, 0);
+            for (int r = first[p]; r < first[p + 1]; r++)
+                for (int a = 0; a < nloc; a++)
+                    if (const int i = emap[(size_t)order[r] * nloc + a]; i >= 0) fill[local(i) + 1]++;
+            for (int i = 0; i < cnt; i++) fill[i + 1] += fill[i];
+            for (int i = 0; i < cnt; i++) out.range[(size_t)m[0] + i] = (uint32_t)fill[i] | (uint32_t)fill[i + 1] << 16;
+            for (int t = 0; t < tp; t++)
+                for (int a = 0; a < 4 * nb; a++) {
+                    const int r = first[p] + t;
+                    const int i = r < first[p + 1] && a < nloc ? emap[(size_t)order[r] * nloc + a] : -1;
+                    uint32_t w = 0xffff0000u | (uint32_t)cnt;
+                    if (i >= 0) {
+                        const int l = local(i);
+                        w = (uint32_t)l | (uint32_t)fill[l]++ << 16;
+                    }
+                    const size_t tile = ((size_t)p * tp + t) / 16;
+                    out.word[(tile * nb + a / 4) * 64 + 16 * (a % 4) + t % 16] = w;
+                }
+        }
+    });
+}
+
 std::vector<int> morton_order(const std::vector<double> &xyz, int n)
 {
     double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};

@@ -200,6 +200,30 @@ struct Tiles {
 void build_tiles(const Csr &A, const std::vector<int> &order, const std::vector<int> &iperm, int tile, int cap,
                  Tiles &out);
 
+// Patches of tets for the matrix-free operator.  The tets are taken along a
+// space-filling curve of their centroids, `tp` (a multiple of 16) per patch.  A
+// patch lists its dofs, first those all of whose tets are in the patch (complete: their
+// sums are final), then the shared ones, each group in increasing number; a
+// shared dof's partial sums from its patches are contiguous, in patch order.
+// For the tile of places 16 t .. 16 t + 15, word (nb t + j) 64 + lane belongs
+// to place 16 t + lane % 16 and its node a = 4 j + lane / 16 (nb = ceil(nloc /
+// 4)): the low half is the node's position in the patch's list (the list's
+// length for an eliminated or missing node), the high half its slot in the
+// patch's element results, 0xffff for none; a dof's slots are contiguous.
+struct Patches {
+    int tp = 0, npatch = 0, max_dofs = 0;
+    std::vector<int> tet;           // [npatch tp] tet of each place, -1 past the last
+    std::vector<int> meta;          // per patch: first entry of dof, dofs, complete dofs, first entry of pos
+    std::vector<int> dof;           // the patches' dofs
+    std::vector<uint32_t> range;    // their slots: first, end << 16
+    std::vector<uint32_t> word;
+    std::vector<int> pos;           // shared dofs of the patches: place of the partial sum
+    std::vector<int> sh_dof, sh_ptr;   // shared dofs, and the ranges of their partial sums
+};
+// emap [nt][nloc]: dof of each node, -1 if eliminated; order: tets along the curve
+void build_patches(int n, int nt, int nloc, const std::vector<int> &emap, const std::vector<int> &order, int tp,
+                   Patches &out);
+
 // Rows sorted by decreasing length (stably) within windows of `window` rows;
 // index16 = false stores every slice with plain 32-bit columns.  With
 // permute_cols the columns are renumbered like the rows (a square operator
