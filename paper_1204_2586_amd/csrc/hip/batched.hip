@@ -40,18 +40,32 @@ inline int brows_grid(int n, int NR) { return grid_cap(((long long)n * NR + kBlo
 constexpr int kBatchParts = 2048;
 inline int bsum_grid(int n, int NR) { return std::min(brows_grid(n, NR), kBatchParts); }
 
+// Sums per column over a block of BS threads (thread t holds column t % NR):
+// within the wavefronts by shuffles, then over the wavefronts in a fixed order.
+// The result is valid in threads below NR.  (Summed from LDS by NR threads, the
+// one-workgroup finish was 7.9 us at 8 columns, a chain of 128 reads.)
+template <int NR, int BS>
+__device__ __forceinline__ double col_sums(double v)
+{
+    __shared__ double red[BS / 64][NR];
+#pragma unroll
+    for (int off = 32; off >= NR; off >>= 1) v += __shfl_xor(v, off, 64);
+    const int lane = threadIdx.x & 63;
+    if (lane < NR) red[threadIdx.x >> 6][lane] = v;
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x < NR)
+#pragma unroll
+        for (int w = 0; w < BS / 64; w++) s += red[w][threadIdx.x];
+    return s;
+}
+
 // per-column partial sums of a block of BS threads: partials[blockIdx.x * NR + c]
 template <int NR, int BS = kBlock>
 __device__ void write_col_partials(double *partials, double v)
 {
-    __shared__ double red[BS];
-    red[threadIdx.x] = v;
-    __syncthreads();
-    if (threadIdx.x < NR) {
-        double s = 0.0;
-        for (int i = threadIdx.x; i < BS; i += NR) s += red[i];
-        partials[(size_t)blockIdx.x * NR + threadIdx.x] = s;
-    }
+    const double s = col_sums<NR, BS>(v);
+    if (threadIdx.x < NR) partials[(size_t)blockIdx.x * NR + threadIdx.x] = s;
 }
 
 // ------------------------------------------------------------------ SELL
@@ -519,16 +533,93 @@ __global__ __launch_bounds__(kBlock) void kt_spmv64(DevTilesView A, const double
     if constexpr (DOT) btile_partials<double, NR, TS>(partials, dot);
 }
 
+// The same products where slices are few: a workgroup takes RU rows of a slice
+// and its KG lane groups share each row's entries, so a level of a few
+// thousand long rows (the middle of the hierarchy) spreads over the chip
+// instead of over one workgroup per 64 rows, and a row's chain is KG times
+// shorter.  The groups' sums are added in LDS in a fixed order.
+template <typename T, int NR, int U, typename XL, typename BODY>
+__device__ __forceinline__ void bsell_rows(const DevSellView &A, XL xload, BODY body)
+{
+    constexpr int RU = NR >= 64 ? 4 : 8, KG = kBlock / (RU * NR), UNITS = kSlice / RU, CH = 64;
+    __shared__ T vs[CH * RU];
+    __shared__ int cs[CH * RU];
+    __shared__ T red[kBlock];
+    const T *__restrict__ val = (const T *)A.val;
+    const int c = threadIdx.x % NR, rl = threadIdx.x / NR % RU, kg = threadIdx.x / (NR * RU);
+    for (int u = blockIdx.x; u < A.nslices * UNITS; u += gridDim.x) {
+        const int sl = u / UNITS, row0 = u % UNITS * RU;
+        const int4 m = A.meta[sl];
+        T acc = T(0);
+        for (int j0 = 0; j0 < m.w; j0 += CH) {
+            const int jn = min(CH, m.w - j0), g = threadIdx.x / RU, lane = row0 + (int)threadIdx.x % RU;
+            T vt[4] = {};
+            int ct[4] = {};
+            const bool mine = threadIdx.x < CH / 4 * RU && 4 * g < jn;
+            if (mine) {
+                const size_t at = ((size_t)m.x + j0 / 4 + g) * (4 * kSlice) + 4 * lane;
+#pragma unroll
+                for (int k = 0; k < 4; k++) vt[k] = val[at + k];
+                if (m.z < 0) {
+                    const ushort4 o = *(const ushort4 *)(A.off + at);
+                    const int2 *__restrict__ bs = A.base + ((size_t)m.x + j0 / 4 + g) * 4;
+                    const unsigned short ok[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+                    for (int k = 0; k < 4; k++) ct[k] = (ok[k] & 0x8000 ? bs[k].y : bs[k].x) + (ok[k] & 0x7fff);
+                } else {
+                    const int4 cc = *(const int4 *)(A.wide + ((size_t)m.z + j0 / 4 + g) * (4 * kSlice) + 4 * lane);
+                    ct[0] = cc.x, ct[1] = cc.y, ct[2] = cc.z, ct[3] = cc.w;
+                }
+            }
+            __syncthreads();                           // the previous chunk is consumed
+            if (mine)
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    vs[(4 * g + k) * RU + threadIdx.x % RU] = vt[k];
+                    cs[(4 * g + k) * RU + threadIdx.x % RU] = ct[k];
+                }
+            __syncthreads();
+#pragma unroll U
+            for (int jj = kg; jj < jn; jj += KG) acc += vs[jj * RU + rl] * xload(cs[jj * RU + rl], c);
+        }
+        if (KG > 1) {
+            __syncthreads();                           // the previous unit's sums are read
+            red[threadIdx.x] = acc;
+            __syncthreads();
+            if (kg == 0)
+#pragma unroll
+                for (int k = 1; k < KG; k++) acc += red[threadIdx.x + k * NR * RU];
+        }
+        const int row = sl * kSlice + row0 + rl;
+        if (kg == 0 && row < A.n) body(row, c, acc);
+    }
+}
+
+// Rows of a level operator, shared out one way or the other: split where a
+// workgroup per slice would not fill the 256 compute units four times (twice in
+// FP32).  Measured with 32 columns, FP32 / FP64 us, whole slices -> split: 72
+// slices 38 / 84 -> 18 / 25, 295 slices 27 / 63 -> 19 / 30, restriction of 927
+// slices 60 / 131 -> 64 / 107; with 8 columns, restriction of 43 slices, FP64
+// 39.7 -> 12.1.
+template <typename T, int NR, int U, bool SPLIT, typename XL, typename BODY>
+__device__ __forceinline__ void blevel_rows(const DevSellView &A, XL xload, BODY body)
+{
+    if constexpr (SPLIT) bsell_rows<T, NR, U>(A, xload, body);
+    else bsell_slices<T, NR, U>(A, xload, body);
+}
+template <typename T>
+constexpr int kSplitSlices = sizeof(T) == 8 ? 1024 : 512;
+
 // ------------------------------------------------------- AMG levels, transfers
 // Row-permuted sliced ELL: internal row r of M is row perm[r] of the
 // operator; columns are not renumbered.
 
-template <typename T, int NR, int MODE, int U>   // MODE 0: Y = M X, 1: Y += M X
+template <typename T, int NR, int MODE, int U, bool SPLIT>   // MODE 0: Y = M X, 1: Y += M X
 __global__ __launch_bounds__(kBlock) void kb_lmatvec(DevSellView M, const int *__restrict__ perm,
                                                      const T *__restrict__ X, T *__restrict__ Y, const int *all_done)
 {
     if (stop_all(all_done)) return;
-    bsell_slices<T, NR, U>(M, [&](int j, int c) { return gather32(X, (unsigned)j * NR + c); }, [&](int r, int c, T s) {
+    blevel_rows<T, NR, U, SPLIT>(M, [&](int j, int c) { return gather32(X, (unsigned)j * NR + c); }, [&](int r, int c, T s) {
         size_t o = (size_t)perm[r] * NR + c;
         if (MODE) Y[o] += s;
         else Y[o] = s;
@@ -536,26 +627,26 @@ __global__ __launch_bounds__(kBlock) void kb_lmatvec(DevSellView M, const int *_
 }
 
 // Y = M [X1; X2] (columns below split index X1, the others X2)
-template <typename T, int NR, int U>
+template <typename T, int NR, int U, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void kb_lmatvec2(DevSellView M, const int *__restrict__ perm,
                                                       const T *__restrict__ X1, const T *__restrict__ X2, int split,
                                                       T *__restrict__ Y, const int *all_done)
 {
     if (stop_all(all_done)) return;
-    bsell_slices<T, NR, U>(
+    blevel_rows<T, NR, U, SPLIT>(
         M, [&](int j, int c) { return j < split ? gather32(X1, (unsigned)j * NR + c) : gather32(X2, (unsigned)(j - split) * NR + c); },
         [&](int r, int c, T s) { Y[(size_t)perm[r] * NR + c] = s; });
 }
 
 // X = D^-1 B, R = B - A X, with AD the values of A D^-1: the product
 // gathers B alone (one load per slot keeps the unrolled gathers in flight)
-template <typename T, int NR, int U>
+template <typename T, int NR, int U, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void kb_lvpre(DevSellView AD, const int *__restrict__ perm,
                                                    const T *__restrict__ dinv, const T *__restrict__ B,
                                                    T *__restrict__ X, T *__restrict__ R, const int *all_done)
 {
     if (stop_all(all_done)) return;
-    bsell_slices<T, NR, U>(AD, [&](int j, int c) { return gather32(B, (unsigned)j * NR + c); }, [&](int r, int c, T s) {
+    blevel_rows<T, NR, U, SPLIT>(AD, [&](int j, int c) { return gather32(B, (unsigned)j * NR + c); }, [&](int r, int c, T s) {
         const int i = perm[r];
         size_t o = (size_t)i * NR + c;
         T b = B[o];
@@ -565,57 +656,80 @@ __global__ __launch_bounds__(kBlock) void kb_lvpre(DevSellView AD, const int *__
 }
 
 // Y = X + D^-1 (B - A X)
-template <typename T, int NR, int U>
+template <typename T, int NR, int U, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void kb_lsweep(DevSellView A, const int *__restrict__ perm,
                                                     const T *__restrict__ dinv, const T *__restrict__ B,
                                                     const T *__restrict__ X, T *__restrict__ Y, const int *all_done)
 {
     if (stop_all(all_done)) return;
-    bsell_slices<T, NR, U>(A, [&](int j, int c) { return gather32(X, (unsigned)j * NR + c); }, [&](int r, int c, T s) {
+    blevel_rows<T, NR, U, SPLIT>(A, [&](int j, int c) { return gather32(X, (unsigned)j * NR + c); }, [&](int r, int c, T s) {
         const int i = perm[r];
         size_t o = (size_t)i * NR + c;
         Y[o] = X[o] + dinv[i] * (B[o] - s);
     });
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+// 16x16x4 forms: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and
+// holds D[row][l % 16] in register v
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+template <typename T>
+__device__ __forceinline__ int mfma16_row(int grp, int v) { return sizeof(T) == 4 ? 4 * grp + v : grp + 4 * v; }
+
 // X = M B for a dense row-major n x n matrix M (the coarsest inverse or the
-// dense sub-cycle).  A workgroup takes kDenseRows rows; its KG = kBlock / NR
-// lane groups split the inner index j (group g takes j = g, g + KG, ...), so
-// each lane keeps kDenseRows independent chains of n / KG terms, and the
-// groups' partial sums are added in LDS in a fixed order.
-constexpr int kDenseRows = 4;
+// dense sub-cycle) on the matrix cores.  A workgroup takes 16 rows and (up to)
+// 32 columns; its kDenseWaves wavefronts split the inner index in steps of 16,
+// of which a lane reads four consecutive entries of its row of M (one load)
+// and, for each, its columns' entries of B, and the partial products are added
+// in LDS in a fixed order.  M is read once (twice with 64 columns): 14 MB in
+// FP64 at n = 1340.  Steps past the end multiply zeros.  With 32 columns 154 ->
+// 17.0 us (FP64) and 27.7 -> 18.1 (FP32) at n = 1340, with 8 columns 26.1 -> 8.2 at
+// n = 960 (the vector units before, four rows per workgroup).
+constexpr int kDenseWaves = 8;
 
 template <typename T, int NR>
-__global__ __launch_bounds__(kBlock) void kb_dense(int n, const T *__restrict__ M, const T *__restrict__ B,
-                                                   T *__restrict__ X, const int *all_done)
+__global__ __launch_bounds__(64 * kDenseWaves) void kb_dense(int n, const T *__restrict__ M, const T *__restrict__ B,
+                                                             T *__restrict__ X, const int *all_done)
 {
     if (stop_all(all_done)) return;
-    constexpr int KG = kBlock / NR;
-    __shared__ T red[KG][kDenseRows][NR];
-    const int c = threadIdx.x % NR, g = threadIdx.x / NR;
-    for (int r0 = blockIdx.x * kDenseRows; r0 < n; r0 += gridDim.x * kDenseRows) {
-        T acc[kDenseRows];
+    constexpr int NC = NR < 32 ? NR : 32, CT = (NC + 15) / 16;
+    typedef T V __attribute__((ext_vector_type(4)));
+    __shared__ T red[kDenseWaves][16 * 16 * CT];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int i = lane & 15, g = lane >> 4, r0 = (int)blockIdx.x * 16, col0 = (int)blockIdx.y * NC;
+    const T *__restrict__ row = M + (size_t)min(r0 + i, n - 1) * n;          // clamped rows unused
+    V acc[CT];
 #pragma unroll
-        for (int r = 0; r < kDenseRows; r++) acc[r] = T(0);
-        const T *m[kDenseRows];
+    for (int t = 0; t < CT; t++) acc[t] = V{0, 0, 0, 0};
+#pragma unroll 2
+    for (int k0 = 16 * w; k0 < n; k0 += 16 * kDenseWaves) {
+        T a[4], b[4][CT];
 #pragma unroll
-        for (int r = 0; r < kDenseRows; r++) m[r] = M + (size_t)min(r0 + r, n - 1) * n;   // clamped rows unused
-#pragma unroll 4
-        for (int j = g; j < n; j += KG) {
-            const T b = B[(size_t)j * NR + c];
+        for (int q = 0; q < 4; q++) {
+            const int k = k0 + 4 * g + q, kc = min(k, n - 1);
+            const T m = row[kc];
+            a[q] = k < n ? m : T(0);
 #pragma unroll
-            for (int r = 0; r < kDenseRows; r++) acc[r] += m[r][j] * b;
+            for (int t = 0; t < CT; t++) b[q][t] = B[(size_t)kc * NR + col0 + min(16 * t + i, NC - 1)];
         }
 #pragma unroll
-        for (int r = 0; r < kDenseRows; r++) red[g][r][c] = acc[r];
-        __syncthreads();
-        if (threadIdx.x < kDenseRows * NR) {
-            const int r = threadIdx.x / NR, cc = threadIdx.x % NR;
-            T s = T(0);
-            for (int k = 0; k < KG; k++) s += red[k][r][cc];
-            if (r0 + r < n) X[(size_t)(r0 + r) * NR + cc] = s;
-        }
-        __syncthreads();
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int t = 0; t < CT; t++) acc[t] = mfma16(a[q], b[q][t], acc[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < CT; t++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) red[w][(mfma16_row<T>(g, v) * CT + t) * 16 + i] = acc[t][v];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * 16 * CT; e += 64 * kDenseWaves) {
+        const int r = r0 + e / (16 * CT), c = e % (16 * CT);
+        T s = T(0);
+#pragma unroll
+        for (int k = 0; k < kDenseWaves; k++) s += red[k][e];
+        if (r < n && c < NC) X[(size_t)r * NR + col0 + c] = s;
     }
 }
 
@@ -642,7 +756,6 @@ __global__ __launch_bounds__(kFinishBlock) void kb_finish(const double *__restri
                                                           double *out, BCgState st)
 {
     if (mode != FIN_PLAIN && *st.all_done) return;
-    __shared__ double red[kFinishBlock];
     constexpr int G = kFinishBlock / NR;           // partial rows summed side by side
     const int c = threadIdx.x % NR, g = threadIdx.x / NR;
     // four independent accumulators keep several loads in flight
@@ -655,14 +768,10 @@ __global__ __launch_bounds__(kFinishBlock) void kb_finish(const double *__restri
         s3 += partials[(size_t)(b + 3 * G) * NR + c];
     }
     for (; b < nparts; b += G) s0 += partials[(size_t)b * NR + c];
-    red[threadIdx.x] = (s0 + s1) + (s2 + s3);
-    __syncthreads();
     __shared__ int active_left;
     if (threadIdx.x == 0) active_left = 0;
-    __syncthreads();
+    const double t = col_sums<NR, kFinishBlock>((s0 + s1) + (s2 + s3));   // (a barrier: active_left is set)
     if (threadIdx.x < NR) {
-        double t = 0.0;
-        for (int i = threadIdx.x; i < kFinishBlock; i += NR) t += red[i];
         const int k = *st.k;
         if (mode == FIN_PLAIN) {
             out[c] = t;
@@ -921,27 +1030,41 @@ int bsell_residual64(hipStream_t s, int nr, const DevSellView &A, const double *
 // Four pays off on operators with long rows (the level matrices, the
 // restrictions); on the short rows of the prolongations the extra registers
 // cost more occupancy than the overlap gains.
-#define U_SWITCH(unroll, CALL)             \
-    do {                                   \
-        if ((unroll) >= 4) {               \
-            constexpr int U = 4;           \
-            CALL;                          \
-        } else {                           \
-            constexpr int U = 1;           \
-            CALL;                          \
-        }                                  \
+#define U_SWITCH(unroll, CALL)                                              \
+    do {                                                                    \
+        if ((unroll) >= 4 && blevel_split<T>(nslices_)) {                      \
+            constexpr int U = 4;                                            \
+            constexpr bool SPLIT = true;                                    \
+            CALL;                                                           \
+        } else if ((unroll) >= 4) {                                         \
+            constexpr int U = 4;                                            \
+            constexpr bool SPLIT = false;                                   \
+            CALL;                                                           \
+        } else {                                                            \
+            constexpr int U = 1;                                            \
+            constexpr bool SPLIT = false;                                   \
+            CALL;                                                           \
+        }                                                                   \
     } while (0)
+
+template <typename T>
+inline bool blevel_split(int nslices) { return nslices < kSplitSlices<T>; }
+template <typename T>
+inline int blevel_grid(const DevSellView &A, int unroll)
+{
+    return unroll >= 4 && blevel_split<T>(A.nslices) ? grid_cap(A.nslices * 8LL) : bsell_grid(A);
+}
 
 template <typename T>
 void blevel_matvec(hipStream_t s, int nr, const DevSellView &M, int unroll, const int *perm, const T *X, T *Y,
                    bool add, const int *all_done)
 {
-    int g = bsell_grid(M);
+    const int nslices_ = M.nslices, g = blevel_grid<T>(M, unroll);
     if (add) {
-        U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lmatvec<T, NR, 1, U>), dim3(g), dim3(kBlock), 0, s, M, perm,
+        U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lmatvec<T, NR, 1, U, SPLIT>), dim3(g), dim3(kBlock), 0, s, M, perm,
                                                      X, Y, all_done)));
     } else {
-        U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lmatvec<T, NR, 0, U>), dim3(g), dim3(kBlock), 0, s, M, perm,
+        U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lmatvec<T, NR, 0, U, SPLIT>), dim3(g), dim3(kBlock), 0, s, M, perm,
                                                      X, Y, all_done)));
     }
 }
@@ -950,8 +1073,8 @@ template <typename T>
 void blevel_matvec2(hipStream_t s, int nr, const DevSellView &M, int unroll, const int *perm, const T *X1, const T *X2, int split,
                     T *Y, const int *all_done)
 {
-    int g = bsell_grid(M);
-    U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lmatvec2<T, NR, U>), dim3(g), dim3(kBlock), 0, s, M, perm, X1,
+    const int nslices_ = M.nslices, g = blevel_grid<T>(M, unroll);
+    U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lmatvec2<T, NR, U, SPLIT>), dim3(g), dim3(kBlock), 0, s, M, perm, X1,
                                                  X2, split, Y, all_done)));
 }
 
@@ -959,8 +1082,8 @@ template <typename T>
 void blevel_vpre(hipStream_t s, int nr, const DevSellView &AD, int unroll, const int *perm, const T *dinv, const T *B, T *X, T *R,
                  const int *all_done)
 {
-    int g = bsell_grid(AD);
-    U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lvpre<T, NR, U>), dim3(g), dim3(kBlock), 0, s, AD, perm, dinv,
+    const int nslices_ = AD.nslices, g = blevel_grid<T>(AD, unroll);
+    U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lvpre<T, NR, U, SPLIT>), dim3(g), dim3(kBlock), 0, s, AD, perm, dinv,
                                                  B, X, R, all_done)));
 }
 
@@ -968,19 +1091,16 @@ template <typename T>
 void blevel_sweep(hipStream_t s, int nr, const DevSellView &A, int unroll, const int *perm, const T *dinv, const T *B, const T *X,
                   T *Y, const int *all_done)
 {
-    int g = bsell_grid(A);
-    U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lsweep<T, NR, U>), dim3(g), dim3(kBlock), 0, s, A, perm, dinv,
+    const int nslices_ = A.nslices, g = blevel_grid<T>(A, unroll);
+    U_SWITCH(unroll, NR_SWITCH(nr, hipLaunchKernelGGL((kb_lsweep<T, NR, U, SPLIT>), dim3(g), dim3(kBlock), 0, s, A, perm, dinv,
                                                  B, X, Y, all_done)));
 }
-
-
-
 
 template <typename T>
 void bdense(hipStream_t s, int nr, int n, const T *Ainv, const T *B, T *X, const int *all_done)
 {
-    int g = grid_cap((n + kDenseRows - 1) / kDenseRows);
-    NR_SWITCH(nr, hipLaunchKernelGGL((kb_dense<T, NR>), dim3(g), dim3(kBlock), 0, s, n, Ainv, B, X, all_done));
+    NR_SWITCH(nr, hipLaunchKernelGGL((kb_dense<T, NR>), dim3((n + 15) / 16, NR > 32 ? 2 : 1), dim3(64 * kDenseWaves), 0, s, n,
+                                     Ainv, B, X, all_done));
 }
 
 int bvec_dot(hipStream_t s, int nr, int n, const double *a, const double *b, double *partials)
