@@ -101,15 +101,16 @@ __device__ __forceinline__ T mf_result(T s, T x, T d, TR b)
     else return s;
 }
 
+template <int BS>
 __device__ __forceinline__ void mf_partial(double acc, double *partials)
 {
-    __shared__ double red[kBlock / 64];
+    __shared__ double red[BS / 64];
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         double b = 0.0;
-        for (int w = 0; w < kBlock / 64; w++) b += red[w];
+        for (int w = 0; w < BS / 64; w++) b += red[w];
         *partials = b;
     }
 }
@@ -135,8 +136,8 @@ __device__ __forceinline__ void mf_partial(double acc, double *partials)
 // and 7.2 us (37 and 13.5 before), 12 us of them on the matrix cores.
 // Requesting the sums' inputs before the products took 40 registers more and
 // was slower (P2 48^3 solve 5.47 -> 5.64 ms).
-template <typename T, typename TR, typename TZ, int NLOC, int MODE, bool DOT>
-__global__ __launch_bounds__(kBlock) void k_mf_patch(MfView<T> op, const T *__restrict__ X, const T *__restrict__ dinv,
+template <typename T, typename TR, typename TZ, int NLOC, int BS, int MODE, bool DOT>
+__global__ __launch_bounds__(BS) void k_mf_patch(MfView<T> op, const T *__restrict__ X, const T *__restrict__ dinv,
                                                  const TR *__restrict__ rhs, TZ *__restrict__ out, double *partials,
                                                  const int *done)
 {
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_mf_patch(MfView<T> op, const T *__re
     const T *s4 = sA + MT * KS * 64 + (threadIdx.x >> 4 & 3) * 4 + (threadIdx.x & 3);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     typedef T tv __attribute__((ext_vector_type(PV)));
-    for (int i = threadIdx.x; i < TBL / PV; i += kBlock) ((tv *)sA)[i] = ((const tv *)op.S)[i];
+    for (int i = threadIdx.x; i < TBL / PV; i += BS) ((tv *)sA)[i] = ((const tv *)op.S)[i];
 
     // Each die (workgroups are dispatched round-robin over kDies dies, b to
     // b % kDies) takes a contiguous range of patches, so what neighbouring
@@ -180,26 +181,26 @@ __global__ __launch_bounds__(kBlock) void k_mf_patch(MfView<T> op, const T *__re
         if (w < tiles) request(w);
         __syncthreads();                         // the previous patch is done with xs and ys
         const unsigned *__restrict__ range = op.range + m.x;
-        for (int i0 = threadIdx.x; i0 < m.y; i0 += U * kBlock) {
+        for (int i0 = threadIdx.x; i0 < m.y; i0 += U * BS) {
             int id[U];
             T x[U];
 #pragma unroll
-            for (int u = 0; u < U; u++) id[u] = op.dof[m.x + min(i0 + u * kBlock, m.y - 1)];
+            for (int u = 0; u < U; u++) id[u] = op.dof[m.x + min(i0 + u * BS, m.y - 1)];
 #pragma unroll
             for (int u = 0; u < U; u++) x[u] = X[id[u]];
 #pragma unroll
-            for (int u = 0; u < U; u++) xs[min(i0 + u * kBlock, m.y - 1)] = x[u];
+            for (int u = 0; u < U; u++) xs[min(i0 + u * BS, m.y - 1)] = x[u];
         }
         if (threadIdx.x == 0) xs[m.y] = T(0);
         __syncthreads();
-        for (int tile = w; tile < tiles; tile += kBlock / 64) {
+        for (int tile = w; tile < tiles; tile += BS / 64) {
             unsigned word[NB];
             T wv[6], xv[NB];
 #pragma unroll
             for (int j = 0; j < NB; j++) word[j] = nw[j], xv[j] = xs[nw[j] & 0xffff];
 #pragma unroll
             for (int k = 0; k < 6; k++) wv[k] = nv[k];
-            if (tile + kBlock / 64 < tiles) request(tile + kBlock / 64);
+            if (tile + BS / 64 < tiles) request(tile + BS / 64);
             // B operand: lane (g, c) holds Z[(k, b)][c] = w_c,k x_c,b, formed step by step
             typename Acc<T>::V acc[MT];
             typename Acc<T>::V4 acc4[M4 > 0 ? M4 : 1];
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(kBlock) void k_mf_patch(MfView<T> op, const T *__re
                 op.part[d] = s;
             }
         };
-        for (int i = threadIdx.x; i < m.y; i += kBlock) {
+        for (int i = threadIdx.x; i < m.y; i += BS) {
             const int d = i < m.z ? op.dof[m.x + i] : op.pos[m.w + i - m.z];
             TR rb{};
             T rd{};
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(kBlock) void k_mf_patch(MfView<T> op, const T *__re
             finish(i, d, range[i], rb, rd);
         }
     }
-    if (DOT) mf_partial(acc_dot, partials + blockIdx.x);
+    if (DOT) mf_partial<BS>(acc_dot, partials + blockIdx.x);
 }
 
 // the shared dofs: their partial sums, and the same results
@@ -278,18 +279,21 @@ __global__ __launch_bounds__(kBlock) void k_mf_shared(MfView<T> op, const T *__r
         out[d] = z;
         if (DOT) acc += (MODE == MF_PRODUCT ? (double)x : (double)b) * (double)z;
     }
-    if (DOT) mf_partial(acc, partials + blockIdx.x);
+    if (DOT) mf_partial<kBlock>(acc, partials + blockIdx.x);
 }
 
 template <typename T, typename TR, typename TZ, int NLOC, int MODE, bool DOT>
 int mf_launch(hipStream_t s, const MfView<T> &op, const T *x, const T *dinv, const TR *rhs, TZ *out, double *partials,
               const int *done)
 {
+    // P4's tables (31 and 62 KB) leave room for few workgroups: eight wavefronts
+    // each instead of four (P4 24^3 solve, FP32 / FP64: 12.0 / 18.6 -> 10.5 / 14.0 ms)
+    constexpr int BS = NLOC > 20 ? 512 : kBlock;
     const size_t lds = mf_lds(NLOC, op.tp, op.max_dofs, sizeof(T));
     // one patch per workgroup as far as the partial sums' places go
     const int g = std::max(1, std::min(op.npatch, kMaxBlocks / 4 * 3));
     const int h = std::max(1, std::min((op.nshared + kBlock - 1) / kBlock, kMaxBlocks / 4));
-    hipLaunchKernelGGL((k_mf_patch<T, TR, TZ, NLOC, MODE, DOT>), dim3(g), dim3(kBlock), lds, s, op, x, dinv, rhs, out,
+    hipLaunchKernelGGL((k_mf_patch<T, TR, TZ, NLOC, BS, MODE, DOT>), dim3(g), dim3(BS), lds, s, op, x, dinv, rhs, out,
                        partials, done);
     hipLaunchKernelGGL((k_mf_shared<T, TR, TZ, MODE, DOT>), dim3(h), dim3(kBlock), 0, s, op, x, dinv, rhs, out,
                        DOT ? partials + g : nullptr, done);
