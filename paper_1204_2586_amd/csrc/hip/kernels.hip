@@ -719,30 +719,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_update_prep(int n, double *__rest
     write_partial(partials, acc);
 }
 
-// RESUM: r.z is summed from its rz_n partials as p.q above
-template <bool RESUM>
 __global__ __launch_bounds__(kBlock) void k_cg_direction(int n, const double *__restrict__ z, double *__restrict__ p,
-                                                         CgState st, const double *__restrict__ rz_parts, int rz_n)
+                                                         CgState st)
 {
     if (*st.done) return;
     const int k = *st.iter;
-    double rz;
-    if (RESUM) {
-        rz = partials_sum_all<kBlock>(rz_parts, rz_n);
-        const int bad = product_stop(rz);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            st.rz[k] = rz;
-            if (bad) stop_solve(st, k, bad);
-        }
-        if (bad) return;
-    } else {
-        rz = st.rz[k];
-    }
     if (k == 0) {
         for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = z[i];
         return;
     }
-    const double beta = rz / st.rz[k - 1];
+    const double beta = st.rz[k] / st.rz[k - 1];
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = z[i] + beta * p[i];
 }
 
@@ -1067,13 +1053,9 @@ template int cg_update_prep<double>(hipStream_t, int, double *, double *, const 
                                     const CgState &, double *, const double *, double *, double *, const double *,
                                     int);
 
-void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st, const double *rz_parts, int rz_n)
+void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st)
 {
-    const int g = vec_grid(n);
-    if (rz_n > 0)
-        hipLaunchKernelGGL(k_cg_direction<true>, dim3(g), dim3(kBlock), 0, s, n, z, p, st, rz_parts, rz_n);
-    else
-        hipLaunchKernelGGL(k_cg_direction<false>, dim3(g), dim3(kBlock), 0, s, n, z, p, st, rz_parts, 0);
+    hipLaunchKernelGGL(k_cg_direction, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, z, p, st);
 }
 
 template <typename T>

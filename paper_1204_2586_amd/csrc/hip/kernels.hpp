@@ -48,7 +48,6 @@ struct DevCsrView {
 struct DevSellView {
     int n;               // rows
     int nslices;
-    int max_width;       // longest slice, in slots of 64 entries
     int waves;           // single-vector kernels: wavefronts per slice (1, 2, 4 or 8)
     // per slice: first group (of 4 slots, 256 entries), groups, first group
     // in wide or -1 (16-bit columns), slots in use
@@ -208,10 +207,8 @@ void finish(hipStream_t s, const double *partials, int nparts, FinishMode mode, 
 template <typename T>
 int cg_update_prep(hipStream_t s, int n, double *x, double *r, const double *p, const double *q, const CgState &st,
                    double *partials, const T *dinv, T *z0, T *rT, const double *pq_parts, int pq_n);
-// p = z + beta p, beta = rz[k]/rz[k-1] (p = z at k = 0); rz_n > 0: rz[k] is
-// summed from its partials here
-void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st,
-                  const double *rz_parts = nullptr, int rz_n = 0);
+// p = z + beta p, beta = rz[k]/rz[k-1] (p = z at k = 0)
+void cg_direction(hipStream_t s, int n, const double *z, double *p, const CgState &st);
 // three component blocks of n (stride n) to or from n interleaved elements:
 // y[i].c = x[c n + idx[i]], and y[c n + idx[i]] = x[i].c (idx null: i)
 void vec_interleave3(hipStream_t s, int n, const int *idx, const double *x, Vec3<double> *y);

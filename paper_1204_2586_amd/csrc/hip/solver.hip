@@ -75,7 +75,7 @@ struct DevOp {   // CSR with values in both precisions
 };
 
 struct DevSell {
-    int n = 0, nslices = 0, max_width = 0;
+    int n = 0, nslices = 0;
     int64_t stored = 0, narrow_slices = 0, index_bytes = 0;
     int4 *meta = nullptr;
     int2 *base = nullptr;
@@ -109,7 +109,7 @@ struct DevSell {
     template <typename T>
     DevSellView view() const
     {
-        return {n, nslices, max_width, waves(), meta, base, off, wide,
+        return {n, nslices, waves(), meta, base, off, wide,
                 std::is_same<T, float>::value ? (const void *)v32 : (const void *)v64};
     }
 };
@@ -579,7 +579,6 @@ struct aux_handle {
         DevSell d;
         d.n = sl.n;
         d.nslices = sl.nslices;
-        d.max_width = sl.max_width;
         d.stored = (int64_t)sl.val.size();
         d.narrow_slices = sl.narrow_slices;
         const int group = kSellGroup * sl.slice;

@@ -84,7 +84,6 @@ void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bo
         if (next > 0x7fffffff) throw std::invalid_argument("operator too large for 32-bit ELL offsets");
         out.slice_off[s + 1] = (int)next;
         out.width[s] = w;
-        out.max_width = std::max(out.max_width, w);
     }
     const size_t total = (size_t)out.slice_off.back();
     std::vector<int> col(total);

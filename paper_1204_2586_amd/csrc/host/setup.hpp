@@ -151,7 +151,6 @@ struct Sell {
     std::vector<uint16_t> off;    // [slice_off[nslices]] (empty without 16-bit columns)
     std::vector<int> wide_off;    // [nslices]
     std::vector<int> wide;
-    int max_width = 0;            // longest slice, in slots
     int narrow_slices = 0;        // 16-bit slices whose slots all have a single range (span < 2^16)
     int short_slices = 0;         // slices with 16-bit columns
 };
