@@ -112,15 +112,26 @@ __device__ __forceinline__ double partials_sum(const double *__restrict__ partia
     for (; i < nparts; i += BS) s0 += partials[i];
     return block_sum<BS>((s0 + s1) + (s2 + s3));
 }
-// the same, known to every thread
+// The same, known to every thread; false if the solve has stopped.  The first
+// workgroup of such a launch may set the flag (the sum is what it tests), so
+// the others read it once for all their wavefronts: these leave together or
+// not at all, and then all see the whole sum.
 template <int BS>
-__device__ __forceinline__ double partials_sum_all(const double *__restrict__ partials, int nparts)
+__device__ __forceinline__ bool partials_sum_all(const int *done, const double *__restrict__ partials, int nparts,
+                                                 double &sum)
 {
     __shared__ double total;
+    __shared__ int halt;
+    int d = 0;
+    if (threadIdx.x == 0) d = *done;
     const double s = partials_sum<BS>(partials, nparts);
-    if (threadIdx.x == 0) total = s;
+    if (threadIdx.x == 0) {
+        total = s;
+        halt = d;
+    }
     __syncthreads();
-    return total;
+    sum = total;
+    return halt == 0;
 }
 
 // the stop code an inner product (r.z or p.Ap) gives: 0 to go on
@@ -247,8 +258,12 @@ constexpr int sell_per_block() { return sell_block<W>() / (64 * W); }
 // stop flag `halt` is set (it is tested after the first slice's meta is
 // requested, so the two loads overlap).  With W > 1 the other wavefronts' sums
 // pass through LDS and are added in a fixed order; every thread of the block
-// then runs the same number of steps, so the barriers are uniform.
-template <typename T, typename X, int W, typename XF, typename PRE, typename EPI>
+// then runs the same number of steps, so the barriers are uniform.  SET: the
+// flag may be set while the launch runs, so the wavefronts of a workgroup may
+// read it differently; with W > 1 those that find it set pass the barriers
+// without doing anything (rows that miss their share are not read again: the
+// solve has stopped).
+template <typename T, typename X, int W, bool SET = false, typename XF, typename PRE, typename EPI>
 __device__ __forceinline__ void sell_rows(const DevSellView &A, int grid, int halt, XF x, PRE pre, EPI epi)
 {
     constexpr int S = sell_per_block<W>();
@@ -258,7 +273,8 @@ __device__ __forceinline__ void sell_rows(const DevSellView &A, int grid, int ha
     int4 m = make_int4(0, 0, -1, 0);
     if (sl < A.nslices) m = A.meta[sl];
     asm volatile("" ::"s"(m.x), "s"(halt));
-    if (halt) return;
+    if (halt && (W == 1 || !SET)) return;
+    const bool work = W == 1 || !SET || !halt;
     if constexpr (W == 1) {
         for (; sl < A.nslices; sl += grid * S) {
             if (sl != (int)blockIdx.x * S + q) m = A.meta[sl];
@@ -275,7 +291,7 @@ __device__ __forceinline__ void sell_rows(const DevSellView &A, int grid, int ha
             const int row = sl * kSlice + lane;
             decltype(pre(0)) in = {};
             X s{};
-            if (sl < A.nslices) {
+            if (sl < A.nslices && work) {
                 if (it > 0) m = A.meta[sl];
                 if (h == 0) in = pre(min(row, A.n - 1));
                 s = sell_part<T, X, W>(A, m, lane, h, x);
@@ -283,7 +299,7 @@ __device__ __forceinline__ void sell_rows(const DevSellView &A, int grid, int ha
             if (it > 0) __syncthreads();           // the previous step's sums are consumed
             if (h > 0) part[q][h - 1][lane] = s;
             __syncthreads();
-            if (h == 0 && sl < A.nslices) {
+            if (h == 0 && sl < A.nslices && work) {
 #pragma unroll
                 for (int k = 0; k < W - 1; k++) s += part[q][k][lane];
                 if (row < A.n) epi(row, s, in);
@@ -330,7 +346,7 @@ __global__ __launch_bounds__(sell_block<W>()) void k_sell_sweep(DevSellView A, c
         double r;
         int o;
     };
-    sell_rows<T, X, W>(
+    sell_rows<T, X, W, FIN>(
         A, grid, halt, [&](int j) { return at32(zin, j); },
         [&](int row) {
             return In{zin[row], cast<X>(rhs[row]), dinv[row], DOT ? rdot[row] : 0.0, operm ? operm[row] : row};
@@ -393,9 +409,9 @@ __global__ __launch_bounds__(sell_block<W>()) void k_cg_product(DevSellView A, c
                                                                 const double *__restrict__ rz_parts, int rz_n,
                                                                 double *__restrict__ pq_parts, CgState st)
 {
-    if (*st.done) return;
     const int k = *st.iter;
-    const double rz = partials_sum_all<sell_block<W>()>(rz_parts, rz_n);
+    double rz;
+    if (!partials_sum_all<sell_block<W>()>(st.done, rz_parts, rz_n, rz)) return;
     const int bad = product_stop(rz);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st.rz[k] = rz;
@@ -691,11 +707,10 @@ __global__ __launch_bounds__(kBlock) void k_cg_update_prep(int n, double *__rest
                                                            T *__restrict__ z0, T *__restrict__ rT,
                                                            const double *__restrict__ pq_parts, int pq_n)
 {
-    if (*st.done) return;
     const int k = *st.iter;
     double pq;
     if (RESUM) {
-        pq = partials_sum_all<kBlock>(pq_parts, pq_n);
+        if (!partials_sum_all<kBlock>(st.done, pq_parts, pq_n, pq)) return;
         const int bad = product_stop(pq);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             st.pq[k] = pq;
@@ -703,6 +718,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update_prep(int n, double *__rest
         }
         if (bad) return;
     } else {
+        if (*st.done) return;
         pq = st.pq[k];
     }
     const double alpha = st.rz[k] / pq;

@@ -67,9 +67,15 @@ __device__ __forceinline__ void write_pair(double a, double b, double *partials,
         if (two) partials[kMaxBlocks + blockIdx.x] = b;
     }
 }
-// the sums of n partials (and of the second set) in every thread
-__device__ __forceinline__ void sum_pair(const double *__restrict__ partials, int n, bool two, double &a, double &b)
+// The sums of n partials (and of the second set) in every thread; false if the
+// solve has stopped.  The first workgroup may set the flag in the launch that
+// tests it here, so a workgroup reads it once for all its wavefronts, which
+// then leave together or all see the whole sums.
+__device__ __forceinline__ bool sum_pair(const int *done, const double *__restrict__ partials, int n, bool two, double &a,
+                                         double &b)
 {
+    __shared__ int halt;
+    if (threadIdx.x == 0) halt = *done;
     a = b = 0.0;
 #pragma unroll 4
     for (int i = threadIdx.x; i < n; i += kBlock) {
@@ -77,6 +83,7 @@ __device__ __forceinline__ void sum_pair(const double *__restrict__ partials, in
         if (two) b += partials[kMaxBlocks + i];
     }
     block_pair(a, b);
+    return halt == 0;
 }
 
 // The head of step k by every workgroup alike: r.r and r.z of the residual
@@ -86,9 +93,8 @@ __device__ __forceinline__ void sum_pair(const double *__restrict__ partials, in
 __device__ __forceinline__ bool mass_head(const double *__restrict__ partials, int n, int k, double tol2,
                                           const CgState &st, double &beta)
 {
-    if (*st.done) return false;
     double rr, rz;
-    sum_pair(partials, n, true, rr, rz);
+    if (!sum_pair(st.done, partials, n, true, rr, rz)) return false;
     const double target = k > 0 ? st.scal[2] : tol2 * rr;
     int d = 0;
     if (!std::isfinite(rr)) d = 4;
@@ -191,9 +197,8 @@ __global__ __launch_bounds__(kBlock) void k_mass_update(int n, double *__restric
                                                         const double *__restrict__ pq_parts, int nparts, int k,
                                                         double *__restrict__ partials, CgState st)
 {
-    if (*st.done) return;
     double pq, none;
-    sum_pair(pq_parts, nparts, false, pq, none);
+    if (!sum_pair(st.done, pq_parts, nparts, false, pq, none)) return;
     const int bad = !std::isfinite(pq) ? 4 : !(pq > 0.0) ? 3 : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st.pq[k] = pq;
