@@ -107,10 +107,18 @@ void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bo
                     out.val[at] = A.val[row[j].second];
                 }
             }
-            // the two ranges of every slot; padding entries (value 0) take
-            // the slot's first column, empty slots column 0
+            // Padding entries (value 0) repeat the last column of their own
+            // row, so that an Inf or NaN in a vector meets only the rows that
+            // have it.  (A row without entries takes its slot's first column.)
+            const int slots = (int)((e1 - e0) / slice);
+            for (int r = r0; r < r1; r++) {
+                const int last = len(out.perm[r]) - 1;
+                for (int j = last + 1; last >= 0 && j < slots; j++)
+                    col[sell_pos(e0, j, r - r0)] = col[sell_pos(e0, last, r - r0)];
+            }
+            // the two ranges of every slot
             char k = 0;
-            for (int j = 0; j < (int)((e1 - e0) / slice); j++) {
+            for (int j = 0; j < slots; j++) {
                 int64_t lo = INT32_MAX, hi = -1, second = INT32_MAX;
                 for (int l = 0; l < slice; l++) {
                     const int c = col[sell_pos(e0, j, l)];
@@ -262,10 +270,16 @@ void build_tiles(const Csr &A, const std::vector<int> &order, const std::vector<
                 const int r = arow[(size_t)t * tile + i];
                 if (r < 0) continue;
                 const size_t b0 = (size_t)out.grp_off[(size_t)t * groups + i / 8] * 64 + 8 * (i % 8);
-                for (int e = A.ptr[r], j = 0; e < A.ptr[r + 1]; e++, j++) {
+                // padding entries repeat the row's last column
+                const int g = t * groups + i / 8, padded = 8 * (out.grp_off[(size_t)g + 1] - out.grp_off[g]);
+                uint16_t p = 0;
+                for (int e = A.ptr[r], j = 0; j < padded; e++, j++) {
                     const size_t at = b0 + 64 * (size_t)(j / 8) + j % 8;
-                    out.lidx[at] = (uint16_t)(std::lower_bound(c.begin(), c.end(), iperm[A.col[e]]) - c.begin());
-                    out.val[at] = A.val[e];
+                    if (e < A.ptr[r + 1]) {
+                        p = (uint16_t)(std::lower_bound(c.begin(), c.end(), iperm[A.col[e]]) - c.begin());
+                        out.val[at] = A.val[e];
+                    }
+                    out.lidx[at] = p;
                 }
             }
         }

@@ -141,7 +141,7 @@ struct Sell {
     std::vector<int> iperm;       // original row -> internal row
     std::vector<int> slice_off;   // [nslices+1] first stored entry, multiples of 4 * slice
     std::vector<int> width;       // [nslices] longest row of the slice
-    std::vector<double> val;      // padding 0
+    std::vector<double> val;      // padding 0, at a column of the row
     // Columns.  Slot t (the t-th group of `slice` entries with one j) has two
     // bases; entry e of a slice with wide_off[s] < 0 has column
     // base[2 t + (off[e] >> 15)] + (off[e] & 0x7fff).  A slice with a slot
@@ -182,7 +182,7 @@ void build_ell(const Csr &A, int lanes, Ell &out);
 // numbering), so a workgroup can stage the gathered block rows once per tile,
 // and each entry stores the 16-bit position of its column in that list.  A tile's rows are
 // sorted by length and taken in groups of eight, padded to blocks of eight
-// entries (value 0, position 0): entry e of row r of a group is entry
+// entries (value 0, the row's last position): entry e of row r of a group is entry
 // 64 (block of e / 8) + 8 r + e % 8.
 struct Tiles {
     int n = 0, tile = 0, ntiles = 0;
