@@ -67,8 +67,9 @@ __global__ __launch_bounds__(kAsmBlock) void k_gather_entries(long long nnz, con
         }
         val[e] = v;
         if (pos) {
-            v64[pos[e]] = v;
-            v32[pos[e]] = (float)v;
+            const unsigned p = (unsigned)pos[e];
+            v64[p] = v;
+            v32[p] = (float)v;
         }
     }
 }

@@ -584,10 +584,11 @@ struct aux_handle {
         const int group = kSellGroup * sl.slice;
         std::vector<int4> meta((size_t)sl.nslices);
         for (int s = 0; s < sl.nslices; s++) {
-            const int entries = sl.slice_off[s + 1] - sl.slice_off[s];
+            const int64_t entries = sl.slice_off[s + 1] - sl.slice_off[s];
             const bool wide = sl.wide_off[s] >= 0;
-            meta[s] = make_int4(sl.slice_off[s] / group, entries / group, wide ? sl.wide_off[s] / group : -1, sl.width[s]);
-            d.index_bytes += wide ? 4 * (int64_t)entries : 2 * (int64_t)entries + 8 * (int64_t)(entries / sl.slice);
+            meta[s] = make_int4((int)(sl.slice_off[s] / group), (int)(entries / group),
+                                wide ? (int)(sl.wide_off[s] / group) : -1, sl.width[s]);
+            d.index_bytes += wide ? 4 * entries : 2 * entries + 8 * (entries / sl.slice);
         }
         d.meta = upload(meta);
         d.base = (int2 *)upload(sl.base);
@@ -2900,7 +2901,7 @@ struct aux_handle {
     // after a coefficient update the host copies of A_h (CSR and sliced-ELL
     // values) and of the composite restriction's values are fetched from
     // the device only when a host-side consumer needs them
-    std::vector<int> a_pos_host;     // sliced-ELL slot of each CSR entry of A_h
+    std::vector<int> a_pos_host;     // sliced-ELL slot of each CSR entry of A_h (unsigned)
     bool host_vals_stale = false;
     void ensure_host_values()
     {
@@ -2911,7 +2912,7 @@ struct aux_handle {
             HIPCHECK(hipMemcpyAsync(RF_host.val.data(), RF.v64, RF_host.val.size() * sizeof(double),
                                     hipMemcpyDeviceToHost, stream));
         HIPCHECK(hipStreamSynchronize(stream));
-        for (size_t e = 0; e < disc.A.val.size(); e++) disc.A.val[e] = sell.val[a_pos_host[e]];
+        for (size_t e = 0; e < disc.A.val.size(); e++) disc.A.val[e] = sell.val[(uint32_t)a_pos_host[e]];
         host_vals_stale = false;
     }
 

@@ -57,6 +57,18 @@ void for_shares(int n, size_t work, F f)
 
 }  // namespace
 
+std::vector<int64_t> sell_offsets(const std::vector<int> &width, int slice)
+{
+    std::vector<int64_t> off(width.size() + 1, 0);
+    int64_t entries = 0;
+    for (size_t s = 0; s < width.size(); s++) {
+        entries += (int64_t)width[s] * slice;
+        off[s + 1] = off[s] + (int64_t)((width[s] + kSellGroup - 1) / kSellGroup) * kSellGroup * slice;
+    }
+    if (entries > 0x7fffffff) throw std::invalid_argument("operator too large for 32-bit ELL offsets");
+    return off;
+}
+
 void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bool permute_cols)
 {
     if (slice != 64) throw std::invalid_argument("build_sell: slices of 64 rows");
@@ -74,17 +86,10 @@ void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bo
     out.iperm.assign(n, 0);
     for (int i = 0; i < n; i++) out.iperm[out.perm[i]] = i;
     const int ns = out.nslices = (n + slice - 1) / slice;
-    out.slice_off.assign((size_t)ns + 1, 0);
     out.width.assign(ns, 0);
-    const int gsz = kSellGroup * slice;
-    for (int s = 0; s < ns; s++) {
-        int w = 0;
-        for (int r = s * slice; r < std::min(n, (s + 1) * slice); r++) w = std::max(w, len(out.perm[r]));
-        const int64_t next = (int64_t)out.slice_off[s] + (int64_t)((w + kSellGroup - 1) / kSellGroup) * gsz;
-        if (next > 0x7fffffff) throw std::invalid_argument("operator too large for 32-bit ELL offsets");
-        out.slice_off[s + 1] = (int)next;
-        out.width[s] = w;
-    }
+    for (int s = 0; s < ns; s++)
+        for (int r = s * slice; r < std::min(n, (s + 1) * slice); r++) out.width[s] = std::max(out.width[s], len(out.perm[r]));
+    out.slice_off = sell_offsets(out.width, slice);
     const size_t total = (size_t)out.slice_off.back();
     std::vector<int> col(total);
     out.val.resize(total);
@@ -157,7 +162,7 @@ void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bo
         out.narrow_slices += kind[s] == 0;
         out.short_slices += kind[s] < 2;
         if (kind[s] == 2) {
-            out.wide_off[s] = (int)wide;
+            out.wide_off[s] = wide;
             wide += out.slice_off[s + 1] - out.slice_off[s];
         }
     }
@@ -170,13 +175,14 @@ void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bo
 
 std::vector<int> sell_positions(const Csr &A, const Sell &s)
 {
+    if (s.slice_off.back() > (int64_t)UINT32_MAX) throw std::invalid_argument("sell_positions: too many entries");
     std::vector<int> pos(A.col.size());
     for_shares(s.n, A.col.size() / 8, [&](int a, int b) {
         std::vector<std::pair<int, int>> row;
         for (int r = a; r < b; r++) {
             row_entries(A, s.perm[r], s.iperm.data(), row);
             for (int j = 0; j < (int)row.size(); j++)
-                pos[row[j].second] = (int)sell_pos((size_t)s.slice_off[r / s.slice], j, r % s.slice);
+                pos[row[j].second] = (int)(uint32_t)sell_pos((size_t)s.slice_off[r / s.slice], j, r % s.slice);
         }
     });
     return pos;

@@ -139,7 +139,7 @@ struct Sell {
     int n = 0, slice = 64, nslices = 0;
     std::vector<int> perm;        // internal row -> original row
     std::vector<int> iperm;       // original row -> internal row
-    std::vector<int> slice_off;   // [nslices+1] first stored entry, multiples of 4 * slice
+    std::vector<int64_t> slice_off;   // [nslices+1] first stored entry, multiples of 4 * slice
     std::vector<int> width;       // [nslices] longest row of the slice
     std::vector<double> val;      // padding 0, at a column of the row
     // Columns.  Slot t (the t-th group of `slice` entries with one j) has two
@@ -149,7 +149,7 @@ struct Sell {
     // first at wide[wide_off[s]], in the order of the entries.
     std::vector<int> base;        // [2 slice_off[nslices] / slice]
     std::vector<uint16_t> off;    // [slice_off[nslices]] (empty without 16-bit columns)
-    std::vector<int> wide_off;    // [nslices]
+    std::vector<int64_t> wide_off;    // [nslices]
     std::vector<int> wide;
     int narrow_slices = 0;        // 16-bit slices whose slots all have a single range (span < 2^16)
     int short_slices = 0;         // slices with 16-bit columns
@@ -230,7 +230,12 @@ void build_patches(int n, int nt, int nloc, const std::vector<int> &emap, const 
 // increasing internal column; otherwise only the rows move (results go to row
 // perm[r]) and entries keep their order.
 void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bool permute_cols = true);
-// place of every entry of A (CSR order) in its layout built with permute_cols
+// first entry of each slice from the slices' widths, and their end.  At most
+// 2^31 - 1 entries, not counting what fills up the groups (offsets are kept
+// in 64 bits, on the device in groups)
+std::vector<int64_t> sell_offsets(const std::vector<int> &width, int slice);
+// place of every entry of A (CSR order) in its layout built with
+// permute_cols, as unsigned 32-bit numbers
 std::vector<int> sell_positions(const Csr &A, const Sell &s);
 // rows of A in the order perm (row r of the result is row perm[r] of A)
 Csr permute_rows(const Csr &A, const std::vector<int> &perm);
