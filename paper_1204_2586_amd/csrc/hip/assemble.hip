@@ -3,7 +3,8 @@
 // sum_T kappa_T int_T grad phi_j . grad phi_i).
 //
 // Everything that depends on the mesh alone is set up once: the tet metrics
-// G_T[p][q] = |T| grad lambda_p . grad lambda_q, the reference tables M^pq,
+// G_T[p][q] = |T| grad lambda_p . grad lambda_q (ten of them: G_T is
+// symmetric to the bit), the reference tables M^pq,
 // the sparsity patterns and, for every entry, the list of element-matrix
 // entries that sum into it in increasing tet order.  The passes here repeat
 // the host assembly's arithmetic in its order (element matrix
@@ -26,6 +27,9 @@ inline int asm_grid(long long n)
     return (int)(g < 1 ? 1 : (g > 65536 ? 65536 : g));
 }
 
+// column of G_t[p][q], p q = 4 p + q, in the metrics (see assemble.hpp)
+__device__ constexpr int kMetricCol[16] = {6, 0, 1, 2, 0, 7, 3, 4, 1, 3, 8, 5, 2, 4, 5, 9};
+
 // Ke[(t nl + a) nl + b] = sum_pq (kappa_t G_t[pq]) M[pq][a nl + b]
 __global__ __launch_bounds__(kAsmBlock) void k_element_matrices(int nt, int nl, const double *__restrict__ G,
                                                                 const double *__restrict__ kappa,
@@ -38,8 +42,9 @@ __global__ __launch_bounds__(kAsmBlock) void k_element_matrices(int nt, int nl, 
         const int t = (int)(u / n2), i = (int)(u % n2);
         const double kap = kappa[t];
         double K = 0.0;
+#pragma unroll
         for (int pq = 0; pq < 16; pq++) {
-            const double g = kap * G[(size_t)t * 16 + pq];
+            const double g = kap * G[(size_t)kMetricCol[pq] * nt + t];
             K += g * M[(size_t)pq * n2 + i];
         }
         Ke[u] = K;
@@ -47,13 +52,13 @@ __global__ __launch_bounds__(kAsmBlock) void k_element_matrices(int nt, int nl, 
 }
 
 // val[e] = sum of src[idx[c]] over c in [ptr[e], ptr[e+1]), in order; with
-// scale, src[idx[c]] is scale[idx[c] / 16] * src[idx[c]] (the P^1 stiffness:
-// kappa_t G_t[pq]).  With pos, the value is also written to v64[pos[e]] and,
+// scale (nt values), src[idx[c]] is scale[idx[c] % nt] * src[idx[c]] (the P^1
+// stiffness: kappa_t G_t[pq], G by column).  With pos, the value is also written to v64[pos[e]] and,
 // rounded, v32[pos[e]].
 __global__ __launch_bounds__(kAsmBlock) void k_gather_entries(long long nnz, const int *__restrict__ ptr,
                                                               const int *__restrict__ idx,
                                                               const double *__restrict__ src,
-                                                              const double *__restrict__ scale,
+                                                              const double *__restrict__ scale, int nt,
                                                               double *__restrict__ val, const int *__restrict__ pos,
                                                               double *__restrict__ v64, float *__restrict__ v32)
 {
@@ -63,7 +68,7 @@ __global__ __launch_bounds__(kAsmBlock) void k_gather_entries(long long nnz, con
         double v = 0.0;
         for (int c = ptr[e]; c < ptr[e + 1]; c++) {
             const int j = idx[c];
-            v += scale ? scale[j / 16] * src[j] : src[j];
+            v += scale ? scale[j % nt] * src[j] : src[j];
         }
         val[e] = v;
         if (pos) {
@@ -89,16 +94,15 @@ __global__ __launch_bounds__(kAsmBlock) void k_row_l1(int n, const int *__restri
 // matrix-free weights w[p][k] = -kappa_t G_t[p_k][q_k] of the tet t of place p
 // (0 at an empty place) over the six vertex pairs (0,1) (0,2) (0,3) (1,2)
 // (1,3) (2,3)
-__global__ __launch_bounds__(kAsmBlock) void k_mf_weights(int places, const int *__restrict__ tet,
+__global__ __launch_bounds__(kAsmBlock) void k_mf_weights(int nt, int places, const int *__restrict__ tet,
                                                           const double *__restrict__ G,
                                                           const double *__restrict__ kappa, double *__restrict__ w64,
                                                           float *__restrict__ w32)
 {
-    const int pq[6] = {1, 2, 3, 6, 7, 11};
     for (long long u = (long long)blockIdx.x * kAsmBlock + threadIdx.x; u < 6LL * places;
          u += (long long)gridDim.x * kAsmBlock) {
         const int t = tet[u / 6], k = (int)(u % 6);
-        const double v = t >= 0 ? -kappa[t] * G[(size_t)t * 16 + pq[k]] : 0.0;
+        const double v = t >= 0 ? -kappa[t] * G[(size_t)k * nt + t] : 0.0;
         w64[u] = v;
         w32[u] = (float)v;
     }
@@ -163,9 +167,9 @@ void element_matrices(hipStream_t s, int nt, int nl, const double *G, const doub
 }
 
 void gather_entries(hipStream_t s, long long nnz, const int *ptr, const int *idx, const double *src,
-                    const double *scale, double *val, const int *pos, double *v64, float *v32)
+                    const double *scale, int nt, double *val, const int *pos, double *v64, float *v32)
 {
-    hipLaunchKernelGGL(k_gather_entries, dim3(asm_grid(nnz)), dim3(kAsmBlock), 0, s, nnz, ptr, idx, src, scale, val,
+    hipLaunchKernelGGL(k_gather_entries, dim3(asm_grid(nnz)), dim3(kAsmBlock), 0, s, nnz, ptr, idx, src, scale, nt, val,
                        pos, v64, v32);
 }
 
@@ -174,9 +178,11 @@ void row_l1(hipStream_t s, int n, const int *ptr, const double *val, double *l1)
     hipLaunchKernelGGL(k_row_l1, dim3(asm_grid(n)), dim3(kAsmBlock), 0, s, n, ptr, val, l1);
 }
 
-void mf_weights(hipStream_t s, int places, const int *tet, const double *G, const double *kappa, double *w64, float *w32)
+void mf_weights(hipStream_t s, int nt, int places, const int *tet, const double *G, const double *kappa, double *w64,
+                float *w32)
 {
-    hipLaunchKernelGGL(k_mf_weights, dim3(asm_grid(6LL * places)), dim3(kAsmBlock), 0, s, places, tet, G, kappa, w64, w32);
+    hipLaunchKernelGGL(k_mf_weights, dim3(asm_grid(6LL * places)), dim3(kAsmBlock), 0, s, nt, places, tet, G, kappa, w64,
+                       w32);
 }
 
 void restrict_values(hipStream_t s, int nrows, int n, const int *rf_ptr, const int *rf_col, const int *ir_ptr,

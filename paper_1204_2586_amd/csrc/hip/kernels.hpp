@@ -220,8 +220,8 @@ void vec_scatter(hipStream_t s, int n, const int *idx, const double *x, double *
 
 // g_t = -kappa_t sum_pq G_pq lam_t^T M^pq u_t per tet (FP64).  By column (entry
 // a of tet t at a nt + t): dofs, the tets' dof numbers (-1 on the boundary);
-// G6, the metrics of the vertex pairs (0,1) (0,2) (0,3) (1,2) (1,3) (2,3).
-// S: the pairs' symmetric tables S^k = M^pp + M^qq - M^pq - M^qp: for each pair
+// G6, the metrics of the vertex pairs (0,1) (0,2) (0,3) (1,2) (1,3) (2,3) (the
+// first columns of those that the coefficient update reads).  S: the pairs' symmetric tables S^k = M^pp + M^qq - M^pq - M^qp: for each pair
 // of rows (2 m, 2 m + 1) and column b >= 2 m the six entries of the first row,
 // then of the second (zero below the diagonal and past the last row), the
 // diagonal's halved.

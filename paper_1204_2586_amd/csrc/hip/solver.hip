@@ -278,9 +278,10 @@ struct aux_handle {
     double last_ff = 0.0;
     std::vector<void *> host_bufs;   // other pinned buffers
 
-    // adjoint data (external dof numbering); the gradient's by column
-    double *G = nullptr, *kappa_d = nullptr, *Mtab = nullptr;
-    double *grad_G6 = nullptr, *grad_S = nullptr;
+    // adjoint data (external dof numbering): the tet metrics, which the
+    // coefficient update and the gradient share, and the gradient's dofs, by
+    // column
+    double *G = nullptr, *kappa_d = nullptr, *Mtab = nullptr, *grad_S = nullptr;
     int *grad_dofs = nullptr;
 
     // matrix-free element operator (internal dof numbering)
@@ -306,19 +307,25 @@ struct aux_handle {
         }
         return S;
     }
-    // tet_metric of every tet: f(t, G_t), tets shared among the host threads
+    // f(t) for every tet, shared among the host threads
     template <typename F>
-    void for_metrics(F f) const
+    void for_tets(F f) const
     {
         const int nt = disc.nt, parts = setup_threads((size_t)nt * 8);
         run_tasks(parts, [&](int part) {
-            for (int t = (int)((int64_t)nt * part / parts); t < (int)((int64_t)nt * (part + 1) / parts); t++) {
-                const int *v = &disc.tets[4 * (size_t)t];
-                double Gt[4][4];
-                tet_metric(&disc.xyz[3 * (size_t)v[0]], &disc.xyz[3 * (size_t)v[1]], &disc.xyz[3 * (size_t)v[2]],
-                           &disc.xyz[3 * (size_t)v[3]], Gt);
-                f(t, Gt);
-            }
+            for (int t = (int)((int64_t)nt * part / parts); t < (int)((int64_t)nt * (part + 1) / parts); t++) f(t);
+        });
+    }
+    // the same with its tet_metric: f(t, G_t)
+    template <typename F>
+    void for_metrics(F f) const
+    {
+        for_tets([&](int t) {
+            const int *v = &disc.tets[4 * (size_t)t];
+            double Gt[4][4];
+            tet_metric(&disc.xyz[3 * (size_t)v[0]], &disc.xyz[3 * (size_t)v[1]], &disc.xyz[3 * (size_t)v[2]],
+                       &disc.xyz[3 * (size_t)v[3]], Gt);
+            f(t, Gt);
         });
     }
 
@@ -2933,6 +2940,9 @@ struct aux_handle {
         std::vector<int> vmap((size_t)nt * 4);
         for (size_t q = 0; q < vmap.size(); q++) vmap[q] = disc.vert_dof[disc.tets[q]];
         assembly_map(disc.AH, nt, 4, vmap.data(), ptr, idx);
+        int col[16];
+        for (int pq = 0; pq < 16; pq++) col[pq] = metric_col(pq / 4, pq % 4);
+        for (int &j : idx) j = col[j % 16] * nt + j / 16;      // its place in the metrics
         asmd.h_ptr = upload(ptr);
         asmd.h_idx = upload(idx);
         asmd.h_rowptr = upload(disc.AH.ptr);
@@ -3019,10 +3029,10 @@ struct aux_handle {
         double *Ke = dnew<double>((size_t)nt * nl * nl);
         double *aval = dnew<double>(nnzA), *l1e = dnew<double>(n), *hval = dnew<double>(std::max<size_t>(nnzH, 1));
         element_matrices(s, nt, nl, G, kappa_d, Mtab, Ke);
-        gather_entries(s, (long long)nnzA, asmd.a_ptr, asmd.a_idx, Ke, nullptr, aval, asmd.a_pos, A.v64, A.v32);
+        gather_entries(s, (long long)nnzA, asmd.a_ptr, asmd.a_idx, Ke, nullptr, nt, aval, asmd.a_pos, A.v64, A.v32);
         row_l1(s, n, asmd.a_rowptr, aval, l1e);
-        if (nnzH) gather_entries(s, (long long)nnzH, asmd.h_ptr, asmd.h_idx, G, kappa_d, hval, nullptr, nullptr, nullptr);
-        if (mf_ready) mf_weights(s, mf_places, mf_tet, G, kappa_d, (double *)mf64.w, (float *)mf32.w);
+        if (nnzH) gather_entries(s, (long long)nnzH, asmd.h_ptr, asmd.h_idx, G, kappa_d, nt, hval, nullptr, nullptr, nullptr);
+        if (mf_ready) mf_weights(s, nt, mf_places, mf_tet, G, kappa_d, (double *)mf64.w, (float *)mf32.w);
         // the composite restriction's block -I_R A_h, in place (same pattern)
         if (RF.ptr)
             restrict_values(s, RF.n, n, RF.ptr, RF.col, IR.ptr, IR.col, IR.v64, asmd.a_rowptr, asmd.a_col, aval, perm,
@@ -3104,24 +3114,41 @@ struct aux_handle {
     {
         if (!kappa_d) kappa_d = upload(disc.kappa);
     }
-    void ensure_adjoint()
+    // column of G_t[p][q] in the metrics (see assemble.hpp)
+    static int metric_col(int p, int q)
+    {
+        if (p == q) return 6 + p;
+        int k = 0;
+        while (pairs[k][0] != std::min(p, q) || pairs[k][1] != std::max(p, q)) k++;
+        return k;
+    }
+    void ensure_metrics()
     {
         if (G) return;
-        std::vector<double> g((size_t)disc.nt * 16);
-        for_metrics([&](int t, const double(&Gt)[4][4]) { std::memcpy(&g[(size_t)t * 16], Gt, sizeof(Gt)); });
+        const int nt = disc.nt;
+        std::vector<double> g((size_t)nt * 10);
+        for_metrics([&](int t, const double(&Gt)[4][4]) {
+            for (int k = 0; k < 6; k++) g[(size_t)k * nt + t] = Gt[pairs[k][0]][pairs[k][1]];
+            for (int p = 0; p < 4; p++) g[(size_t)(6 + p) * nt + t] = Gt[p][p];
+        });
+        G = upload(g);
+    }
+    void ensure_adjoint()
+    {
+        if (Mtab) return;
+        ensure_metrics();
         ensure_kappa_device();
         Mtab = upload(stiffness_tables(disc.k));
-        G = upload(g);
     }
     // the gradient's arrays (see kappa_grad)
     void ensure_gradient()
     {
         if (grad_dofs) return;
         const int nt = disc.nt, nl = disc.nloc;
-        std::vector<double> g((size_t)nt * 6), S;
+        ensure_metrics();
+        std::vector<double> S;
         std::vector<int> dofs((size_t)nt * nl);
-        for_metrics([&](int t, const double(&Gt)[4][4]) {
-            for (int k = 0; k < 6; k++) g[(size_t)k * nt + t] = Gt[pairs[k][0]][pairs[k][1]];
+        for_tets([&](int t) {
             for (int a = 0; a < nl; a++) dofs[(size_t)a * nt + t] = disc.tet_dof[(size_t)t * nl + a];
         });
         const std::vector<double> T = pair_tables();
@@ -3131,7 +3158,6 @@ struct aux_handle {
                     for (int k = 0; k < 6; k++)
                         S.push_back(a >= nl || b < a ? 0.0 : T[((size_t)a * 6 + k) * nl + b] * (a == b ? 0.5 : 1.0));
         ensure_kappa_device();
-        grad_G6 = upload(g);
         grad_S = upload(S);
         grad_dofs = upload(dofs);
     }
@@ -3752,7 +3778,7 @@ int aux_kappa_grad(aux_handle *h, const double *u, const double *lam, double *g)
         if (!u || !lam || !g) throw AuxError(AUX_EINVAL, "null vector");
         set_dev(h);
         h->ensure_gradient();
-        kappa_grad(h->stream, h->disc.nt, h->disc.nloc, h->grad_dofs, h->grad_G6, h->kappa_d, h->grad_S, u, lam, g);
+        kappa_grad(h->stream, h->disc.nt, h->disc.nloc, h->grad_dofs, h->G, h->kappa_d, h->grad_S, u, lam, g);
         HIPCHECK(hipGetLastError());
         return AUX_OK;
     });
