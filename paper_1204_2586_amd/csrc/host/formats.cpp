@@ -39,11 +39,16 @@ void sort_window(int w0, int w1, Len len, std::vector<int> &perm)
     for (int i = w0; i < w1; i++) perm[w0 + at[top - len(i)]++] = i;
 }
 
-// the entries of original row i as (column in the layout, entry), in the layout's order
-void row_entries(const Csr &A, int i, const int *iperm, std::vector<std::pair<int, int>> &out)
+// the entries of original row i in the layout's order: column in the layout,
+// and in the low half the entry
+void row_entries(const Csr &A, int i, const int *iperm, std::vector<uint64_t> &out)
 {
-    out.clear();
-    for (int e = A.ptr[i]; e < A.ptr[i + 1]; e++) out.push_back({iperm ? iperm[A.col[e]] : A.col[e], e});
+    const int n = A.ptr[i + 1] - A.ptr[i];
+    out.resize(n);
+    for (int q = 0; q < n; q++) {
+        const int e = A.ptr[i] + q;
+        out[q] = (uint64_t)(uint32_t)(iperm ? iperm[A.col[e]] : A.col[e]) << 32 | (uint32_t)e;
+    }
     if (iperm) std::sort(out.begin(), out.end());
 }
 
@@ -98,7 +103,7 @@ void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bo
     std::vector<char> kind(ns, 2);             // 0: one range per slot, 1: two, 2: 32-bit columns
     const int *ip = permute_cols ? out.iperm.data() : nullptr;
     for_shares(ns, A.col.size() / 8, [&](int sa, int sb) {
-        std::vector<std::pair<int, int>> row;
+        std::vector<uint64_t> row;
         for (int s = sa; s < sb; s++) {
             const size_t e0 = (size_t)out.slice_off[s], e1 = (size_t)out.slice_off[s + 1];
             const int r0 = s * slice, r1 = std::min(n, r0 + slice);
@@ -108,8 +113,8 @@ void build_sell(const Csr &A, int slice, int window, bool index16, Sell &out, bo
                 row_entries(A, out.perm[r], ip, row);
                 for (int j = 0; j < (int)row.size(); j++) {
                     const size_t at = sell_pos(e0, j, r - r0);
-                    col[at] = row[j].first;
-                    out.val[at] = A.val[row[j].second];
+                    col[at] = (int)(row[j] >> 32);
+                    out.val[at] = A.val[(uint32_t)row[j]];
                 }
             }
             // Padding entries (value 0) repeat the last column of their own
@@ -178,11 +183,11 @@ std::vector<int> sell_positions(const Csr &A, const Sell &s)
     if (s.slice_off.back() > (int64_t)UINT32_MAX) throw std::invalid_argument("sell_positions: too many entries");
     std::vector<int> pos(A.col.size());
     for_shares(s.n, A.col.size() / 8, [&](int a, int b) {
-        std::vector<std::pair<int, int>> row;
+        std::vector<uint64_t> row;
         for (int r = a; r < b; r++) {
             row_entries(A, s.perm[r], s.iperm.data(), row);
             for (int j = 0; j < (int)row.size(); j++)
-                pos[row[j].second] = (int)(uint32_t)sell_pos((size_t)s.slice_off[r / s.slice], j, r % s.slice);
+                pos[(uint32_t)row[j]] = (int)(uint32_t)sell_pos((size_t)s.slice_off[r / s.slice], j, r % s.slice);
         }
     });
     return pos;
