@@ -22,6 +22,7 @@
 
 #include "../host/parallel.hpp"
 #include "../host/setup.hpp"
+#include "../host/wait.hpp"
 #include "aux.h"
 #include "amgsetup.hpp"
 #include "assemble.hpp"
@@ -1602,6 +1603,7 @@ struct aux_handle {
             // wait for the stop, or until only two enqueued iterations are left
             const int most = std::min(issued, maxit);
             double ratio = 0.0;
+            Polling poll;
             for (int spin = 1;; spin++) {
                 const unsigned long long w = __atomic_load_n(&cg_report->word, __ATOMIC_RELAXED);
                 iter = (int)(w >> 32 & 0xfffffff);
@@ -1611,6 +1613,7 @@ struct aux_handle {
                 std::memcpy(&fr, &bits, sizeof(fr));
                 ratio = fr;
                 if (done || (iter > seen_iter && iter >= std::min(most, limit - 2))) break;
+                poll.pause();
                 if (spin % 4096 == 0) {
                     const hipError_t e = hipStreamQuery(s);
                     if (e == hipSuccess) {              // drained: the report is complete
