@@ -700,7 +700,9 @@ struct aux_handle {
         partials = dnew<double>(kMaxBlocks);
         scal = dnew<double>(8);
         istate = dnew<int>(4);
-        HIPCHECK(hipHostMalloc((void **)&cg_report, sizeof(CgReport), hipHostMallocDefault));
+        // coherent: the host reads it while the kernels that write it still run
+        // (the default kind is that only as long as HIP_HOST_COHERENT says so)
+        HIPCHECK(hipHostMalloc((void **)&cg_report, sizeof(CgReport), hipHostMallocCoherent));
         HIPCHECK(hipHostMalloc((void **)&host_scal, 8 * sizeof(double), hipHostMallocDefault));
         ensure_hist(std::max(opt.maxit, 16));
     }

@@ -14,3 +14,10 @@ def test_polling_gives_up_the_core(tmp_path):
     solver = open(os.path.join(ROOT, "paper_1204_2586_amd", "csrc", "hip", "solver.hip")).read()
     loop = solver[solver.index("__atomic_load_n(&cg_report->word"):]
     assert "poll.pause();" in loop[:loop.index("limit = iter + kAhead")]
+
+
+def test_report_is_coherent_memory():
+    """The report is read while kernels write it, which only coherent host memory promises."""
+    solver = open(os.path.join(ROOT, "paper_1204_2586_amd", "csrc", "hip", "solver.hip")).read()
+    call = solver[solver.index("hipHostMalloc((void **)&cg_report"):]
+    assert "hipHostMallocCoherent" in call[:call.index(";")]
