@@ -178,8 +178,7 @@ typedef struct aux_info {
     int64_t level_nnz_P[32]; /* entries of the interpolation P_l from level l+1 to level l
                                 (0 on the coarsest level) */
     int64_t sell_slices;     /* 64-row slices of the device A_h */
-    int64_t sell_narrow_slices; /* of which have 16-bit columns that span less than 2^16 in every
-                                slot (one range; the other 16-bit slices use two) */
+    int64_t sell_narrow_slices; /* of which store 16-bit columns */
     int64_t sell_index_bytes; /* bytes of the column stream one product reads: 2 per stored
                                 entry of a 16-bit slice plus 8 per slot for its bases, 4 per
                                 stored entry of a 32-bit slice */
@@ -196,9 +195,9 @@ typedef struct aux_info {
      * L > 0 row-split sliced ELL with L lanes per row (64 / L rows per
      * wavefront), -L CSR with L lanes per row. */
     int32_t dense_cycle_level; /* first level evaluated by the dense cycle matrix, -1 if none */
-    int32_t sell_split;      /* 1: slices of at least 56 slots on average (wide: their
-                                single-vector passes share a slice among two to eight
-                                wavefronts; short slices do so only where they are few) */
+    int32_t sell_split;      /* 1: slices of at least 56 slots on average (how many wavefronts
+                                share a slice in the single-vector passes, 1 to 8, depends on
+                                their number too) */
     int32_t lanes_restrict;  /* fused restriction [I_R, -I_R A_h] (0 if not fused) */
     int32_t lanes_prolong;   /* I_P; 0: fixed-width column-major slots (its rows have 1 to 4
                                 entries; the default unless cycle_lanes forces a storage) */

@@ -588,7 +588,7 @@ struct aux_handle {
         d.n = sl.n;
         d.nslices = sl.nslices;
         d.stored = (int64_t)sl.val.size();
-        d.narrow_slices = sl.narrow_slices;
+        d.narrow_slices = sl.short_slices;
         const int group = kSellGroup * sl.slice;
         std::vector<int4> meta((size_t)sl.nslices);
         for (int s = 0; s < sl.nslices; s++) {
