@@ -1,6 +1,7 @@
 """aux_info counts the slices that store 16-bit columns, in one range or two."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime, before the library's)
 
 import paper_1204_2586_amd as aux
 import workloads as W
