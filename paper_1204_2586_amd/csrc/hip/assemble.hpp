@@ -6,7 +6,7 @@
 namespace auxp {
 
 // Tet metrics G_t[p][q], by column: ten columns of nt, the vertex pairs (0,1)
-// (0,2) (0,3) (1,2) (1,3) (2,3), then the diagonal.
+// (0,2) (0,3) (1,2) (1,3) (2,3), which the gradient reads too, then the diagonal.
 
 // Ke [nt][nl][nl] = kappa_t sum_pq G_t[pq] M^pq (M [16][nl*nl])
 void element_matrices(hipStream_t s, int nt, int nl, const double *G, const double *kappa, const double *M, double *Ke);
