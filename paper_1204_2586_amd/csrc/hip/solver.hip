@@ -332,8 +332,9 @@ struct aux_handle {
 
     // Tets per patch.  Large ones have fewer shared dofs and fill the tables'
     // LDS better; 512 patches are two per compute unit, and with fewer the
-    // chain of one patch shows.  Solves, ms, with 32 / 64 / 128 / 256: P2 48^3
-    // mixed 7.30, 6.03, 5.47, 5.35; P2 8^3 0.78, 0.78, 0.83, 1.24; P3 32^3 mixed
+    // chain of one patch shows.  Solves on cubes without jitter, kappa = 1, ms,
+    // with 32 / 64 / 128 / 256: P2 48^3 mixed 7.30, 6.03, 5.47, 5.35 (assembled
+    // 5.31); P2 8^3 0.78, 0.78, 0.83, 1.24; P3 32^3 mixed
     // 7.51, 6.30, 5.86; P3 24^3 FP64 5.34, 4.40, 4.12; P3 8^3 1.51, 1.57, 1.77;
     // P4 24^3 FP64 17.5, 15.7, 14.0; P4 18^3 FP64 9.47, 8.56, 8.94; P4 14^3 FP64
     // 6.25, 5.95, 7.66; P4 6^3 4.15, 4.18, 5.80.
